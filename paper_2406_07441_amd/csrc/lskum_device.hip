@@ -5,7 +5,7 @@
 //   k_qgrad<...>   x (1 + m)        q-derivatives, eq. (16): first-order pass and
 //                                   m inner passes; the optional limiter is
 //                                   applied in the last pass
-//   k_residual<...>                 LSKUM residual eq. (11), (15); local time
+//   k_residual[_tiled]<...>         LSKUM residual eq. (11), (15); local time
 //                                   step and scalar diagonal eq. (25), (34)-(35);
 //                                   per-point linearisation data for the sweeps
 //   k_norm_partial, k_norm_comp     density residual norm per component and the
@@ -101,8 +101,10 @@ __device__ __forceinline__ void split_flux(const Prim& w, double dx, double dy, 
     (void)inv_gm1;
     const double ud = DIR == 0 ? w.u1 : (DIR == 1 ? w.u2 : w.u1 * dx + w.u2 * dy);
     const double S = ud * w.sb;
-    const double A = 0.5 * (1.0 + sg * erf_fast(S));
-    const double B = exp_fast(-(S * S)) * (0.5 * kInvSqrtPi) * w.isb;
+    double er, g;
+    erf_exp(S, er, g);
+    const double A = 0.5 * (1.0 + sg * er);
+    const double B = g * (0.5 * kInvSqrtPi) * w.isb;
     const double mass = w.rho * (ud * A + sg * B);
     const double pA = w.p * A;
     G[0] = mass;
@@ -117,16 +119,6 @@ __device__ __forceinline__ void split_flux(const Prim& w, double dx, double dy, 
         G[2] = pA * dy + w.u2 * mass;
     }
     G[3] = (w.rhoE + w.p) * ud * A + sg * (w.rhoE + 0.5 * w.p) * B;
-}
-
-template <int DIR>
-__device__ __forceinline__ void acc_split_diff(const Prim& wi, const Prim& w0, double dx, double dy,
-                                               double sg, double wgt, double inv_gm1, double R[4]) {
-    double Gi[4], G0[4];
-    split_flux<DIR>(wi, dx, dy, sg, inv_gm1, Gi);
-    split_flux<DIR>(w0, dx, dy, sg, inv_gm1, G0);
-#pragma unroll
-    for (int v = 0; v < 4; ++v) R[v] += wgt * (Gi[v] - G0[v]);
 }
 
 // ---------------------------------------------------------------------------
@@ -695,53 +687,190 @@ __device__ __forceinline__ Nbr load_nbr(int32_t i, const D2* __restrict__ xy,
     return {xy[i], q[i], qx[i], qy[i]};
 }
 
+// One end of a stencil pair: the weighted sum of its split fluxes along the
+// two split directions of the point,
+//   sum_d w_d G_d^{sg_d},   d = x, y (interior) or t, n (frame points),
+// from a reconstructed q vector.  The primitive state is that of prim_from_q;
+// with A_d = (1 + sg_d erf S_d)/2, B_d = exp(-S_d^2)/(2 sqrt(pi beta)) and
+//   P = sum_d w_d u_d A_d,   Q = sum_d w_d sg_d B_d,   F = P + Q,
+// the mass term is rho F, the momentum term sum_d w_d p A_d d + u rho F and
+// the energy term (rhoE + p) P + (rhoE + p/2) Q = p ((1/(gamma-1) + 1/2 +
+// beta |u|^2) F + P/2), since rhoE = p (1/(gamma-1) + beta |u|^2).  The two
+// directions share everything but A, B: 18 instructions after the functions
+// where two separate fluxes took about 60.  hw_d = w_d/2 and hs_d = sg_d w_d/2.
+// Written in explicit fused steps with contraction off, so that both ends of a
+// pair round alike (a uniform field's residual is exactly zero).
+// 1/sqrt(x) for x > 0; for x <= 0, infinite or NaN the split fluxes end as NaN
+// with this as with a guarded function, so it has no guard (four instructions
+// fewer of ten).
+__device__ __forceinline__ double rsqrt_pos(double x) {
+    const double y = __builtin_amdgcn_rsq(x);
+    const double e = fma(-x * y, y, 1.0);
+    return fma(y * e, fma(e, 0.375, 0.5), y);
+}
+
+// v for s < 0, -v for s > 0 (the sign of the split that offset s lies in)
+__device__ __forceinline__ double flip_by(double v, double s) {
+    const uint64_t sign = (uint64_t)1 << 63;
+    return __longlong_as_double((int64_t)((uint64_t)__double_as_longlong(v) ^
+                                          (~(uint64_t)__double_as_longlong(s) & sign)));
+}
+
+__device__ __forceinline__ void unit_or_outer(double S, double t, const PolyLead& lead, double& er,
+                                              double& g) {  // g scaled by e^(1/2)
+    if (t < 1.0) {
+        erf_exp_unit(S, t, lead, er, g);
+    } else {  // fast flow (or a non-physical state)
+        erf_exp_outer(S, t, er, g);
+        g *= 1.0 / kExpHalf;
+    }
+}
+
+template <bool FRAME, bool G14>
+__device__ __forceinline__ D4 end_sum(const D4& q, const D2& t, double hwa, double hsa,
+                                      double hwb, double hsb, double inv_gm1,
+                                      const PolyLead& lead) {
+#pragma clang fp contract(off)
+    const double beta = -0.5 * q.w;
+    const double r = rsqrt_pos(beta);
+    const double r2 = r * r, i2b = 0.5 * r2;
+    const double u1 = q.y * i2b, u2 = q.z * i2b;
+    const double sb = beta * r;  // sqrt(beta)
+    const double ua = FRAME ? fma(u1, t.x, u2 * t.y) : u1;
+    const double ub = FRAME ? fma(u2, t.x, -(u1 * t.y)) : u2;
+    const double Sa = ua * sb, Sb = ub * sb;
+    const double ta = Sa * Sa, tb = Sb * Sb;
+    const double bu = FRAME ? beta * fma(u1, u1, u2 * u2) : ta + tb;
+    double era, ga, erb, gb;
+    unit_or_outer(Sa, ta, lead, era, ga);
+    unit_or_outer(Sb, tb, lead, erb, gb);
+    const double e = exp_lead(q.x + bu, lead);
+    const double rho = G14 ? e * (r2 * r2 * r) : e * exp(-inv_gm1 * log(beta));
+    const double p = rho * i2b;
+    const double aa = fma(hsa, era, hwa), ab = fma(hsb, erb, hwb);  // w A
+    const double P = fma(ua, aa, ub * ab);
+    const double F = fma(fma(hsa, ga, hsb * gb), r * (kInvSqrtPi * kExpHalf), P);
+    const double M = rho * F;
+    const double pa = FRAME ? fma(aa, t.x, -(ab * t.y)) : aa;
+    const double pb = FRAME ? fma(aa, t.y, ab * t.x) : ab;
+    return {M, fma(p, pa, u1 * M), fma(p, pb, u2 * M),
+            p * fma((inv_gm1 + 0.5) + bu, F, 0.5 * P)};
+}
+
 // One (point, neighbour) pair of the residual sum (eq. 11): the q~
 // reconstructions at both ends (eq. 15), their primitive states and the split
 // flux differences of every split the neighbour lies in (x+-/y+- at interior
 // points, t+-/n- at a wall), weighted by the point's split coefficients.
-__device__ __forceinline__ void residual_pair(int8_t ty, const D2& t, const D2& r0, const D4& q0,
-                                              const D4& gx0, const D4& gy0, const D2& c0,
-                                              const D2& c1, const D2& c2, const D2& c3,
-                                              const Nbr& nb, double inv_gm1, bool g14,
-                                              double Rp[4], int& bad) {
-    const double dx = nb.r.x - r0.x, dy = nb.r.y - r0.y;
-    const D4 qi = nb.q, gxi = nb.gx, gyi = nb.gy;
-    const D4 qti = {qi.x - 0.5 * (dx * gxi.x + dy * gyi.x), qi.y - 0.5 * (dx * gxi.y + dy * gyi.y),
-                    qi.z - 0.5 * (dx * gxi.z + dy * gyi.z), qi.w - 0.5 * (dx * gxi.w + dy * gyi.w)};
-    const D4 qt0 = {q0.x - 0.5 * (dx * gx0.x + dy * gy0.x), q0.y - 0.5 * (dx * gx0.y + dy * gy0.y),
-                    q0.z - 0.5 * (dx * gx0.z + dy * gy0.z), q0.w - 0.5 * (dx * gx0.w + dy * gy0.w)};
-    if (ty != kInterior) {  // wall, or an outer point under the kinetic far field
-        const double ds = dot_nc(dx, dy, t.x, t.y);
-        const double dn = dot_nc(dx, dy, -t.y, t.x);
-        const bool in_t = ds != 0.0, in_n = in_normal_split(ty, dn);
-        if (!in_t && !in_n) return;
-        bad |= !(qti.w < 0.0) || !(qt0.w < 0.0);
-        const Prim wi = prim_from_q(qti, inv_gm1, g14);
-        const Prim w0 = prim_from_q(qt0, inv_gm1, g14);
-        if (in_t) {
-            const D2 c = ds < 0.0 ? c0 : c1;
-            const double sg = ds < 0.0 ? 1.0 : -1.0;
-            acc_split_diff<2>(wi, w0, t.x, t.y, sg, c.x * ds + c.y * dn, inv_gm1, Rp);
-        }
-        if (in_n)
-            acc_split_diff<2>(wi, w0, -t.y, t.x, ty == kWall ? -1.0 : 1.0, c2.x * dn + c2.y * ds,
-                              inv_gm1, Rp);
-        return;
+// A split that the neighbour is not in has weight zero.
+// q~ = q - (dx q_x + dy q_y)/2 from hx = -dx/2, hy = -dy/2 (eq. 15)
+__device__ __forceinline__ D4 reconstruct(const D4& q, const D4& gx, const D4& gy, double hx,
+                                          double hy) {
+    return {fma(hy, gy.x, fma(hx, gx.x, q.x)), fma(hy, gy.y, fma(hx, gx.y, q.y)),
+            fma(hy, gy.z, fma(hx, gx.z, q.z)), fma(hy, gy.w, fma(hx, gx.w, q.w))};
+}
+
+// The longest tile list that the tiled residual stages: 18 KiB per block, so
+// that a CU holds seven blocks; a 16 x 4 block of points with 5 x 5 stencils
+// lists 160 points.
+constexpr int kResidualTile = 160;
+constexpr int kResidualMinTiles = 256;  // one block per CU
+
+// Everything a residual launch reads and writes.
+struct ResidualArgs {
+    int64_t n;
+    double gamma;
+    const double* cfl;
+    const D2* xy;
+    const D2* frame;
+    const int8_t* type;
+    const int32_t* off;
+    const int32_t* idx;
+    const PointGeom* geom;
+    const int32_t* comp;
+    const int32_t* active;
+    const int32_t* tile_pts;  // the LDS tiles of lskum_tiles.h (tiled kernel only)
+    const uint16_t* lnbr;
+    const int32_t* tile_off;
+    const int32_t* tile_idx;
+    const D4* U;
+    const D4* q;
+    const D4* qx;
+    const D4* qy;
+    D4* R;
+    double* Dg;
+    D4* jv0;
+    D4* jv2;
+    F4* jv0f;
+    F4* jv2f;
+    float* Df;
+    double* rr_out;
+    int32_t* flags;
+    int variant, fd;
+    D4* dUio;
+    F4* dUfio;
+    D4* Rs;
+    const int32_t* colour;
+    int sweep0, farfield;
+    const double* vinf;
+};
+
+// A residual sum and whether one of its q~ had beta <= 0.
+struct ResidualSum {
+    double x, y, z, w;
+    bool bad;
+};
+
+// The pair (point, neighbour at offset (dx, dy)) added to R; coef[k * stride]
+// is the point's split coefficient k.
+template <bool FRAME, bool G14>
+__device__ __forceinline__ void pair_add(double dx, double dy, const D4& qti, const D4& qt0,
+                                         const D2& t, int8_t ty, const D2* coef, int stride,
+                                         double inv_gm1, const PolyLead& lead, ResidualSum& R) {
+#pragma clang fp contract(off)
+    double da = dx, db = dy;
+    if (FRAME) {
+        da = dot_nc(dx, dy, t.x, t.y);
+        db = dot_nc(dx, dy, -t.y, t.x);
     }
-    const bool in_x = dx != 0.0, in_y = dy != 0.0;
-    if (!in_x && !in_y) return;
-    bad |= !(qti.w < 0.0) || !(qt0.w < 0.0);
-    const Prim wi = prim_from_q(qti, inv_gm1, g14);
-    const Prim w0 = prim_from_q(qt0, inv_gm1, g14);
-    if (in_x) {
-        const D2 c = dx < 0.0 ? c0 : c1;
-        const double sg = dx < 0.0 ? 1.0 : -1.0;
-        acc_split_diff<0>(wi, w0, 1.0, 0.0, sg, c.x * dx + c.y * dy, inv_gm1, Rp);
+    const bool in_a = da != 0.0, in_b = FRAME ? in_normal_split(ty, db) : db != 0.0;
+    if (!in_a && !in_b) return;
+    const D2 ca = coef[da < 0.0 ? 0 : stride];
+    const D2 cb = coef[FRAME || db < 0.0 ? 2 * stride : 3 * stride];
+    const double wa = 0.5 * fma(ca.x, da, ca.y * db), wb = 0.5 * fma(cb.x, db, cb.y * da);
+    const double hwa = in_a ? wa : 0.0, hwb = in_b ? wb : 0.0;
+    const double hsa = flip_by(hwa, da), hsb = flip_by(hwb, db);
+    R.bad |= !(qti.w < 0.0) || !(qt0.w < 0.0);
+    const D4 ci = end_sum<FRAME, G14>(qti, t, hwa, hsa, hwb, hsb, inv_gm1, lead);
+    const D4 c0 = end_sum<FRAME, G14>(qt0, t, hwa, hsa, hwb, hsb, inv_gm1, lead);
+    R.x += ci.x - c0.x;
+    R.y += ci.y - c0.y;
+    R.z += ci.z - c0.z;
+    R.w += ci.w - c0.w;
+}
+
+// The walk of a lane over its entries of a point's list, compiled apart for
+// interior and frame points (a wavefront of interior points then holds no
+// registers for frames) and for gamma = 1.4: W<FRAME, G14>.
+template <class Walk>
+__device__ __forceinline__ ResidualSum residual_walks(int8_t ty, bool g14, Walk walk) {
+    if (g14) {
+        if (ty == kInterior) return walk(std::false_type{}, std::true_type{});
+        return walk(std::true_type{}, std::true_type{});
     }
-    if (in_y) {
-        const D2 c = dy < 0.0 ? c2 : c3;
-        const double sg = dy < 0.0 ? 1.0 : -1.0;
-        acc_split_diff<1>(wi, w0, 0.0, 1.0, sg, c.x * dy + c.y * dx, inv_gm1, Rp);
+    if (ty == kInterior) return walk(std::false_type{}, std::false_type{});
+    return walk(std::true_type{}, std::false_type{});
+}
+
+// Sum over the lanes of a point, by every lane.
+template <int LANES>
+__device__ __forceinline__ void residual_lane_sum(ResidualSum& R) {
+#pragma unroll
+    for (int o = LANES / 2; o > 0; o >>= 1) {
+        R.x += __shfl_xor(R.x, o, 64);
+        R.y += __shfl_xor(R.y, o, 64);
+        R.z += __shfl_xor(R.z, o, 64);
+        R.w += __shfl_xor(R.w, o, 64);
+        R.bad |= __shfl_xor((int)R.bad, o, 64) != 0;
     }
 }
 
@@ -749,245 +878,393 @@ __device__ __forceinline__ void residual_pair(int8_t ty, const D2& t, const D2& 
 // Residual (eq. 11 with the q~ reconstruction of eq. 15), local time step,
 // scalar diagonal (eq. 25, 34-35) and the sweep linearisation data.
 // ---------------------------------------------------------------------------
-// LANES consecutive lanes share one point: each takes every LANES-th
-// neighbour, the four residual sums are combined with cross-lane shuffles and
-// the first lane finishes the point.
+// The kernel's arguments, and loads and stores through pointers among them,
+// for code after a long loop: the arguments are read from the kernel-argument
+// segment again (a second look that the compiler does not merge with the
+// first), where holding them through the loop would spill scalar registers
+// into vector lanes and cost a vector instruction for each one's way back.
+typedef const __attribute__((address_space(4))) ResidualArgs KernArgs;
+
+__device__ __forceinline__ KernArgs& reread_args() {
+    auto* k = (KernArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(k));
+    return *k;
+}
+
+template <class T>
+struct Raw { using type = T; };
+template <>
+struct Raw<D4> { typedef double type __attribute__((ext_vector_type(4))); };
+template <>
+struct Raw<D2> { typedef double type __attribute__((ext_vector_type(2))); };
+template <>
+struct Raw<F4> { typedef float type __attribute__((ext_vector_type(4))); };
+
+template <class T>
+__device__ __forceinline__ T gload(const T* p, int64_t i) {
+    using V = typename Raw<T>::type;
+    const V v = *(const __attribute__((address_space(1))) V*)(p + i);
+    return __builtin_bit_cast(T, v);
+}
+template <class T>
+__device__ __forceinline__ void gstore(T* p, int64_t i, const T& v) {
+    using V = typename Raw<T>::type;
+    *(__attribute__((address_space(1))) V*)(p + i) = __builtin_bit_cast(V, v);
+}
+
+// What follows a point's sum over its neighbours: wall tangency, the far
+// field's ghost, R and its square, linearisation data, time step, diagonal and
+// the forward sweep's first colour phase.
+template <bool MIXED>
+__device__ __forceinline__ void residual_finish(int64_t p, int8_t ty, const ResidualSum& sum,
+                                                double inv_gm1, bool g14) {
+    KernArgs& A = reread_args();
+    double Rp[4] = {sum.x, sum.y, sum.z, sum.w};
+    const bool bad = sum.bad;
+    const D2 t = gload(A.frame, p);
+    const bool part = ty != kOuter || A.farfield;  // outer points: kinetic far field only
+    if (ty == kWall) {  // drop the normal-momentum component
+        const double nx = -t.y, ny = t.x;
+        const double mn = Rp[1] * nx + Rp[2] * ny;
+        Rp[1] -= mn * nx;
+        Rp[2] -= mn * ny;
+    }
+    if (ty == kOuter && A.farfield) {
+        // kinetic far field: the n- half (molecules entering the domain)
+        // from a free-stream ghost one nearest-neighbour distance outside,
+        // (G_n-(U_inf) - G_n-(U_0)) / h with the point's own q
+        const int k = A.comp ? gload(A.comp, p) : 0;
+        const double v1 = gload(A.vinf, 2 * k), v2 = gload(A.vinf, 2 * k + 1);
+        Prim wf;
+        wf.rho = 1.0;
+        wf.u1 = v1;
+        wf.u2 = v2;
+        wf.p = 1.0 / A.gamma;
+        wf.sb = sqrt(0.5 * A.gamma);
+        wf.isb = 1.0 / wf.sb;
+        wf.rhoE = wf.p * inv_gm1 + 0.5 * (v1 * v1 + v2 * v2);
+        const Prim w0 = prim_from_q(gload(A.q, p), inv_gm1, g14);
+        double Gf[4], G0[4];
+        split_flux<2>(wf, -t.y, t.x, -1.0, inv_gm1, Gf);
+        split_flux<2>(w0, -t.y, t.x, -1.0, inv_gm1, G0);
+        const double ih = 1.0 / gload(&A.geom[p].lsq, 0).w;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) Rp[v] += (Gf[v] - G0[v]) * ih;
+    }
+    gstore(A.rr_out, p, ty != kOuter ? Rp[0] * Rp[0] : 0.0);
+    gstore(A.R, p, D4{Rp[0], Rp[1], Rp[2], Rp[3]});
+
+    // linearisation data at the current state, local time step, diagonal
+    const D4 u = gload(A.U, p);
+    const double rho = u.x, irho = 1.0 / rho;
+    const double u1 = u.y * irho, u2 = u.z * irho;
+    const double usq = u1 * u1 + u2 * u2;
+    const double pr = (A.gamma - 1.0) * (u.w - 0.5 * rho * usq);
+    const double beta = 0.5 * rho / pr;
+    const double sb = sqrt(beta);
+    const double sx = u1 * sb, sy = u2 * sb;
+    const D4 j0 = {rho, u1, u2, pr};
+    D4 j2;
+    erf_exp(sx, j2.x, j2.y);
+    erf_exp(sy, j2.z, j2.w);
+    const double a = sqrt(A.gamma * pr / rho);
+    const PointGeom& Gp = A.geom[p];
+    const double hn = gload(&Gp.lsq, 0).w;  // nearest-neighbour distance
+    const D4 ls1 = gload(&Gp.ls1, 0);
+    const double dt = gload(A.cfl, A.comp ? gload(A.comp, p) : 0) * hn / (sqrt(usq) + a);
+    double Dp = 1.0 / dt;
+    if (A.variant == 0) {
+        // Anandhanarayanan et al.: split Jacobians -> +-rho(A+-) I (eq. 34-35)
+        if (ty == kWall) {
+            const double ut = u1 * t.x + u2 * t.y, un = -u1 * t.y + u2 * t.x;
+            Dp -= ls1.x * fmax(ut + a, 0.0);
+            Dp += ls1.y * fmax(a - ut, 0.0);
+            Dp += ls1.z * fmax(a - un, 0.0);
+        } else if (ty != kOuter) {
+            Dp -= ls1.x * fmax(u1 + a, 0.0);
+            Dp += ls1.y * fmax(a - u1, 0.0);
+            Dp -= ls1.z * fmax(u2 + a, 0.0);
+            Dp += ls1.w * fmax(a - u2, 0.0);
+        } else if (A.farfield) {
+            // t+, t-, n+ of the stencil and the ghost's n- half, whose
+            // single weight is 1/h (its increment is zero)
+            const double ut = u1 * t.x + u2 * t.y, un = -u1 * t.y + u2 * t.x;
+            Dp -= ls1.x * fmax(ut + a, 0.0);
+            Dp += ls1.y * fmax(a - ut, 0.0);
+            Dp -= ls1.z * fmax(un + a, 0.0);
+            Dp += fmax(a - un, 0.0) / hn;
+        }
+    } else {
+        // Manish et al.: A+- = (A +- rho(A) I)/2, rho(A) = |u_d| + a (eq. 29-33); the
+        // A part, S_0 = -1/2 sum_k LS_k(1) A_k dU_0, is taken with the previous
+        // iteration's increment onto the forward right-hand side A.R - S (eq. 36-38)
+        double dv[4] = {0, 0, 0, 0};
+        if (MIXED) {
+            const F4 d = gload(A.dUfio, p);
+            dv[0] = d.x; dv[1] = d.y; dv[2] = d.z; dv[3] = d.w;
+        } else {
+            const D4 d = gload(A.dUio, p);
+            dv[0] = d.x; dv[1] = d.y; dv[2] = d.z; dv[3] = d.w;
+        }
+        double Sv[4] = {0, 0, 0, 0}, Ja[4], Jb[4];
+        double ca = 0.0, cb = 0.0;
+        if (ty == kWall) {
+            const double ut = u1 * t.x + u2 * t.y, un = -u1 * t.y + u2 * t.x;
+            Dp -= 0.5 * (fabs(ut) + a) * (ls1.x - ls1.y);
+            Dp += 0.5 * (fabs(un) + a) * ls1.z;
+            if (A.fd) {
+                unsplit_jvp<true>(u, dv, t.x, t.y, A.gamma - 1.0, Ja);
+                unsplit_jvp<true>(u, dv, -t.y, t.x, A.gamma - 1.0, Jb);
+            } else {
+                unsplit_jvp<false>(u, dv, t.x, t.y, A.gamma - 1.0, Ja);
+                unsplit_jvp<false>(u, dv, -t.y, t.x, A.gamma - 1.0, Jb);
+            }
+            ca = ls1.x + ls1.y;
+            cb = ls1.z;
+        } else if (ty == kOuter && A.farfield) {
+            const double ut = u1 * t.x + u2 * t.y, un = -u1 * t.y + u2 * t.x;
+            Dp -= 0.5 * (fabs(ut) + a) * (ls1.x - ls1.y);
+            Dp -= 0.5 * (fabs(un) + a) * ls1.z;
+            if (A.fd) {
+                unsplit_jvp<true>(u, dv, t.x, t.y, A.gamma - 1.0, Ja);
+                unsplit_jvp<true>(u, dv, -t.y, t.x, A.gamma - 1.0, Jb);
+            } else {
+                unsplit_jvp<false>(u, dv, t.x, t.y, A.gamma - 1.0, Ja);
+                unsplit_jvp<false>(u, dv, -t.y, t.x, A.gamma - 1.0, Jb);
+            }
+            ca = ls1.x + ls1.y;
+            cb = ls1.z;
+        } else if (ty != kOuter) {
+            Dp -= 0.5 * (fabs(u1) + a) * (ls1.x - ls1.y);
+            Dp -= 0.5 * (fabs(u2) + a) * (ls1.z - ls1.w);
+            if (A.fd) {
+                unsplit_jvp<true>(u, dv, 1.0, 0.0, A.gamma - 1.0, Ja);
+                unsplit_jvp<true>(u, dv, 0.0, 1.0, A.gamma - 1.0, Jb);
+            } else {
+                unsplit_jvp<false>(u, dv, 1.0, 0.0, A.gamma - 1.0, Ja);
+                unsplit_jvp<false>(u, dv, 0.0, 1.0, A.gamma - 1.0, Jb);
+            }
+            ca = ls1.x + ls1.y;
+            cb = ls1.z + ls1.w;
+        }
+        if (part)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) Sv[v] = -0.5 * (ca * Ja[v] + cb * Jb[v]);
+        gstore(A.Rs, p, D4{Rp[0] - Sv[0], Rp[1] - Sv[1], Rp[2] - Sv[2], Rp[3] - Sv[3]});
+        if (A.sweep0)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) Sv[v] = Rp[v] - Sv[v];
+    }
+    if (MIXED) {
+        gstore(A.jv0f, p, F4{(float)j0.x, (float)j0.y, (float)j0.z, (float)j0.w});
+        gstore(A.jv2f, p, F4{(float)j2.x, (float)j2.y, (float)j2.z, (float)j2.w});
+        gstore(A.Df, p, (float)Dp);
+    } else {
+        gstore(A.jv0, p, j0);
+        gstore(A.jv2, p, j2);
+        gstore(A.Dg, p, Dp);
+    }
+    // the forward sweep's first colour phase: its points have no lower
+    // neighbours, dU* = -R / D (R - S for the Manish variant), in the
+    // sweep precision and with the sweep kernel's arithmetic
+    if (A.sweep0 && gload(A.colour, p) == 0) {
+        double rs[4] = {Rp[0], Rp[1], Rp[2], Rp[3]};
+        if (A.variant != 0) {
+            const D4 r2 = gload(A.Rs, p);
+            rs[0] = r2.x; rs[1] = r2.y; rs[2] = r2.z; rs[3] = r2.w;
+        }
+        if (MIXED) {
+            float o[4] = {0.f, 0.f, 0.f, 0.f};
+            if (part) {
+                const float iD = 1.0f / (float)Dp;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) o[v] = -((float)rs[v] + 0.0f) * iD;
+                if (ty == kWall) {
+                    const float nx = (float)(-t.y), ny = (float)t.x;
+                    const float mn = o[1] * nx + o[2] * ny;
+                    o[1] -= mn * nx;
+                    o[2] -= mn * ny;
+                }
+            }
+            gstore(A.dUfio, p, F4{o[0], o[1], o[2], o[3]});
+        } else {
+            double o[4] = {0, 0, 0, 0};
+            if (part) {
+                const double iD = 1.0 / Dp;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) o[v] = -(rs[v] + 0.0) * iD;
+                if (ty == kWall) {
+                    const double nx = -t.y, ny = t.x;
+                    const double mn = o[1] * nx + o[2] * ny;
+                    o[1] -= mn * nx;
+                    o[2] -= mn * ny;
+                }
+            }
+            gstore(A.dUio, p, D4{o[0], o[1], o[2], o[3]});
+        }
+    }
+    if (bad || !(rho > 0.0) || !(pr > 0.0)) gstore(A.flags, 0, 1);
+}
+
+// Direct gathers, for clouds without tiles.  LANES consecutive lanes share one
+// point: each takes every LANES-th neighbour, the four residual sums are
+// combined with cross-lane shuffles and the first lane finishes the point.
+// Software pipeline (interior points, gamma 1.4): neighbour indices two
+// entries ahead; the next neighbour's data is requested as soon as this one's
+// has gone into q~, and arrives during the flux evaluation; past the end the
+// last entry is re-read (in bounds), unused.
 template <bool MIXED, int LANES>
-__global__ void __launch_bounds__(kBlock) k_residual(
-    int64_t n, double gamma, const double* __restrict__ cfl, const D2* __restrict__ xy,
-    const D2* __restrict__ frame,
-    const int8_t* __restrict__ type, const int32_t* __restrict__ off,
-    const int32_t* __restrict__ idx, const PointGeom* __restrict__ geom,
-    const int32_t* __restrict__ comp, const int32_t* __restrict__ active,
-    const D4* __restrict__ U, const D4* __restrict__ q, const D4* __restrict__ qx,
-    const D4* __restrict__ qy, D4* __restrict__ R, double* __restrict__ Dg,
-    D4* __restrict__ jv0, D4* __restrict__ jv2, F4* __restrict__ jv0f, F4* __restrict__ jv2f,
-    float* __restrict__ Df,
-    double* __restrict__ rr_out, int32_t* __restrict__ flags, int variant, int fd,
-    D4* dUio, F4* dUfio, D4* __restrict__ Rs, const int32_t* __restrict__ colour, int sweep0,
-    int farfield, const double* __restrict__ vinf) {
-    const int lb = xcd_block(blockIdx.x, gridDim.x);
-    const int64_t gt = (int64_t)lb * blockDim.x + threadIdx.x;
+__global__ void __launch_bounds__(kBlock) k_residual(ResidualArgs A) {
+    const int64_t gt = (int64_t)xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
     const int64_t p = gt / LANES;
     const int lane = (int)(gt % LANES);
-    const double inv_gm1 = 1.0 / (gamma - 1.0);
-    const bool g14 = gamma == 1.4;
-    if (p < n && live(comp, active, p)) {
-        const int8_t ty = type[p];
-        const D2 r0 = xy[p];
-        const D2 t = frame[p];
-        double Rp[4] = {0, 0, 0, 0};
-        int bad = 0;
-        // outer points take part only under the kinetic far field
-        const bool part = ty != kOuter || farfield;
-        if (part) {
-            const D4 q0 = q[p], gx0 = qx[p], gy0 = qy[p];
-            const PointGeom& G = geom[p];
-            const D2 c0 = G.split[0], c1 = G.split[1], c2 = G.split[2], c3 = G.split[3];
-            const int32_t e1 = off[p + 1];
-            int32_t e = off[p] + lane;
-            if (e < e1) {
-                // software pipeline: neighbour indices two entries ahead and
-                // neighbour data one entry ahead of the pair being computed;
-                // past the end the last entry is re-read (in bounds), unused
-                const int32_t last = e1 - 1;
-                int32_t i_next = idx[min(e + LANES, last)];
-                Nbr cur = load_nbr(idx[e], xy, q, qx, qy);
-                for (; e < e1; e += LANES) {
-                    const int32_t i_after = idx[min(e + 2 * LANES, last)];
-                    const Nbr nxt = load_nbr(i_next, xy, q, qx, qy);
-                    residual_pair(ty, t, r0, q0, gx0, gy0, c0, c1, c2, c3, cur, inv_gm1, g14, Rp,
-                                  bad);
-                    cur = nxt;
-                    i_next = i_after;
+    const double inv_gm1 = 1.0 / (A.gamma - 1.0);
+    const bool g14 = A.gamma == 1.4;
+    const PolyLead lead = poly_lead();
+    __shared__ D2 s_coef[4 * kBlock];  // each lane writes and reads its own copy
+    if (p >= A.n || !live(A.comp, A.active, p)) return;
+    const int8_t ty = A.type[p];
+    ResidualSum sum{};
+    if (ty != kOuter || A.farfield) {
+        const D2 r0 = A.xy[p];
+        const D4 q0 = A.q[p], gx0 = A.qx[p], gy0 = A.qy[p];
+        D2* coef = s_coef + threadIdx.x;
+        const PointGeom& G = A.geom[p];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) coef[k * kBlock] = G.split[k];
+        const int32_t e1 = A.off[p + 1], last = e1 - 1;
+        const int32_t eb = A.off[p] + lane;
+        sum = residual_walks(ty, g14, [&](auto frame, auto is14) __attribute__((always_inline)) {
+            ResidualSum R{};
+            constexpr bool FRAME = decltype(frame)::value, G14 = decltype(is14)::value;
+            constexpr bool PIPE = !FRAME && G14;
+            const D2 t = FRAME ? A.frame[p] : D2{1.0, 0.0};
+            int32_t e = eb;
+            if (e >= e1) return R;
+            int32_t i_next = A.idx[min(e + LANES, last)];
+            Nbr nb = load_nbr(A.idx[e], A.xy, A.q, A.qx, A.qy);
+            for (; e < e1; e += LANES) {
+                const double dx = nb.r.x - r0.x, dy = nb.r.y - r0.y;
+                const double hx = -0.5 * dx, hy = -0.5 * dy;
+                const D4 qti = reconstruct(nb.q, nb.gx, nb.gy, hx, hy);
+                const D4 qt0 = reconstruct(q0, gx0, gy0, hx, hy);
+                if (PIPE) {
+                    nb = load_nbr(i_next, A.xy, A.q, A.qx, A.qy);
+                    i_next = A.idx[min(e + 2 * LANES, last)];
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                pair_add<FRAME, G14>(dx, dy, qti, qt0, t, ty, coef, kBlock, inv_gm1, lead, R);
+                if (!PIPE) {
+                    nb = load_nbr(i_next, A.xy, A.q, A.qx, A.qy);
+                    i_next = A.idx[min(e + 2 * LANES, last)];
                 }
             }
-        }
-#pragma unroll
-        for (int o = LANES / 2; o > 0; o >>= 1) {
-#pragma unroll
-            for (int v = 0; v < 4; ++v) Rp[v] += __shfl_xor(Rp[v], o, 64);
-            bad |= __shfl_xor(bad, o, 64);
-        }
-        if (lane == 0) {
-            if (ty == kWall) {  // drop the normal-momentum component
-                const double nx = -t.y, ny = t.x;
-                const double mn = Rp[1] * nx + Rp[2] * ny;
-                Rp[1] -= mn * nx;
-                Rp[2] -= mn * ny;
-            }
-            if (ty == kOuter && farfield) {
-                // kinetic far field: the n- half (molecules entering the domain)
-                // from a free-stream ghost one nearest-neighbour distance outside,
-                // (G_n-(U_inf) - G_n-(U_0)) / h with the point's own q
-                const int k = comp ? comp[p] : 0;
-                const double v1 = vinf[2 * k], v2 = vinf[2 * k + 1];
-                Prim wf;
-                wf.rho = 1.0;
-                wf.u1 = v1;
-                wf.u2 = v2;
-                wf.p = 1.0 / gamma;
-                wf.sb = sqrt(0.5 * gamma);
-                wf.isb = 1.0 / wf.sb;
-                wf.rhoE = wf.p * inv_gm1 + 0.5 * (v1 * v1 + v2 * v2);
-                const Prim w0 = prim_from_q(q[p], inv_gm1, g14);
-                double Gf[4], G0[4];
-                split_flux<2>(wf, -t.y, t.x, -1.0, inv_gm1, Gf);
-                split_flux<2>(w0, -t.y, t.x, -1.0, inv_gm1, G0);
-                const double ih = 1.0 / geom[p].lsq.w;
-#pragma unroll
-                for (int v = 0; v < 4; ++v) Rp[v] += (Gf[v] - G0[v]) * ih;
-            }
-            rr_out[p] = ty != kOuter ? Rp[0] * Rp[0] : 0.0;
-            R[p] = {Rp[0], Rp[1], Rp[2], Rp[3]};
+            return R;
+        });
+    }
+    residual_lane_sum<LANES>(sum);
+    if (lane == 0) residual_finish<MIXED>(p, ty, sum, inv_gm1, g14);
+}
 
-            // linearisation data at the current state, local time step, diagonal
-            const D4 u = U[p];
-            const double rho = u.x, irho = 1.0 / rho;
-            const double u1 = u.y * irho, u2 = u.z * irho;
-            const double usq = u1 * u1 + u2 * u2;
-            const double pr = (gamma - 1.0) * (u.w - 0.5 * rho * usq);
-            const double beta = 0.5 * rho / pr;
-            const double sb = sqrt(beta);
-            const double sx = u1 * sb, sy = u2 * sb;
-            const D4 j0 = {rho, u1, u2, pr};
-            const D4 j2 = {erf_fast(sx), exp_fast(-(sx * sx)), erf_fast(sy), exp_fast(-(sy * sy))};
-            const double a = sqrt(gamma * pr / rho);
-            const PointGeom& G = geom[p];
-            const double dt = cfl[comp ? comp[p] : 0] * G.lsq.w / (sqrt(usq) + a);
-            double Dp = 1.0 / dt;
-            if (variant == 0) {
-                // Anandhanarayanan et al.: split Jacobians -> +-rho(A+-) I (eq. 34-35)
-                if (ty == kWall) {
-                    const double ut = u1 * t.x + u2 * t.y, un = -u1 * t.y + u2 * t.x;
-                    Dp -= G.ls1.x * fmax(ut + a, 0.0);
-                    Dp += G.ls1.y * fmax(a - ut, 0.0);
-                    Dp += G.ls1.z * fmax(a - un, 0.0);
-                } else if (ty != kOuter) {
-                    Dp -= G.ls1.x * fmax(u1 + a, 0.0);
-                    Dp += G.ls1.y * fmax(a - u1, 0.0);
-                    Dp -= G.ls1.z * fmax(u2 + a, 0.0);
-                    Dp += G.ls1.w * fmax(a - u2, 0.0);
-                } else if (farfield) {
-                    // t+, t-, n+ of the stencil and the ghost's n- half, whose
-                    // single weight is 1/h (its increment is zero)
-                    const double ut = u1 * t.x + u2 * t.y, un = -u1 * t.y + u2 * t.x;
-                    Dp -= G.ls1.x * fmax(ut + a, 0.0);
-                    Dp += G.ls1.y * fmax(a - ut, 0.0);
-                    Dp -= G.ls1.z * fmax(un + a, 0.0);
-                    Dp += fmax(a - un, 0.0) / G.lsq.w;
-                }
-            } else {
-                // Manish et al.: A+- = (A +- rho(A) I)/2, rho(A) = |u_d| + a (eq. 29-33); the
-                // A part, S_0 = -1/2 sum_k LS_k(1) A_k dU_0, is taken with the previous
-                // iteration's increment onto the forward right-hand side R - S (eq. 36-38)
-                double dv[4] = {0, 0, 0, 0};
-                if (MIXED) {
-                    const F4 d = dUfio[p];
-                    dv[0] = d.x; dv[1] = d.y; dv[2] = d.z; dv[3] = d.w;
-                } else {
-                    const D4 d = dUio[p];
-                    dv[0] = d.x; dv[1] = d.y; dv[2] = d.z; dv[3] = d.w;
-                }
-                double Sv[4] = {0, 0, 0, 0}, Ja[4], Jb[4];
-                double ca = 0.0, cb = 0.0;
-                if (ty == kWall) {
-                    const double ut = u1 * t.x + u2 * t.y, un = -u1 * t.y + u2 * t.x;
-                    Dp -= 0.5 * (fabs(ut) + a) * (G.ls1.x - G.ls1.y);
-                    Dp += 0.5 * (fabs(un) + a) * G.ls1.z;
-                    if (fd) {
-                        unsplit_jvp<true>(u, dv, t.x, t.y, gamma - 1.0, Ja);
-                        unsplit_jvp<true>(u, dv, -t.y, t.x, gamma - 1.0, Jb);
-                    } else {
-                        unsplit_jvp<false>(u, dv, t.x, t.y, gamma - 1.0, Ja);
-                        unsplit_jvp<false>(u, dv, -t.y, t.x, gamma - 1.0, Jb);
-                    }
-                    ca = G.ls1.x + G.ls1.y;
-                    cb = G.ls1.z;
-                } else if (ty == kOuter && farfield) {
-                    const double ut = u1 * t.x + u2 * t.y, un = -u1 * t.y + u2 * t.x;
-                    Dp -= 0.5 * (fabs(ut) + a) * (G.ls1.x - G.ls1.y);
-                    Dp -= 0.5 * (fabs(un) + a) * G.ls1.z;
-                    if (fd) {
-                        unsplit_jvp<true>(u, dv, t.x, t.y, gamma - 1.0, Ja);
-                        unsplit_jvp<true>(u, dv, -t.y, t.x, gamma - 1.0, Jb);
-                    } else {
-                        unsplit_jvp<false>(u, dv, t.x, t.y, gamma - 1.0, Ja);
-                        unsplit_jvp<false>(u, dv, -t.y, t.x, gamma - 1.0, Jb);
-                    }
-                    ca = G.ls1.x + G.ls1.y;
-                    cb = G.ls1.z;
-                } else if (ty != kOuter) {
-                    Dp -= 0.5 * (fabs(u1) + a) * (G.ls1.x - G.ls1.y);
-                    Dp -= 0.5 * (fabs(u2) + a) * (G.ls1.z - G.ls1.w);
-                    if (fd) {
-                        unsplit_jvp<true>(u, dv, 1.0, 0.0, gamma - 1.0, Ja);
-                        unsplit_jvp<true>(u, dv, 0.0, 1.0, gamma - 1.0, Jb);
-                    } else {
-                        unsplit_jvp<false>(u, dv, 1.0, 0.0, gamma - 1.0, Ja);
-                        unsplit_jvp<false>(u, dv, 0.0, 1.0, gamma - 1.0, Jb);
-                    }
-                    ca = G.ls1.x + G.ls1.y;
-                    cb = G.ls1.z + G.ls1.w;
-                }
-                if (part)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) Sv[v] = -0.5 * (ca * Ja[v] + cb * Jb[v]);
-                Rs[p] = {Rp[0] - Sv[0], Rp[1] - Sv[1], Rp[2] - Sv[2], Rp[3] - Sv[3]};
-                if (sweep0)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) Sv[v] = Rp[v] - Sv[v];
+// The same with the neighbours staged in LDS, on the tiles of the
+// q-derivative passes: a block of kQTile points, LANES lanes each, copies
+// position, q and derivatives of the tile's listed points once (112 bytes
+// each, about 2.5 listed points per point) and every pair reads its neighbour
+// there.  S is the stride of the staged arrays, at least the longest list of
+// the cloud.  The lanes' sums meet in LDS, and the first wavefront finishes
+// the tile's points, one per lane.  The arithmetic and the order of the sums
+// are those of k_residual.
+// Bound by vector instruction issue: about 260 per pair after sharing the two
+// directions' work (end_sum), 430 before.  2,621,440 points, two lanes per
+// point: 854 us with separate fluxes per direction, 665 us now (FP64); a bound
+// of four wavefronts per SIMD spills 56 bytes and takes 1,055 us.
+template <bool MIXED, int LANES, int S>
+__global__ void __launch_bounds__(kQTile * LANES) k_residual_tiled(ResidualArgs A) {
+    __shared__ D2 s_nb[7 * S];  // (x, y), q, q_x, q_y in pairs of components
+    __shared__ D2 s_coef[4 * kQTile];
+    const int tile = xcd_block(blockIdx.x, gridDim.x);
+    const int pt = threadIdx.x / LANES, lane = threadIdx.x % LANES;
+    const int64_t p = A.tile_pts[(int64_t)tile * kQTile + pt];
+    const double inv_gm1 = 1.0 / (A.gamma - 1.0);
+    const bool g14 = A.gamma == 1.4;
+    const PolyLead lead = poly_lead();
+    // the point's own data is requested before the staging
+    const bool on = p >= 0 && live(A.comp, A.active, p);
+    int8_t ty = kOuter;
+    D2 r0{};
+    D4 q0{}, gx0{}, gy0{};
+    int32_t eb = 0, e1 = 0;
+    if (on) {
+        ty = A.type[p];
+        r0 = A.xy[p];
+        q0 = A.q[p];
+        gx0 = A.qx[p];
+        gy0 = A.qy[p];
+        eb = A.off[p] + lane;
+        e1 = A.off[p + 1];
+        for (int k = lane; k < 4; k += LANES) s_coef[k * kQTile + pt] = A.geom[p].split[k];
+    }
+    // a pointer of its own, so that the loop holds it and not its neighbours among the arguments
+    auto* lnbr = (const __attribute__((address_space(1))) uint16_t*)A.lnbr;
+    asm volatile("" : "+s"(lnbr));
+    int li = eb < e1 ? lnbr[eb] : 0;
+    const int32_t h0 = A.tile_off[tile], nh = A.tile_off[tile + 1] - h0;
+    for (int32_t k = threadIdx.x; k < nh; k += kQTile * LANES) {
+        const int32_t i = A.tile_idx[h0 + k];
+        const D4 a = A.q[i], b = A.qx[i], c = A.qy[i];
+        s_nb[k] = A.xy[i];
+        s_nb[S + k] = {a.x, a.y};
+        s_nb[2 * S + k] = {a.z, a.w};
+        s_nb[3 * S + k] = {b.x, b.y};
+        s_nb[4 * S + k] = {b.z, b.w};
+        s_nb[5 * S + k] = {c.x, c.y};
+        s_nb[6 * S + k] = {c.z, c.w};
+    }
+    __syncthreads();
+    ResidualSum sum{};
+    if (on && (ty != kOuter || A.farfield)) {
+        const D2* coef = s_coef + pt;
+        sum = residual_walks(ty, g14, [&](auto frame, auto is14) __attribute__((always_inline)) {
+            ResidualSum R{};
+            constexpr bool FRAME = decltype(frame)::value, G14 = decltype(is14)::value;
+            const D2 t = FRAME ? A.frame[p] : D2{1.0, 0.0};
+            for (int32_t e = eb; e < e1; e += LANES) {
+                const D2 r = s_nb[li], qa = s_nb[S + li], qb = s_nb[2 * S + li];
+                const D2 xa = s_nb[3 * S + li], xb = s_nb[4 * S + li];
+                const D2 ya = s_nb[5 * S + li], yb = s_nb[6 * S + li];
+                li = lnbr[min(e + LANES, e1 - 1)];  // the next entry's position
+                const double dx = r.x - r0.x, dy = r.y - r0.y;
+                const double hx = -0.5 * dx, hy = -0.5 * dy;
+                const D4 qti = reconstruct({qa.x, qa.y, qb.x, qb.y}, {xa.x, xa.y, xb.x, xb.y},
+                                           {ya.x, ya.y, yb.x, yb.y}, hx, hy);
+                const D4 qt0 = reconstruct(q0, gx0, gy0, hx, hy);
+                pair_add<FRAME, G14>(dx, dy, qti, qt0, t, ty, coef, kQTile, inv_gm1, lead, R);
             }
-            if (MIXED) {
-                jv0f[p] = {(float)j0.x, (float)j0.y, (float)j0.z, (float)j0.w};
-                jv2f[p] = {(float)j2.x, (float)j2.y, (float)j2.z, (float)j2.w};
-                Df[p] = (float)Dp;
-            } else {
-                jv0[p] = j0;
-                jv2[p] = j2;
-                Dg[p] = Dp;
-            }
-            // the forward sweep's first colour phase: its points have no lower
-            // neighbours, dU* = -R / D (R - S for the Manish variant), in the
-            // sweep precision and with the sweep kernel's arithmetic
-            if (sweep0 && colour[p] == 0) {
-                double rs[4] = {Rp[0], Rp[1], Rp[2], Rp[3]};
-                if (variant != 0) {
-                    const D4 r2 = Rs[p];
-                    rs[0] = r2.x; rs[1] = r2.y; rs[2] = r2.z; rs[3] = r2.w;
-                }
-                if (MIXED) {
-                    float o[4] = {0.f, 0.f, 0.f, 0.f};
-                    if (part) {
-                        const float iD = 1.0f / (float)Dp;
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) o[v] = -((float)rs[v] + 0.0f) * iD;
-                        if (ty == kWall) {
-                            const float nx = (float)(-t.y), ny = (float)t.x;
-                            const float mn = o[1] * nx + o[2] * ny;
-                            o[1] -= mn * nx;
-                            o[2] -= mn * ny;
-                        }
-                    }
-                    dUfio[p] = {o[0], o[1], o[2], o[3]};
-                } else {
-                    double o[4] = {0, 0, 0, 0};
-                    if (part) {
-                        const double iD = 1.0 / Dp;
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) o[v] = -(rs[v] + 0.0) * iD;
-                        if (ty == kWall) {
-                            const double nx = -t.y, ny = t.x;
-                            const double mn = o[1] * nx + o[2] * ny;
-                            o[1] -= mn * nx;
-                            o[2] -= mn * ny;
-                        }
-                    }
-                    dUio[p] = {o[0], o[1], o[2], o[3]};
-                }
-            }
-            if (bad || !(rho > 0.0) || !(pr > 0.0)) flags[0] = 1;
+            return R;
+        });
+    }
+    residual_lane_sum<LANES>(sum);
+    if (LANES > 1) {
+        // hand the sums to the first wavefront through the staging area
+        __syncthreads();
+        double* s_R = reinterpret_cast<double*>(s_nb);
+        int32_t* s_bad = reinterpret_cast<int32_t*>(s_nb + 2 * kQTile);
+        int32_t* s_p = s_bad + kQTile;
+        if (lane == 0) {
+            s_R[pt] = sum.x;
+            s_R[kQTile + pt] = sum.y;
+            s_R[2 * kQTile + pt] = sum.z;
+            s_R[3 * kQTile + pt] = sum.w;
+            s_bad[pt] = sum.bad ? 1 : 0;
+            s_p[pt] = on ? (int32_t)p : -1;
         }
+        __syncthreads();
+        const int t = threadIdx.x;
+        if (t >= kQTile || s_p[t] < 0) return;
+        sum = {s_R[t], s_R[kQTile + t], s_R[2 * kQTile + t], s_R[3 * kQTile + t], s_bad[t] != 0};
+        residual_finish<MIXED>(s_p[t], gload(reread_args().type, s_p[t]), sum, inv_gm1, g14);
+    } else if (on) {
+        residual_finish<MIXED>(p, ty, sum, inv_gm1, g14);
     }
 }
 
@@ -1134,8 +1411,9 @@ __device__ __forceinline__ void jvp_fluxdiff(const Lin<double>& L, double er, do
     W.beta = 0.5 * W.rho / W.p;
     W.sb = sqrt(W.beta);
     const double S = (W.u1 * dx + W.u2 * dy) * W.sb;
-    double Ga[4], Gb[4];
-    flux_lin(W, erf_fast(S), exp_fast(-(S * S)), dx, dy, sg, inv_gm1, Ga);
+    double Ga[4], Gb[4], ea, xa;
+    erf_exp(S, ea, xa);
+    flux_lin(W, ea, xa, dx, dy, sg, inv_gm1, Ga);
     flux_lin(L, er, g, dx, dy, sg, inv_gm1, Gb);
 #pragma unroll
     for (int v = 0; v < 4; ++v) J[v] = Ga[v] - Gb[v];
@@ -1246,15 +1524,18 @@ __device__ __forceinline__ void sweep_contrib(uint8_t cd, const D2* __restrict__
     if (cd & kSwWall) {
         // wall-frame directions: erf/exp at the neighbour state are formed here
         const D2 t = frame[p];
+        T er, g;
         if (cd & kSwA) {
             const double sg = (cd & kSwNegA) ? 1.0 : -1.0;
             if constexpr (MODE == 1) {
                 const double S = (L.u1 * t.x + L.u2 * t.y) * L.sb;
-                jvp_fluxdiff(L, erf_fast(S), exp_fast(-(S * S)), U[i], t.x, t.y, sg, dv, gamma,
+                erf_exp(S, er, g);
+                jvp_fluxdiff(L, er, g, U[i], t.x, t.y, sg, dv, gamma,
                              1.0 / (gamma - 1.0), J);
             } else {
                 const T S = (L.u1 * T(t.x) + L.u2 * T(t.y)) * L.sb;
-                jvp_exact<T>(L, erf_k(S), exp_k(-(S * S)), T(t.x), T(t.y), T(sg), dv, gm1, inv_gm1, J);
+                erf_exp(S, er, g);
+                jvp_exact<T>(L, er, g, T(t.x), T(t.y), T(sg), dv, gm1, inv_gm1, J);
             }
             const T wa = T(w.x);
 #pragma unroll
@@ -1264,11 +1545,13 @@ __device__ __forceinline__ void sweep_contrib(uint8_t cd, const D2* __restrict__
             const double sg = (cd & kSwNegB) ? 1.0 : -1.0;
             if constexpr (MODE == 1) {
                 const double S = (-L.u1 * t.y + L.u2 * t.x) * L.sb;
-                jvp_fluxdiff(L, erf_fast(S), exp_fast(-(S * S)), U[i], -t.y, t.x, sg, dv, gamma,
+                erf_exp(S, er, g);
+                jvp_fluxdiff(L, er, g, U[i], -t.y, t.x, sg, dv, gamma,
                              1.0 / (gamma - 1.0), J);
             } else {
                 const T S = (-L.u1 * T(t.y) + L.u2 * T(t.x)) * L.sb;
-                jvp_exact<T>(L, erf_k(S), exp_k(-(S * S)), T(-t.y), T(t.x), T(sg), dv, gm1, inv_gm1, J);
+                erf_exp(S, er, g);
+                jvp_exact<T>(L, er, g, T(-t.y), T(t.x), T(sg), dv, gm1, inv_gm1, J);
             }
             const T wb = T(w.y);
 #pragma unroll
@@ -1660,14 +1943,27 @@ static int fused_first_colour(const State& s) { return s.prm.order == 0 && s.prm
 template <bool MIXED, int LANES>
 static void residual_lanes(State& s, bool in_step) {
     const Cloud& c = *s.cloud;
-    const unsigned nb = grid_for(c.n * LANES);
-    hipLaunchKernelGGL((k_residual<MIXED, LANES>), dim3(nb), dim3(kBlock), 0, s.stream, c.n,
-                       s.prm.gamma, s.cfl, c.xy, c.frame, c.type, c.off, c.idx, c.geom, c.comp,
-                       s.active, s.U, s.q, s.prm.limiter ? s.qxl : s.qx[s.qsel],
-                       s.prm.limiter ? s.qyl : s.qy[s.qsel], s.R, s.D, s.jv0, s.jv2, s.jv0f,
-                       s.jv2f, s.Df, s.rr, s.flags, s.prm.variant,
-                       s.prm.jvp_mode, s.dU, s.dUf, s.Rs, c.colour,
-                       in_step && fused_first_colour(s), s.prm.farfield, s.vinf);
+    const ResidualArgs A{c.n,        s.prm.gamma, s.cfl,      c.xy,
+                         c.frame,    c.type,      c.off,      c.idx,
+                         c.geom,     c.comp,      s.active,   c.tile_pts,
+                         c.lnbr,     c.tile_off,  c.tile_idx, s.U,
+                         s.q,        s.prm.limiter ? s.qxl : s.qx[s.qsel],
+                         s.prm.limiter ? s.qyl : s.qy[s.qsel], s.R,
+                         s.D,        s.jv0,       s.jv2,      s.jv0f,
+                         s.jv2f,     s.Df,        s.rr,       s.flags,
+                         s.prm.variant, s.prm.jvp_mode, s.dU, s.dUf,
+                         s.Rs,       c.colour,    in_step && fused_first_colour(s),
+                         s.prm.farfield, s.vinf};
+    // Tiles pay once there is a block for every CU: below, a launch lasts as
+    // long as one block, and the staging and its barriers lengthen that (FP64,
+    // 6,400 points: 18.5 us gathered, 23.5 us tiled; 40,250 points: 28.5 and
+    // 26.8; 2,621,440 points: 712 and 665).  Both forms give the same bits.
+    if (s.qgrad_tiled && c.ntile >= kResidualMinTiles && c.tile_hmax <= kResidualTile)
+        hipLaunchKernelGGL((k_residual_tiled<MIXED, LANES, kResidualTile>), dim3((unsigned)c.ntile),
+                           dim3(kQTile * LANES), 0, s.stream, A);
+    else
+        hipLaunchKernelGGL((k_residual<MIXED, LANES>), dim3(grid_for(c.n * LANES)), dim3(kBlock), 0,
+                           s.stream, A);
 }
 
 template <bool MIXED>

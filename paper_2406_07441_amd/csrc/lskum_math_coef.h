@@ -28,6 +28,41 @@ constexpr double kErfP[12] = {
     -0x1.812746b0379c1p-2,
     0x1.20dd750429b6dp+0};
 
+// E(u) = e^(-u) on [-1/2, 1/2], degree 12, fit error 4.98e-18
+constexpr double kExpN[13] = {
+    0x1.2036290a2a4e6p-29,
+    -0x1.b0a38fe8033d7p-26,
+    0x1.27e42df3ab7bcp-22,
+    -0x1.71dcd28a56ee8p-19,
+    0x1.a01a021b73430p-16,
+    -0x1.a01a02780e87dp-13,
+    0x1.6c16c16bf2c5dp-10,
+    -0x1.11111110d2113p-7,
+    0x1.55555555555e5p-5,
+    -0x1.555555555574dp-3,
+    0x1.0000000000000p-1,
+    -0x1.fffffffffffffp-1,
+    0x1.0000000000000p+0};
+
+// W(v) = erfcx(3 (1 + v)/(1 - v)) on [-1/2, 1/3], degree 14, fit error 1.01e-17
+constexpr double kErfcxW[15] = {
+    0x1.57a5fe2b9b75ep-20,
+    0x1.0f9a79cee3e31p-19,
+    -0x1.0cb4611cc29f6p-17,
+    -0x1.af2329d757293p-17,
+    0x1.0cb1db32e0c9fp-14,
+    0x1.7b9fc8eb630e9p-15,
+    -0x1.39085a31b18abp-11,
+    0x1.73101ea8fe252p-11,
+    0x1.17c838fea5806p-8,
+    -0x1.8fa58eb5bd68fp-6,
+    0x1.258b13b0139fep-4,
+    -0x1.336ffbef08cbbp-3,
+    0x1.f6ff20410599bp-3,
+    -0x1.4e102b9cf8512p-2,
+    0x1.6e9827d229d2dp-3};
+
+constexpr double kExpHalf = 0x1.368b2fc6f960ap-1;
 constexpr double kLog2e = 0x1.71547652b82fep+0;
 constexpr double kLn2Hi = 0x1.62e42fefa39efp-1;
 constexpr double kLn2Lo = 0x1.abc9e3b39803fp-56;
