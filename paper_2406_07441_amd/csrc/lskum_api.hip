@@ -60,7 +60,7 @@ hipError_t upload(T* dst, const T* src, size_t count) {
 void free_cloud(lskum::Cloud& c) {
     void* ptrs[] = {c.xy,     c.frame,     c.type,   c.off,      c.idx,      c.colour,
                     c.col_perm, c.wall_list, c.geom, c.lo_off,   c.lo_idx,   c.up_off,
-                    c.up_idx, c.lo_w,      c.up_w,     c.lo_code,  c.up_code,  c.comp,
+                    c.up_idx, c.lo_w,      c.up_w,     c.lo_code,  c.up_code,  c.comp, c.qcomp,
                     c.lo_wf, c.up_wf,
                     c.comp_off, c.wall_off, c.comp_inv_active,
                     c.comp_orient, c.chunk_start, c.chunk_comp, c.comp_chunk_off,
@@ -173,6 +173,7 @@ int upload_cloud(lskum::Cloud& c) {
         }
         lo_off[q + 1] = (int32_t)lo_idx.size();
         up_off[q + 1] = (int32_t)up_idx.size();
+        c.max_list = std::max({c.max_list, lo_off[q + 1] - lo_off[q], up_off[q + 1] - up_off[q]});
     }
 
     // wall list per component (storage order) and polygon orientation
@@ -282,12 +283,15 @@ int upload_cloud(lskum::Cloud& c) {
     chk(dalloc(&c.chunk_start, chunk_start.size()));
     chk(dalloc(&c.chunk_comp, chunk_comp.size()));
     chk(dalloc(&c.comp_chunk_off, comp_chunk_off.size()));
-    std::vector<int32_t> comp;
+    std::vector<int32_t> comp, qcomp;
     if (c.ncomp > 1) {
         comp.resize(n);
+        qcomp.resize(n);
         for (int32_t k = 0; k < c.ncomp; ++k)
             for (int64_t p = c.h_comp_off[k]; p < c.h_comp_off[k + 1]; ++p) comp[p] = k;
+        for (int64_t q = 0; q < n; ++q) qcomp[q] = comp[perm[q]];
         chk(dalloc(&c.comp, n));
+        chk(dalloc(&c.qcomp, n));
     }
     if (e == hipSuccess) {
         chk(upload(c.xy, hxy.data(), n));
@@ -313,6 +317,7 @@ int upload_cloud(lskum::Cloud& c) {
         chk(upload(c.comp_inv_active, c.h_comp_inv_active.data(), c.ncomp));
         chk(upload(c.comp_orient, c.h_comp_orient.data(), c.ncomp));
         if (c.comp) chk(upload(c.comp, comp.data(), n));
+        if (c.qcomp) chk(upload(c.qcomp, qcomp.data(), n));
         chk(upload(c.chunk_start, chunk_start.data(), chunk_start.size()));
         chk(upload(c.chunk_comp, chunk_comp.data(), chunk_comp.size()));
         chk(upload(c.comp_chunk_off, comp_chunk_off.data(), comp_chunk_off.size()));
@@ -336,7 +341,7 @@ void free_state(lskum::State& s) {
     if (s.have_events)
         for (hipEvent_t ev : s.ev) (void)hipEventDestroy(ev);
     void* ptrs[] = {s.U,    s.q,      s.qx[0], s.qx[1],  s.qy[0],   s.qy[1],    s.qxl, s.Rs,
-                    s.qyl,  s.R,      s.dU,    s.jv0,    s.jv2,      s.D,
+                    s.qyl,  s.R,      s.dU,    s.jv0,    s.D,
                     s.jv0f, s.jv2f,  s.dUf,    s.Df,      s.rr,       s.fsum, s.partial,
                     s.res_hist, s.flags, s.active, s.status, s.iters, s.res_last, s.tol_abs, s.cfl,
                     s.vinf};
@@ -385,9 +390,16 @@ lskum::Params to_params(const lskum_params* p) {
 
 // Lanes per point: the caller's choice, else 8 for the latency-bound sweeps
 // and 2 for the compute-bound residual (measured best on the 163,840-point
-// transonic cloud, FP64 and mixed).
+// transonic cloud, FP64 and mixed).  Up to kSmallSweep points a colour phase
+// leaves most of the chip idle and lasts as long as one lane's walk: 16 lanes
+// then (the sums of 8 lanes bit for bit while no list exceeds 32 entries, so
+// the choice may depend on how many conditions share a launch).  Iteration at
+// 6,400 points with 8 and 16 lanes: 116.5 and 110.4 us; 40,250: 142.5 and
+// 141.6; 80,000: 173 and 176; 163,840: 227 and 229.
+constexpr int64_t kSmallSweep = 50000;
 void apply_lanes(lskum::State& s) {
-    s.sweep_lanes = s.prm.sweep_lanes ? s.prm.sweep_lanes : 8;
+    const bool small = s.cloud->n <= kSmallSweep && s.cloud->max_list <= 32;
+    s.sweep_lanes = s.prm.sweep_lanes ? s.prm.sweep_lanes : (small ? 16 : 8);
     s.residual_lanes = s.prm.residual_lanes ? s.prm.residual_lanes : 2;
     s.qgrad_tiled = s.prm.qgrad_lanes == 0;
     s.qgrad_lanes = s.prm.qgrad_lanes ? s.prm.qgrad_lanes : 4;
@@ -484,7 +496,6 @@ int init_state(lskum::State& s, const lskum::Cloud& c, const lskum_params* prm,
     chk(dalloc(&s.Rs, n));
     chk(dalloc(&s.dU, n));
     chk(dalloc(&s.jv0, n));
-    chk(dalloc(&s.jv2, n));
     chk(dalloc(&s.D, n));
     chk(dalloc(&s.jv0f, n));
     chk(dalloc(&s.jv2f, n));
@@ -707,7 +718,8 @@ __device__ __align__(256) unsigned char scratch[kScratchBytes];
 std::mutex g_scratch_mu;
 unsigned char* g_scratch[kMaxDevices] = {};
 
-// bytes per point of the scratch layout below, and the fixed part
+// bytes per point that the capacity is reckoned with (the layout below takes a
+// record of 32 bytes less), and the fixed part
 constexpr size_t kNoallocPerPoint = 11 * sizeof(lskum::D4) + 2 * sizeof(double);
 constexpr size_t kNoallocFixed = (size_t)1 << 20;
 
@@ -1051,7 +1063,6 @@ int lskum_residual_noalloc(const lskum_cloud* cl, double mach, double aoa_deg,
     s.qyl = cv.take<lskum::D4>(n);
     s.R = cv.take<lskum::D4>(n);
     s.jv0 = cv.take<lskum::D4>(n);
-    s.jv2 = cv.take<lskum::D4>(n);
     s.D = cv.take<double>(n);
     s.rr = cv.take<double>(n);
     s.partial = cv.take<double>(c.nchunk);

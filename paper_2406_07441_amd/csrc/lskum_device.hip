@@ -726,6 +726,22 @@ __device__ __forceinline__ void unit_or_outer(double S, double t, const PolyLead
     }
 }
 
+template <bool FRAME>
+__device__ __forceinline__ D4 weighted_flux(double rho, double p, double r, double u1, double u2,
+                                            double ua, double ub, double bu, double era, double ga,
+                                            double erb, double gb, const D2& t, double hwa,
+                                            double hsa, double hwb, double hsb, double inv_gm1) {
+#pragma clang fp contract(off)
+    const double aa = fma(hsa, era, hwa), ab = fma(hsb, erb, hwb);  // w A
+    const double P = fma(ua, aa, ub * ab);
+    const double F = fma(fma(hsa, ga, hsb * gb), r * (kInvSqrtPi * kExpHalf), P);
+    const double M = rho * F;
+    const double pa = FRAME ? fma(aa, t.x, -(ab * t.y)) : aa;
+    const double pb = FRAME ? fma(aa, t.y, ab * t.x) : ab;
+    return {M, fma(p, pa, u1 * M), fma(p, pb, u2 * M),
+            p * fma((inv_gm1 + 0.5) + bu, F, 0.5 * P)};
+}
+
 template <bool FRAME, bool G14>
 __device__ __forceinline__ D4 end_sum(const D4& q, const D2& t, double hwa, double hsa,
                                       double hwb, double hsb, double inv_gm1,
@@ -746,15 +762,8 @@ __device__ __forceinline__ D4 end_sum(const D4& q, const D2& t, double hwa, doub
     unit_or_outer(Sb, tb, lead, erb, gb);
     const double e = exp_lead(q.x + bu, lead);
     const double rho = G14 ? e * (r2 * r2 * r) : e * exp(-inv_gm1 * log(beta));
-    const double p = rho * i2b;
-    const double aa = fma(hsa, era, hwa), ab = fma(hsb, erb, hwb);  // w A
-    const double P = fma(ua, aa, ub * ab);
-    const double F = fma(fma(hsa, ga, hsb * gb), r * (kInvSqrtPi * kExpHalf), P);
-    const double M = rho * F;
-    const double pa = FRAME ? fma(aa, t.x, -(ab * t.y)) : aa;
-    const double pb = FRAME ? fma(aa, t.y, ab * t.x) : ab;
-    return {M, fma(p, pa, u1 * M), fma(p, pb, u2 * M),
-            p * fma((inv_gm1 + 0.5) + bu, F, 0.5 * P)};
+    return weighted_flux<FRAME>(rho, rho * i2b, r, u1, u2, ua, ub, bu, era, ga, erb, gb, t, hwa, hsa,
+                                hwb, hsb, inv_gm1);
 }
 
 // One (point, neighbour) pair of the residual sum (eq. 11): the q~
@@ -799,7 +808,6 @@ struct ResidualArgs {
     D4* R;
     double* Dg;
     D4* jv0;
-    D4* jv2;
     F4* jv0f;
     F4* jv2f;
     float* Df;
@@ -961,12 +969,7 @@ __device__ __forceinline__ void residual_finish(int64_t p, int8_t ty, const Resi
     const double usq = u1 * u1 + u2 * u2;
     const double pr = (A.gamma - 1.0) * (u.w - 0.5 * rho * usq);
     const double beta = 0.5 * rho / pr;
-    const double sb = sqrt(beta);
-    const double sx = u1 * sb, sy = u2 * sb;
     const D4 j0 = {rho, u1, u2, pr};
-    D4 j2;
-    erf_exp(sx, j2.x, j2.y);
-    erf_exp(sy, j2.z, j2.w);
     const double a = sqrt(A.gamma * pr / rho);
     const PointGeom& Gp = A.geom[p];
     const double hn = gload(&Gp.lsq, 0).w;  // nearest-neighbour distance
@@ -1056,12 +1059,16 @@ __device__ __forceinline__ void residual_finish(int64_t p, int8_t ty, const Resi
             for (int v = 0; v < 4; ++v) Sv[v] = Rp[v] - Sv[v];
     }
     if (MIXED) {
+        // erf and exp of the fp32 sweeps, formed in double precision
+        const double sb = sqrt(beta), sx = u1 * sb, sy = u2 * sb;
+        D4 j2;
+        erf_exp(sx, j2.x, j2.y);
+        erf_exp(sy, j2.z, j2.w);
         gstore(A.jv0f, p, F4{(float)j0.x, (float)j0.y, (float)j0.z, (float)j0.w});
         gstore(A.jv2f, p, F4{(float)j2.x, (float)j2.y, (float)j2.z, (float)j2.w});
         gstore(A.Df, p, (float)Dp);
     } else {
         gstore(A.jv0, p, j0);
-        gstore(A.jv2, p, j2);
         gstore(A.Dg, p, Dp);
     }
     // the forward sweep's first colour phase: its points have no lower
@@ -1338,109 +1345,92 @@ __global__ void k_reset_components(int ncomp, int32_t* __restrict__ active,
 // ---------------------------------------------------------------------------
 // Split-flux Jacobian-vector products for the sweeps.
 // ---------------------------------------------------------------------------
-template <class T>
-struct Lin {  // linearisation data of one neighbour
-    T rho, u1, u2, p, sb, beta, irho, ip;
-};
-
-// Tangent of the split flux along unit direction (dx, dy) with sign sg,
-// given erf(S) and exp(-S^2) at the linearisation state.  Hand-written
-// forward-mode derivative of the closed-form split flux (the paper's exact
-// Jacobian-vector product): with rho', u', p' from dU,
-//   beta' = (rho' - 2 beta p')/(2p),  S' = u_d' sqrt(beta) + u_d beta'/(2 sqrt(beta)),
-//   A' = sg exp(-S^2) S'/sqrt(pi),    B' = B (-2 S S' - beta'/(2 beta)),
-// and the product rule on each flux component.
-template <class T>
-__device__ __forceinline__ void jvp_exact(const Lin<T>& L, T er, T g, T dx, T dy, T sg,
-                                          const T dU[4], T gm1, T inv_gm1, T J[4]) {
-    const T rd = dU[0];
-    const T u1d = (dU[1] - L.u1 * rd) * L.irho;
-    const T u2d = (dU[2] - L.u2 * rd) * L.irho;
-    const T usq = L.u1 * L.u1 + L.u2 * L.u2;
-    const T pd = gm1 * (dU[3] - T(0.5) * rd * usq - L.rho * (L.u1 * u1d + L.u2 * u2d));
-    const T bd = (rd - T(2) * L.beta * pd) * (T(0.5) * L.ip);
-    const T ud = L.u1 * dx + L.u2 * dy;
-    const T udd = u1d * dx + u2d * dy;
-    const T ib = T(2) * L.p * L.irho;  // 1/beta = 2p/rho, without a division
-    const T isb = L.sb * ib;           // 1/sqrt(beta)
-    const T S = ud * L.sb;
-    const T Sd = udd * L.sb + T(0.5) * ud * bd * isb;
-    const T A = T(0.5) * (T(1) + sg * er);
-    const T Ad = sg * g * Sd * T(kInvSqrtPi);
-    const T B = g * T(0.5 * kInvSqrtPi) * isb;
-    const T Bd = B * (T(-2) * S * Sd - T(0.5) * bd * ib);
-    const T F = ud * A + sg * B;
-    const T Fd = udd * A + ud * Ad + sg * Bd;
-    const T rhoE = L.p * inv_gm1 + T(0.5) * L.rho * usq;
-    const T J0 = rd * F + L.rho * Fd;
-    const T mass = L.rho * F;
-    const T pAd = pd * A + L.p * Ad;
-    J[0] = J0;
-    J[1] = pAd * dx + u1d * mass + L.u1 * J0;
-    J[2] = pAd * dy + u2d * mass + L.u2 * J0;
-    J[3] = (dU[3] + pd) * ud * A + (rhoE + L.p) * (udd * A + ud * Ad) +
-           sg * ((dU[3] + T(0.5) * pd) * B + (rhoE + T(0.5) * L.p) * Bd);
+// Half the split weight and its signed copy, (w/2, sg w/2), from a list
+// entry's weight and its negative-offset bit (sg = +1 when set).
+__device__ __forceinline__ double signed_half(double hw, uint8_t cd, int neg_bit) {
+    const uint64_t flip = (uint64_t)((~(uint32_t)cd >> neg_bit) & 1u) << 63;
+    return __longlong_as_double((int64_t)((uint64_t)__double_as_longlong(hw) ^ flip));
+}
+__device__ __forceinline__ float signed_half(float hw, uint8_t cd, int neg_bit) {
+    return __uint_as_float(__float_as_uint(hw) ^ (((~(uint32_t)cd >> neg_bit) & 1u) << 31));
 }
 
-// Split flux from the linearisation data (value only, used by the
-// flux-difference products).
-__device__ __forceinline__ void flux_lin(const Lin<double>& L, double er, double g, double dx,
-                                         double dy, double sg, double inv_gm1, double G[4]) {
-    const double ud = L.u1 * dx + L.u2 * dy;
-    const double A = 0.5 * (1.0 + sg * er);
-    const double B = g * (0.5 * kInvSqrtPi) / L.sb;
-    const double rhoE = L.p * inv_gm1 + 0.5 * L.rho * (L.u1 * L.u1 + L.u2 * L.u2);
-    const double mass = L.rho * (ud * A + sg * B);
-    G[0] = mass;
-    G[1] = L.p * A * dx + L.u1 * mass;
-    G[2] = L.p * A * dy + L.u2 * mass;
-    G[3] = (rhoE + L.p) * ud * A + sg * (rhoE + 0.5 * L.p) * B;
+// The reciprocal of rho p (one for 1/rho and 1/p) and 1/sqrt(beta) of a
+// physical state: hardware seeds refined to double precision without the
+// guards of a division; the fp32 sweeps use the seeds (about 1 ulp).
+__device__ __forceinline__ double recip_pos(double x) {
+    double y = __builtin_amdgcn_rcp(x);
+    y = fma(fma(-x, y, 1.0), y, y);
+    return fma(fma(-x, y, 1.0), y, y);
+}
+__device__ __forceinline__ float recip_pos(float x) { return __builtin_amdgcn_rcpf(x); }
+__device__ __forceinline__ float rsqrt_pos(float x) { return __builtin_amdgcn_rsqf(x); }
+
+// Adds sum_d w_d A_d(U_i) dU_i over the two split directions of the point to
+// acc (d = x, y, or t, n of a frame point): the exact tangent of the weighted
+// split fluxes of weighted_flux (the paper's exact Jacobian-vector product).
+// With rho', u', p' from dU, beta' = (rho' - 2 beta p')/(2p) and
+// h = beta'/(2 beta), differentiating F_d = u_d A_d + sg_d B_d leaves
+//   F_d' = u_d' A_d - h sg_d B_d
+// (the terms in S_d' cancel), and A_d' = sg_d exp(-S_d^2) S_d'/sqrt(pi),
+// S_d' = sqrt(beta) (u_d' + h u_d).  With P = sum w u_d A_d, P' = sum w u_d' A_d,
+// Q = sum w sg_d B_d, X_d = w A_d':
+//   mass      rho' F + rho F',  F = P + Q, F' = P' - h Q
+//   momentum  sum_d (p' w A_d + p X_d) d + u_i' rho F + u_i mass
+//   energy    E' F + p' (P + Q/2) + (rhoE + p/2) F' + (p/2) (P' + sum_d u_d X_d)
+// About 130 instructions in double precision, erf and exp included; two
+// separate directions took about 160 with erf and exp gathered.
+// ga, gb are exp(-S^2), scaled by e^(1/2) in double precision (erf_exp_unit).
+template <bool FRAME, class T>
+__device__ __forceinline__ void weighted_jvp(const Vec4<T>& a, const Vec4<T>& d, T irho, T beta,
+                                             T isb, T sb, T ua, T ub, T era, T ga, T erb, T gb,
+                                             T tx, T ty, T hwa, T hsa, T hwb, T hsb, T gm1,
+                                             T inv_gm1, T acc[4]) {
+    constexpr T kC = T(std::is_same_v<T, double> ? kInvSqrtPi * kExpHalf : kInvSqrtPi);
+    const T u1d = (d.y - a.y * d.x) * irho, u2d = (d.z - a.z * d.x) * irho;
+    const T hu2 = T(0.5) * (a.y * a.y + a.z * a.z);
+    const T pd = gm1 * (d.w - d.x * hu2 - a.x * (a.y * u1d + a.z * u2d));
+    const T h = (d.x - (T(2) * beta) * pd) * (T(0.5) * irho);
+    const T uad = FRAME ? u1d * tx + u2d * ty : u1d, ubd = FRAME ? u2d * tx - u1d * ty : u2d;
+    const T aa = hsa * era + hwa, ab = hsb * erb + hwb;  // w A
+    const T Ga = hsa * ga, Gb = hsb * gb;
+    const T P = ua * aa + ub * ab, Pd = uad * aa + ubd * ab;
+    const T Q = (Ga + Gb) * (isb * kC);
+    const T c = T(2) * kC * sb;
+    const T Xa = Ga * c * (uad + h * ua), Xb = Gb * c * (ubd + h * ub);
+    const T F = P + Q, Fd = Pd - h * Q;
+    const T m = d.x * F + a.x * Fd, rF = a.x * F;
+    const T va = pd * aa + a.w * Xa, vb = pd * ab + a.w * Xb;
+    const T hE = a.w * (inv_gm1 + T(0.5)) + a.x * hu2;
+    acc[0] += m;
+    acc[1] += (FRAME ? va * tx - vb * ty : va) + u1d * rF + a.y * m;
+    acc[2] += (FRAME ? va * ty + vb * tx : vb) + u2d * rF + a.z * m;
+    acc[3] += d.w * F + pd * (P + T(0.5) * Q) + hE * Fd +
+              (T(0.5) * a.w) * (Pd + ua * Xa + ub * Xb);
 }
 
-// Flux difference G(U + dU) - G(U) of eq. (28).
-__device__ __forceinline__ void jvp_fluxdiff(const Lin<double>& L, double er, double g, const D4& u,
-                                             double dx, double dy, double sg, const double dU[4],
-                                             double gamma, double inv_gm1, double J[4]) {
-    const double a0 = u.x + dU[0], a1 = u.y + dU[1], a2 = u.z + dU[2], a3 = u.w + dU[3];
-    Lin<double> W;
-    W.rho = a0;
-    W.irho = 1.0 / a0;
-    W.u1 = a1 * W.irho;
-    W.u2 = a2 * W.irho;
-    W.p = (gamma - 1.0) * (a3 - 0.5 * W.rho * (W.u1 * W.u1 + W.u2 * W.u2));
-    W.beta = 0.5 * W.rho / W.p;
-    W.sb = sqrt(W.beta);
-    const double S = (W.u1 * dx + W.u2 * dy) * W.sb;
-    double Ga[4], Gb[4], ea, xa;
-    erf_exp(S, ea, xa);
-    flux_lin(W, ea, xa, dx, dy, sg, inv_gm1, Ga);
-    flux_lin(L, er, g, dx, dy, sg, inv_gm1, Gb);
-#pragma unroll
-    for (int v = 0; v < 4; ++v) J[v] = Ga[v] - Gb[v];
-}
-
-// The linearisation data of neighbour i from its (rho, u1, u2, p) record: the
-// derived quantities are formed here rather than read, which halves the bytes
-// a sweep gathers per neighbour for them.
-// One reciprocal, of rho p, gives both 1/rho and 1/p; the fp32 sweeps use
-// the hardware reciprocal and square root (about 1 ulp).
-template <class T>
-__device__ __forceinline__ Lin<T> load_lin(const Vec4<T>* jv0, int32_t i) {
-    const Vec4<T> a = jv0[i];
-    T r, sb;
-    if constexpr (std::is_same_v<T, float>) {
-        r = __builtin_amdgcn_rcpf(a.x * a.w);
-    } else {
-        r = T(1) / (a.x * a.w);
-    }
-    const T irho = a.w * r, ip = a.x * r;
-    const T beta = T(0.5) * a.x * ip;
-    if constexpr (std::is_same_v<T, float>) {
-        sb = __builtin_amdgcn_sqrtf(beta);
-    } else {
-        sb = sqrt(beta);
-    }
-    return Lin<T>{a.x, a.y, a.z, a.w, sb, beta, irho, ip};
+// Weighted split fluxes of a conserved state, for the flux differences of
+// eq. (28).
+template <bool FRAME>
+__device__ __forceinline__ D4 state_flux(const D4& u, const D2& t, double hwa, double hsa,
+                                         double hwb, double hsb, double gm1, double inv_gm1,
+                                         const PolyLead& lead) {
+#pragma clang fp contract(off)
+    const double irho = recip_pos(u.x);
+    const double u1 = u.y * irho, u2 = u.z * irho;
+    const double usq = fma(u1, u1, u2 * u2);
+    const double p = gm1 * fma(-0.5 * u.x, usq, u.w);
+    const double beta = 0.5 * u.x * recip_pos(p);
+    const double r = rsqrt_pos(beta);
+    const double sb = beta * r;
+    const double ua = FRAME ? fma(u1, t.x, u2 * t.y) : u1;
+    const double ub = FRAME ? fma(u2, t.x, -(u1 * t.y)) : u2;
+    const double Sa = ua * sb, Sb = ub * sb;
+    double era, ga, erb, gb;
+    unit_or_outer(Sa, Sa * Sa, lead, era, ga);
+    unit_or_outer(Sb, Sb * Sb, lead, erb, gb);
+    return weighted_flux<FRAME>(u.x, p, r, u1, u2, ua, ub, beta * usq, era, ga, erb, gb, t, hwa,
+                                hsa, hwb, hsb, inv_gm1);
 }
 
 // Split weights and bits of the sweep-list entries of the colour-sorted point
@@ -1506,99 +1496,123 @@ __global__ void __launch_bounds__(kBlock) k_sweep_weights(int64_t n,
 // sum (eq. 22-27) from the entry's weights and split bits: interior points
 // use the x and y split the neighbour falls in, frame points the t split and
 // the normal split (n- at a wall, n+ at a far-field outer point) in the frame
-// t of point p.
-template <class T, int MODE>
-__device__ __forceinline__ void sweep_contrib(uint8_t cd, const D2* __restrict__ frame, int32_t p,
-                                              const W2<T>& w, int32_t i,
-                                              const Vec4<T>* __restrict__ jv0,
-                                              const Vec4<T>* __restrict__ jv2,
-                                              const D4* __restrict__ U,
-                                              const Vec4<T>* __restrict__ dU, double gamma,
-                                              T acc[4]) {
-    const T gm1 = T(gamma - 1.0), inv_gm1 = T(1.0 / (gamma - 1.0));
-    const Vec4<T> di = dU[i];
-    const T dv[4] = {di.x, di.y, di.z, di.w};
-    const Lin<T> L = load_lin(jv0, i);
-    const Vec4<T> k2 = jv2[i];  // interior entries only; loaded with the rest
-    T J[4];
-    if (cd & kSwWall) {
-        // wall-frame directions: erf/exp at the neighbour state are formed here
-        const D2 t = frame[p];
-        T er, g;
-        if (cd & kSwA) {
-            const double sg = (cd & kSwNegA) ? 1.0 : -1.0;
-            if constexpr (MODE == 1) {
-                const double S = (L.u1 * t.x + L.u2 * t.y) * L.sb;
-                erf_exp(S, er, g);
-                jvp_fluxdiff(L, er, g, U[i], t.x, t.y, sg, dv, gamma,
-                             1.0 / (gamma - 1.0), J);
-            } else {
-                const T S = (L.u1 * T(t.x) + L.u2 * T(t.y)) * L.sb;
-                erf_exp(S, er, g);
-                jvp_exact<T>(L, er, g, T(t.x), T(t.y), T(sg), dv, gm1, inv_gm1, J);
-            }
-            const T wa = T(w.x);
-#pragma unroll
-            for (int v = 0; v < 4; ++v) acc[v] += wa * J[v];
+// t of point p.  A split that the neighbour is not in has weight zero.
+// The double-precision sweeps gather (rho, u1, u2, p) and dU of a neighbour,
+// 64 bytes, and form erf and exp of S; the fp32 sweeps gather those too (16
+// bytes more, formed in double precision by the residual kernel).
+template <bool FRAME, class T, int MODE>
+__device__ __forceinline__ void sweep_entry(uint8_t cd, const D2& t, const W2<T>& w, int32_t i,
+                                            const Vec4<T>* __restrict__ jv0,
+                                            const Vec4<T>* __restrict__ jv2,
+                                            const D4* __restrict__ U,
+                                            const Vec4<T>* __restrict__ dU, T gm1, T inv_gm1,
+                                            const PolyLead& lead, T acc[4]) {
+    const Vec4<T> d = dU[i];
+    const T hwa = T(0.5) * w.x, hwb = T(0.5) * w.y;
+    const T hsa = signed_half(hwa, cd, 1), hsb = signed_half(hwb, cd, 3);
+    if constexpr (MODE == 1) {
+        const D4 u = U[i];
+        const D4 v = {u.x + d.x, u.y + d.y, u.z + d.z, u.w + d.w};
+        const D4 f1 = state_flux<FRAME>(v, t, hwa, hsa, hwb, hsb, gm1, inv_gm1, lead);
+        const D4 f0 = state_flux<FRAME>(u, t, hwa, hsa, hwb, hsb, gm1, inv_gm1, lead);
+        acc[0] += f1.x - f0.x;
+        acc[1] += f1.y - f0.y;
+        acc[2] += f1.z - f0.z;
+        acc[3] += f1.w - f0.w;
+    } else {
+        const Vec4<T> a = jv0[i];
+        Vec4<T> k{};
+        if constexpr (std::is_same_v<T, float>) k = jv2[i];
+        const T rp = recip_pos(a.x * a.w);
+        const T irho = a.w * rp, beta = T(0.5) * a.x * (a.x * rp);
+        const T isb = rsqrt_pos(beta), sb = beta * isb;
+        const T tx = T(t.x), ty = T(t.y);
+        const T ua = FRAME ? a.y * tx + a.z * ty : a.y, ub = FRAME ? a.z * tx - a.y * ty : a.z;
+        if constexpr (std::is_same_v<T, double>) {
+            const T Sa = ua * sb, Sb = ub * sb;
+            unit_or_outer(Sa, Sa * Sa, lead, k.x, k.y);
+            unit_or_outer(Sb, Sb * Sb, lead, k.z, k.w);
+        } else if (FRAME) {  // frame directions: erf/exp at the neighbour state are formed here
+            erf_exp(ua * sb, k.x, k.y);
+            erf_exp(ub * sb, k.z, k.w);
         }
-        if (cd & kSwB) {
-            const double sg = (cd & kSwNegB) ? 1.0 : -1.0;
-            if constexpr (MODE == 1) {
-                const double S = (-L.u1 * t.y + L.u2 * t.x) * L.sb;
-                erf_exp(S, er, g);
-                jvp_fluxdiff(L, er, g, U[i], -t.y, t.x, sg, dv, gamma,
-                             1.0 / (gamma - 1.0), J);
-            } else {
-                const T S = (-L.u1 * T(t.y) + L.u2 * T(t.x)) * L.sb;
-                erf_exp(S, er, g);
-                jvp_exact<T>(L, er, g, T(-t.y), T(t.x), T(sg), dv, gm1, inv_gm1, J);
-            }
-            const T wb = T(w.y);
+        weighted_jvp<FRAME>(a, d, irho, beta, isb, sb, ua, ub, k.x, k.y, k.z, k.w, tx, ty, hwa, hsa,
+                            hwb, hsb, gm1, inv_gm1, acc);
+    }
+}
+
+// Cross-lane moves by data-parallel primitives (vector instructions; shuffles
+// go through LDS): xor 1 and 2 within a quad, the mirror of 8 lanes, which
+// takes a quad's lanes to the other quad's, and lane l of 16 to l + 8.
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppMirror8 = 0x141, kDppRotate8 = 0x128;
+constexpr int kDppQuad1 = 0x55, kDppQuad2 = 0xAA;  // broadcast of a quad's lane 1, 2
+
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) {
+    return __int_as_float(
+        __builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp(double v) {
+    return __hiloint2double(
+        __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true),
+        __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true));
+}
+
+// Sums of four values over a point's LANES (4, 8, 16) lanes, scattered: lane l
+// gets the sum of value l % 4.  Sixteen lanes come as (first, rest), a lane's
+// first entry and the sum of its others, and add up in the order of eight
+// lanes: entry l, then l + 8, l + 16, l + 24.  Lists of up to 32 entries thus
+// give the same bits with either.
+template <int LANES, class T>
+__device__ __forceinline__ T scatter_sum(T a[4], const T rest[4], int lane) {
+    if constexpr (LANES == 16) {
+        const bool low = lane < 8;
 #pragma unroll
-            for (int v = 0; v < 4; ++v) acc[v] += wb * J[v];
+        for (int v = 0; v < 4; ++v) {
+            const T other = dpp<kDppRotate8>(rest[v]);
+            const T f = dpp<kDppRotate8>(a[v]);
+            a[v] += f;
+            a[v] += low ? rest[v] : other;
+            a[v] += low ? other : rest[v];
         }
-        return;
     }
-    if (cd & kSwA) {
-        const T sg = (cd & kSwNegA) ? T(1) : T(-1);
-        if constexpr (MODE == 1)
-            jvp_fluxdiff(L, k2.x, k2.y, U[i], 1.0, 0.0, sg, dv, gamma, 1.0 / (gamma - 1.0), J);
-        else
-            jvp_exact<T>(L, k2.x, k2.y, T(1), T(0), sg, dv, gm1, inv_gm1, J);
-        const T wa = T(w.x);
 #pragma unroll
-        for (int v = 0; v < 4; ++v) acc[v] += wa * J[v];
-    }
-    if (cd & kSwB) {
-        const T sg = (cd & kSwNegB) ? T(1) : T(-1);
-        if constexpr (MODE == 1)
-            jvp_fluxdiff(L, k2.z, k2.w, U[i], 0.0, 1.0, sg, dv, gamma, 1.0 / (gamma - 1.0), J);
-        else
-            jvp_exact<T>(L, k2.z, k2.w, T(0), T(1), sg, dv, gm1, inv_gm1, J);
-        const T wb = T(w.y);
-#pragma unroll
-        for (int v = 0; v < 4; ++v) acc[v] += wb * J[v];
-    }
+    for (int v = 0; v < 4; ++v)
+        if (LANES >= 8) a[v] += dpp<kDppMirror8>(a[v]);
+    const bool hi = lane & 2, odd = lane & 1;
+    T x0 = hi ? a[2] : a[0], x1 = hi ? a[3] : a[1];
+    x0 += dpp<kDppXor2>(hi ? a[0] : a[2]);
+    x1 += dpp<kDppXor2>(hi ? a[1] : a[3]);
+    return (odd ? x1 : x0) + dpp<kDppXor1>(odd ? x0 : x1);
 }
 
 // One colour phase of a sweep (eq. 27).  FWD: dU*_0 = -(R_0 + sum_lower w A dU*) / D_0;
 // backward: dU_0 = dU*_0 - (sum_upper w A dU) / D_0.  MODE 0 exact tangent,
 // 1 flux difference.  T is the arithmetic of the products and increments.
 // LANES consecutive lanes share one point: each walks every LANES-th entry of
-// the point's lower (forward) or upper (backward) list, and the partial sums
-// are combined with cross-lane shuffles.  The phase's points are the
-// colour-sorted positions [start, start + count) and their lists one
-// contiguous block.
+// the point's lower (forward) or upper (backward) list.  From four lanes on,
+// the partial sums are scattered so that lane v finishes component v, its own
+// data requested with the list entries; below, lane 0 finishes the point.  The
+// phase's points are the colour-sorted positions [start, start + count) and
+// their lists one contiguous block.
+// Bound by the bytes gathered at 2,621,440 points (each phase re-reads the
+// records of the colours around its points) and by the dependent loads of a
+// phase at small ones.  Forward sweep, eight lanes, FP64: 600 us with erf and
+// exp of S gathered beside the state and lane 0 finishing a point, 446 us now;
+// 163,840 points 78 and 66 us; flux differences there 111 and 78 us; 640,000
+// points in mixed precision 145 and 119 us.
 template <class T, bool FWD, int MODE, int LANES>
-__global__ void __launch_bounds__(kBlock, 5) k_sweep(
+__global__ void __launch_bounds__(kBlock, MODE == 1 || LANES == 16 ? 4 : 5) k_sweep(
     int32_t start, int32_t count, const int32_t* __restrict__ col_perm,
     const D2* __restrict__ frame, const int8_t* __restrict__ type,
     const int32_t* __restrict__ loff, const int32_t* __restrict__ lidx,
     const W2<T>* __restrict__ lw, const uint8_t* __restrict__ lcode,
-    const int32_t* __restrict__ comp, const int32_t* __restrict__ active,
+    const int32_t* __restrict__ qcomp, const int32_t* __restrict__ active,
     const Vec4<T>* __restrict__ jv0, const Vec4<T>* __restrict__ jv2,
     const D4* __restrict__ U, const D4* __restrict__ R,
     const T* __restrict__ Dg, Vec4<T>* __restrict__ dU, double gamma, int farfield) {
+    constexpr bool SCATTER = LANES >= 4;
     const int gt = xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
     const int pt = gt / LANES, lane = gt % LANES;
     if (pt >= count) return;  // uniform over the lanes of a point
@@ -1610,9 +1624,9 @@ __global__ void __launch_bounds__(kBlock, 5) k_sweep(
     const int32_t q = start + pt;
     const int32_t p = col_perm[q];
     const int32_t e0 = loff[q], e1 = loff[q + 1];
-    if (comp && !active[comp[p]]) return;  // retired component of a batch (uniform per point)
-    if (!comp && !active[0]) return;
-    // the lane's first list entry, requested before the point's own record
+    const int32_t k = qcomp ? qcomp[q] : 0;
+    if (!qcomp && !active[0]) return;  // beside the loads above, not before them
+    // the lane's first list entry, then the point's own record
     int32_t e = e0 + lane;
     uint8_t cd = 0;
     W2<T> w = {T(0), T(0)};
@@ -1622,7 +1636,22 @@ __global__ void __launch_bounds__(kBlock, 5) k_sweep(
         w = lw[e];
         i = lidx[e];
     }
+    const int v = lane & 3;
+    T own = T(0), dg = T(1);
+    int8_t ty = kInterior;
+    if (SCATTER) {
+        ty = type[p];
+        dg = Dg[p];
+        own = FWD ? T(reinterpret_cast<const double*>(R + p)[v])
+                  : reinterpret_cast<const T*>(dU + p)[v];
+    }
+    // retired component of a batch (uniform per point): looked up beside the
+    // loads above, not before them
+    if (qcomp && !active[k]) return;
+    const T gm1 = T(gamma - 1.0), inv_gm1 = T(1.0 / (gamma - 1.0));
+    const PolyLead lead = poly_lead<T>();
     T acc[4] = {T(0), T(0), T(0), T(0)};
+    T first[4] = {T(0), T(0), T(0), T(0)};  // sixteen lanes: the first entry's part
     while (e < e1) {
         // the next entry is requested before this one's neighbour data is used;
         // past the end the last entry is re-read (in bounds) and not used
@@ -1631,53 +1660,74 @@ __global__ void __launch_bounds__(kBlock, 5) k_sweep(
         const uint8_t cdn = lcode[ec];
         const W2<T> wn = lw[ec];
         const int32_t in = lidx[ec];
-        sweep_contrib<T, MODE>(cd, frame, p, w, i, jv0, jv2, U, dU, gamma, acc);
+        if (cd & kSwWall)
+            sweep_entry<true, T, MODE>(cd, frame[p], w, i, jv0, jv2, U, dU, gm1, inv_gm1, lead, acc);
+        else
+            sweep_entry<false, T, MODE>(cd, D2{1.0, 0.0}, w, i, jv0, jv2, U, dU, gm1, inv_gm1, lead,
+                                        acc);
+        if constexpr (LANES == 16)
+            if (e < e0 + LANES) {
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    first[c] = acc[c];
+                    acc[c] = T(0);
+                }
+            }
         cd = cdn;
         w = wn;
         i = in;
         e = en;
     }
-#pragma unroll
-    for (int o = LANES / 2; o > 0; o >>= 1)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) acc[v] += __shfl_xor(acc[v], o, 64);
-    if (lane != 0) return;
-    // the point's own data is read after the walk, by the one lane that uses
-    // it: held through the walk it cost every lane ten registers
-    const int8_t ty = type[p];
-    const T dg = Dg[p];
-    Vec4<T> own;
-    if (FWD) {
-        const D4 r = R[p];
-        own = {T(r.x), T(r.y), T(r.z), T(r.w)};
+    if constexpr (SCATTER) {
+        const T sum = LANES == 16 ? scatter_sum<LANES>(first, acc, lane)
+                                  : scatter_sum<LANES>(acc, first, lane);
+        T out = FWD ? -(own + sum) / dg : own - sum / dg;
+        if (ty == kOuter && !farfield) {
+            if (!FWD) return;
+            out = T(0);
+        }
+        if (ty == kWall) {
+            const D2 t = frame[p];
+            const T nx = T(-t.y), ny = T(t.x);
+            const T mn = dpp<kDppQuad1>(out) * nx + dpp<kDppQuad2>(out) * ny;
+            out -= v == 1 ? mn * nx : (v == 2 ? mn * ny : T(0));
+        }
+        if (lane < 4) reinterpret_cast<T*>(dU + p)[v] = out;
     } else {
-        own = dU[p];
+        if constexpr (LANES == 2)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) acc[c] += dpp<kDppXor1>(acc[c]);
+        if (lane != 0) return;
+        ty = type[p];
+        dg = Dg[p];
+        Vec4<T> o;
+        if (FWD) {
+            const D4 r = R[p];
+            o = {T(r.x), T(r.y), T(r.z), T(r.w)};
+        } else {
+            o = dU[p];
+        }
+        if (ty == kOuter && !farfield) {
+            if (FWD) dU[p] = {T(0), T(0), T(0), T(0)};
+            return;
+        }
+        const T iD = T(1) / dg;
+        T out[4] = {o.x - acc[0] * iD, o.y - acc[1] * iD, o.z - acc[2] * iD, o.w - acc[3] * iD};
+        if (FWD) {
+            out[0] = -(o.x + acc[0]) * iD;
+            out[1] = -(o.y + acc[1]) * iD;
+            out[2] = -(o.z + acc[2]) * iD;
+            out[3] = -(o.w + acc[3]) * iD;
+        }
+        if (ty == kWall) {
+            const D2 t = frame[p];
+            const T nx = T(-t.y), ny = T(t.x);
+            const T mn = out[1] * nx + out[2] * ny;
+            out[1] -= mn * nx;
+            out[2] -= mn * ny;
+        }
+        dU[p] = {out[0], out[1], out[2], out[3]};
     }
-    if (ty == kOuter && !farfield) {
-        if (FWD) dU[p] = {T(0), T(0), T(0), T(0)};
-        return;
-    }
-    const T iD = T(1) / dg;
-    T out[4];
-    if (FWD) {
-        out[0] = -(own.x + acc[0]) * iD;
-        out[1] = -(own.y + acc[1]) * iD;
-        out[2] = -(own.z + acc[2]) * iD;
-        out[3] = -(own.w + acc[3]) * iD;
-    } else {
-        out[0] = own.x - acc[0] * iD;
-        out[1] = own.y - acc[1] * iD;
-        out[2] = own.z - acc[2] * iD;
-        out[3] = own.w - acc[3] * iD;
-    }
-    if (ty == kWall) {
-        const D2 t = frame[p];
-        const T nx = T(-t.y), ny = T(t.x);
-        const T mn = out[1] * nx + out[2] * ny;
-        out[1] -= mn * nx;
-        out[2] -= mn * ny;
-    }
-    dU[p] = {out[0], out[1], out[2], out[3]};
 }
 
 // U += dU (Section 3) and the q-variables of the new state (eq. 14).
@@ -1949,7 +1999,7 @@ static void residual_lanes(State& s, bool in_step) {
                          c.lnbr,     c.tile_off,  c.tile_idx, s.U,
                          s.q,        s.prm.limiter ? s.qxl : s.qx[s.qsel],
                          s.prm.limiter ? s.qyl : s.qy[s.qsel], s.R,
-                         s.D,        s.jv0,       s.jv2,      s.jv0f,
+                         s.D,        s.jv0,       s.jv0f,
                          s.jv2f,     s.Df,        s.rr,       s.flags,
                          s.prm.variant, s.prm.jvp_mode, s.dU, s.dUf,
                          s.Rs,       c.colour,    in_step && fused_first_colour(s),
@@ -2043,13 +2093,13 @@ static void sweep_lanes(State& s, bool forward, const Vec4<T>* jv0, const Vec4<T
         if (forward)
             hipLaunchKernelGGL((k_sweep<T, true, MODE, LANES>), g, b, 0, s.stream, start, cnt,
                                c.col_perm, c.frame, c.type, c.lo_off, c.lo_idx,
-                               list_weights<T>(c.lo_w, c.lo_wf), c.lo_code, c.comp, s.active,
+                               list_weights<T>(c.lo_w, c.lo_wf), c.lo_code, c.qcomp, s.active,
                                jv0, jv2, s.U, s.prm.variant ? s.Rs : s.R, Dg, dU,
                                s.prm.gamma, s.prm.farfield);
         else
             hipLaunchKernelGGL((k_sweep<T, false, MODE, LANES>), g, b, 0, s.stream, start, cnt,
                                c.col_perm, c.frame, c.type, c.up_off, c.up_idx,
-                               list_weights<T>(c.up_w, c.up_wf), c.up_code, c.comp, s.active,
+                               list_weights<T>(c.up_w, c.up_wf), c.up_code, c.qcomp, s.active,
                                jv0, jv2, s.U, s.R, Dg, dU, s.prm.gamma, s.prm.farfield);
     }
 }
@@ -2085,11 +2135,11 @@ hipError_t launch_sweep_dir(State& s, bool forward) {
                                c.n, s.dU);
     }
     if (s.prm.precision == 1)
-        sweep_t<float, 0>(s, forward, s.jv0f, s.jv2f, s.Df, s.dUf);
+        sweep_t<float, 0>(s, forward, s.jv0f, (const F4*)s.jv2f, s.Df, s.dUf);
     else if (s.prm.jvp_mode == 1)
-        sweep_t<double, 1>(s, forward, s.jv0, s.jv2, s.D, s.dU);
+        sweep_t<double, 1>(s, forward, s.jv0, (const D4*)nullptr, s.D, s.dU);
     else
-        sweep_t<double, 0>(s, forward, s.jv0, s.jv2, s.D, s.dU);
+        sweep_t<double, 0>(s, forward, s.jv0, (const D4*)nullptr, s.D, s.dU);
     return hipGetLastError();
 }
 

@@ -87,6 +87,7 @@ struct Cloud {
     D2* lo_w = nullptr;
     F2* lo_wf = nullptr;  // the weights rounded to fp32 (mixed-precision sweeps)
     uint8_t* lo_code = nullptr;
+    int32_t max_list = 0;  // longest list of either kind
     int32_t* up_off = nullptr;
     int32_t* up_idx = nullptr;
     D2* up_w = nullptr;
@@ -98,6 +99,7 @@ struct Cloud {
     // one component and comp == nullptr.
     int32_t ncomp = 1;
     int32_t* comp = nullptr;        // component of each point (batch clouds only)
+    int32_t* qcomp = nullptr;       // the same in colour-sorted point order
     int32_t* comp_off = nullptr;    // device, ncomp + 1
     int32_t* wall_off = nullptr;    // device, ncomp + 1
     std::vector<int64_t> h_comp_off, h_wall_off, h_comp_active;
@@ -188,11 +190,10 @@ struct State {
     D4* Rs = nullptr;    // forward-sweep right-hand side R - S (Manish variant)
     D4* dU = nullptr;    // increment; kept between iterations (zero after a new U)
     D4* jv0 = nullptr;   // (rho, u1, u2, p) at the state the sweeps linearise about
-    D4* jv2 = nullptr;   // (erf(Sx), exp(-Sx^2), erf(Sy), exp(-Sy^2))
     double* D = nullptr; // scalar diagonal
     // fp32 copies for the mixed-precision sweeps
     F4* jv0f = nullptr;
-    F4* jv2f = nullptr;
+    F4* jv2f = nullptr;  // (erf(Sx), exp(-Sx^2), erf(Sy), exp(-Sy^2))
     F4* dUf = nullptr;
     float* Df = nullptr;
     // reductions

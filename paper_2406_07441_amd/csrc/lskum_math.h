@@ -61,9 +61,10 @@ __device__ __forceinline__ double exp_fast(double x) {
 struct PolyLead {
     double erf, exp;
 };
+template <class T = double>  // unused by single precision
 __device__ __forceinline__ PolyLead poly_lead() {
     PolyLead l{kErfP[0], kExpN[0]};
-    asm volatile("" : "+v"(l.erf), "+v"(l.exp));
+    if constexpr (std::is_same_v<T, double>) asm volatile("" : "+v"(l.erf), "+v"(l.exp));
     return l;
 }
 

@@ -59,3 +59,51 @@ def test_residual_lanes_and_gamma(lk, nw, nk, lanes, gamma):
     e = max(np.abs(R[v] - Ro[v]).max() / np.abs(Ro[v]).max() for v in range(4))
     print(f"residual {nw}x{nk} lanes {lanes} gamma {gamma}: {e:.2e}")
     assert e < 1e-11 and abs(res - reso) <= 1e-11 * reso
+
+
+@pytest.mark.parametrize("kw", [dict(), dict(precision=1), dict(jvp_mode=1), dict(farfield=1)])
+def test_sweeps_of_8_and_16_lanes_agree_bitwise(lk, kw):
+    """Lists of at most 32 entries: sixteen lanes add in the order of eight."""
+    gc = lk.Cloud(cg.ogrid(96, 24, r=1.12))
+    got = []
+    for lanes in (8, 16):
+        st = lk.State(gc, 0.6, 2.0, lk.default_params(cfl=50.0, limiter=1, sweep_lanes=lanes, **kw))
+        for _ in range(3):
+            st.step(want_res=False)
+        got.append((st.get_dU(), st.get_U()))
+        st.close()
+    assert np.array_equal(got[0][0], got[1][0]) and np.array_equal(got[0][1], got[1][1])
+
+
+def _ring(cloud, r):
+    """The box cloud with every point within r rows and columns as neighbour."""
+    nx, ny = cloud.nw, cloud.nk
+    off, idx = [0], []
+    for p in range(cloud.n):
+        j, k = p % nx, p // nx
+        idx += [q * nx + i for q in range(max(0, k - r), min(ny, k + r + 1))
+                for i in range(max(0, j - r), min(nx, j + r + 1)) if q * nx + i != p]
+        off.append(len(idx))
+    cloud.nbr_off, cloud.nbr_idx = np.array(off, np.int32), np.array(idx, np.int32)
+    return cloud
+
+
+@pytest.mark.parametrize("lanes", [0, 1, 2, 4, 8, 16])
+def test_sweeps_with_long_lists(lk, lanes):
+    """Up to 80 neighbours a point (lists beyond 32 entries) at every lane
+    count, wall and outer points among them: one increment against the oracle,
+    the suite's bar of 1e-11."""
+    cloud = _ring(cg.box(15, 14, wall_bottom=True), 4)
+    kw = dict(cfl=5.0, inner_iters=0)
+    o = O.Oracle(cloud, mach=0.4, aoa_deg=0.0, **kw)
+    rng = np.random.default_rng(5)
+    U = o.free_stream() * (1.0 + 0.01 * rng.uniform(-1, 1, (4, cloud.n)))
+    U[2, cloud.type == 0] = 0.0
+    _, _, dUo, _ = o.iteration(U)
+    st = lk.State(lk.Cloud(cloud), 0.4, 0.0, lk.default_params(sweep_lanes=lanes, **kw))
+    st.set_U(U)
+    st.step()
+    dU = st.get_dU()
+    e = max(np.abs(dU[v] - dUo[v]).max() / np.abs(dUo[v]).max() for v in range(4))
+    print(f"long lists, {lanes} lanes: {e:.2e}")
+    assert e < 1e-11
