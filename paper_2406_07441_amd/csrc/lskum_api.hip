@@ -59,7 +59,7 @@ hipError_t upload(T* dst, const T* src, size_t count) {
 
 void free_cloud(lskum::Cloud& c) {
     void* ptrs[] = {c.xy,     c.frame,     c.type,   c.off,      c.idx,      c.colour,
-                    c.col_perm, c.wall_list, c.geom, c.lo_off,   c.lo_idx,   c.up_off,
+                    c.col_perm, c.wall_list, c.geom, c.lsq, c.lo_off,   c.lo_idx,   c.up_off,
                     c.up_idx, c.lo_w,      c.up_w,     c.lo_code,  c.up_code,  c.comp, c.qcomp,
                     c.lo_wf, c.up_wf,
                     c.comp_off, c.wall_off, c.comp_inv_active,
@@ -248,6 +248,7 @@ int upload_cloud(lskum::Cloud& c) {
     chk(dalloc(&c.col_perm, n));
     chk(dalloc(&c.wall_list, wall.size()));
     chk(dalloc(&c.geom, n));
+    chk(dalloc(&c.lsq, n));
     if (c.ntile) {
         chk(dalloc(&c.tile_pts, tiles.pts.size()));
         chk(dalloc(&c.tile_off, tiles.off.size()));

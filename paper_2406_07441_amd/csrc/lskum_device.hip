@@ -130,6 +130,7 @@ __global__ void __launch_bounds__(kBlock) k_precompute(int64_t n, const D2* __re
                                                        const int32_t* __restrict__ off,
                                                        const int32_t* __restrict__ idx,
                                                        PointGeom* __restrict__ geom,
+                                                       D4* __restrict__ lsq,
                                                        unsigned long long* __restrict__ counts) {
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= n) return;
@@ -174,9 +175,9 @@ __global__ void __launch_bounds__(kBlock) k_precompute(int64_t n, const D2* __re
     const double det = sxx * syy - sxy * sxy;
     if (!(det > 1e-12 * sxx * syy)) {
         atomicAdd(&counts[0], 1ull);  // singular full stencil
-        g.lsq = {0, 0, 0, sqrt(rmin2)};
+        lsq[p] = {0, 0, 0, sqrt(rmin2)};
     } else {
-        g.lsq = {syy / det, -sxy / det, sxx / det, sqrt(rmin2)};
+        lsq[p] = {syy / det, -sxy / det, sxx / det, sqrt(rmin2)};
     }
     const int nsplit = ty == kInterior ? 4 : 3;
     double cb[4] = {0, 0, 0, 0}, cab[4] = {0, 0, 0, 0};
@@ -266,6 +267,52 @@ __global__ void __launch_bounds__(kBlock) k_q_from_U(int64_t n, double gamma,
     if (bad) flags[0] = 1;
 }
 
+// Cross-lane moves by data-parallel primitives (vector instructions; shuffles
+// go through LDS): xor 1 and 2 within a quad, the mirror of 8 lanes, which
+// takes a quad's lanes to the other quad's, and lane l of 16 to l + 8.
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppMirror8 = 0x141, kDppRotate8 = 0x128;
+constexpr int kDppQuad1 = 0x55, kDppQuad2 = 0xAA;  // broadcast of a quad's lane 1, 2
+
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) {
+    return __int_as_float(
+        __builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp(double v) {
+    return __hiloint2double(
+        __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true),
+        __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true));
+}
+
+// Sums of four values over a point's LANES (4, 8, 16) lanes, scattered: lane l
+// gets the sum of value l % 4.  Sixteen lanes come as (first, rest), a lane's
+// first entry and the sum of its others, and add up in the order of eight
+// lanes: entry l, then l + 8, l + 16, l + 24.  Lists of up to 32 entries thus
+// give the same bits with either.
+template <int LANES, class T>
+__device__ __forceinline__ T scatter_sum(T a[4], const T rest[4], int lane) {
+    if constexpr (LANES == 16) {
+        const bool low = lane < 8;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const T other = dpp<kDppRotate8>(rest[v]);
+            const T f = dpp<kDppRotate8>(a[v]);
+            a[v] += f;
+            a[v] += low ? rest[v] : other;
+            a[v] += low ? other : rest[v];
+        }
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+        if (LANES >= 8) a[v] += dpp<kDppMirror8>(a[v]);
+    const bool hi = lane & 2, odd = lane & 1;
+    T x0 = hi ? a[2] : a[0], x1 = hi ? a[3] : a[1];
+    x0 += dpp<kDppXor2>(hi ? a[0] : a[2]);
+    x1 += dpp<kDppXor2>(hi ? a[1] : a[3]);
+    return (odd ? x1 : x0) + dpp<kDppXor1>(odd ? x0 : x1);
+}
+
 // ---------------------------------------------------------------------------
 // q-derivatives (eq. 16): first-order pass and Jacobi inner passes, with the
 // optional limiter fused into the last pass.
@@ -344,7 +391,7 @@ constexpr int kDxyCache = 8;  // limiter: LDS slots per thread for neighbour off
 template <bool INNER, bool LIMIT, int LANES>
 __global__ void __launch_bounds__(kBlock, 4) k_qgrad(
     int64_t n, double K, const D2* __restrict__ xy, const int32_t* __restrict__ off,
-    const int32_t* __restrict__ idx, const PointGeom* __restrict__ geom,
+    const int32_t* __restrict__ idx, const D4* __restrict__ lsq,
     const int32_t* __restrict__ comp, const int32_t* __restrict__ active,
     const D4* __restrict__ q, const D4* __restrict__ qx_in, const D4* __restrict__ qy_in,
     D4* __restrict__ qx_out, D4* __restrict__ qy_out, D4* __restrict__ qxl,
@@ -409,8 +456,7 @@ __global__ void __launch_bounds__(kBlock, 4) k_qgrad(
         bx[v] = lane_sum<LANES>(bx[v]);
         by[v] = lane_sum<LANES>(by[v]);
     }
-    const PointGeom& G = geom[p];
-    const D4 L = G.lsq;
+    const D4 L = lsq[p];
     double gx[4], gy[4];
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
@@ -481,28 +527,68 @@ __global__ void __launch_bounds__(kBlock, 4) k_qgrad(
 // its neighbours in the order of k_qgrad<INNER, LIMIT, 4>; the compiler may
 // contract the products differently, so the two forms can differ in the
 // last bits.
+// The lanes' sums and extremes are scattered (data-parallel moves), lane v
+// getting component v's: it forms and stores that component's derivatives,
+// and the limiter's two divisions run for four components at once; the second
+// walk needs all components in every lane and gets them by quad broadcasts.
+// Both passes at 2,621,440 points: 553 us with all-lane sums by shuffles (which
+// go through LDS), lane 0 doing the limiter and a runtime stride of the staged
+// arrays; 454 us without; 418 us with the least-squares inverse in an array of
+// its own instead of a 160-byte record.  The limited pass then issues vector
+// instructions for 171 us of its time.
 static_assert(kQTile * 4 == kBlock, "a q-derivative tile is one point per four lanes");
 constexpr int kLnPre = 8;  // list positions per lane held in registers (a whole stencil of <= 32)
 
-template <bool INNER, bool LIMIT>
+// The usual stride of the staged arrays: a 16 x 4 block of points with 5 x 5
+// stencils lists 160 points, 18 KiB with derivatives.
+constexpr int kTileStride = 160;
+
+template <int C>
+__device__ __forceinline__ double quad_bcast(double v) {  // component C's value, held by lane C
+    return dpp<C * 0x55>(v);
+}
+
+// fmax and fmin as the one instruction they are.  The functions' operands are
+// first brought to a canonical form (an instruction each) wherever the
+// compiler cannot see that they are no signalling NaNs, as after a branch or a
+// cross-lane move; the instruction treats NaNs as the functions do.
+__device__ __forceinline__ double max_f64(double a, double b) {
+    double r;
+    asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ double min_f64(double a, double b) {
+    double r;
+    asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+
+// The largest / smallest of four values over a quad, scattered as scatter_sum.
+template <bool MAX>
+__device__ __forceinline__ double scatter_extreme(const double a[4], int lane) {
+    auto pick = [](double x, double y) { return MAX ? max_f64(x, y) : min_f64(x, y); };
+    const bool hi = lane & 2, odd = lane & 1;
+    const double x0 = pick(hi ? a[2] : a[0], dpp<kDppXor2>(hi ? a[0] : a[2]));
+    const double x1 = pick(hi ? a[3] : a[1], dpp<kDppXor2>(hi ? a[1] : a[3]));
+    return pick(odd ? x1 : x0, dpp<kDppXor1>(odd ? x0 : x1));
+}
+
+// S: stride of the staged arrays, at least the cloud's longest list (160 for
+// the 16 x 4 blocks of 5 x 5 stencils; kQTileMax otherwise).
+template <bool INNER, bool LIMIT, int S>
 __global__ void __launch_bounds__(kBlock, 4) k_qgrad_tiled(
     double K, const D2* __restrict__ xy, const int32_t* __restrict__ off,
     const int32_t* __restrict__ tile_pts, const uint16_t* __restrict__ lnbr,
     const int32_t* __restrict__ tile_off,
-    const int32_t* __restrict__ tile_idx, int32_t hmax, const PointGeom* __restrict__ geom,
+    const int32_t* __restrict__ tile_idx, const D4* __restrict__ lsq,
     const int32_t* __restrict__ comp, const int32_t* __restrict__ active,
     const D4* __restrict__ q, const D4* __restrict__ qx_in, const D4* __restrict__ qy_in,
     D4* __restrict__ qx_out, D4* __restrict__ qy_out, D4* __restrict__ qxl,
     D4* __restrict__ qyl) {
-    // one double array per field component (structure of arrays): the lanes
-    // of a wave read consecutive list positions, so 8-byte reads fall in
-    // distinct banks, where 32-byte records would put lanes four records
-    // apart into the same bank
-    extern __shared__ double smem[];
-    double* s_x = smem;
-    double* s_y = s_x + hmax;
-    double* s_q = s_y + hmax;                  // 4 components
-    double* s_g = s_q + 4 * hmax;              // 8 components (x then y derivatives)
+    // arrays of component pairs: the lanes of a wave read consecutive list
+    // positions, so 16-byte reads fall in distinct banks, and the fixed stride
+    // makes the arrays' offsets immediate operands
+    __shared__ D2 s_nb[(INNER ? 7 : 3) * S];  // (x, y), q, then q_x, q_y
     const int tile = xcd_block(blockIdx.x, gridDim.x);
     // the point's own data and its first list positions are requested before
     // the staging, so their latency overlaps it
@@ -517,7 +603,7 @@ __global__ void __launch_bounds__(kBlock, 4) k_qgrad_tiled(
         q0 = q[p];
         e0 = off[p];
         e1 = off[p + 1];
-        L = geom[p].lsq;
+        L = lsq[p];
         if (INNER) {
             gx0 = qx_in[p];
             gy0 = qy_in[p];
@@ -532,24 +618,16 @@ __global__ void __launch_bounds__(kBlock, 4) k_qgrad_tiled(
     const int32_t h0 = tile_off[tile], nh = tile_off[tile + 1] - h0;
     for (int32_t k = threadIdx.x; k < nh; k += kBlock) {
         const int32_t i = tile_idx[h0 + k];
-        const D2 r = xy[i];
         const D4 qi = q[i];
-        s_x[k] = r.x;
-        s_y[k] = r.y;
-        s_q[k] = qi.x;
-        s_q[hmax + k] = qi.y;
-        s_q[2 * hmax + k] = qi.z;
-        s_q[3 * hmax + k] = qi.w;
+        s_nb[k] = xy[i];
+        s_nb[S + k] = {qi.x, qi.y};
+        s_nb[2 * S + k] = {qi.z, qi.w};
         if (INNER) {
             const D4 gx = qx_in[i], gy = qy_in[i];
-            s_g[k] = gx.x;
-            s_g[hmax + k] = gx.y;
-            s_g[2 * hmax + k] = gx.z;
-            s_g[3 * hmax + k] = gx.w;
-            s_g[4 * hmax + k] = gy.x;
-            s_g[5 * hmax + k] = gy.y;
-            s_g[6 * hmax + k] = gy.z;
-            s_g[7 * hmax + k] = gy.w;
+            s_nb[3 * S + k] = {gx.x, gx.y};
+            s_nb[4 * S + k] = {gx.z, gx.w};
+            s_nb[5 * S + k] = {gy.x, gy.y};
+            s_nb[6 * S + k] = {gy.z, gy.w};
         }
     }
     __syncthreads();
@@ -560,24 +638,23 @@ __global__ void __launch_bounds__(kBlock, 4) k_qgrad_tiled(
     // a lane takes entries e0 + lane, e0 + lane + 4, ... in order: the first
     // kLnPre from registers, any further ones from memory
     auto first_walk = [&](int li) {
-        const double dx = s_x[li] - r0.x, dy = s_y[li] - r0.y;
-        const D4 qi = {s_q[li], s_q[hmax + li], s_q[2 * hmax + li], s_q[3 * hmax + li]};
-        double dq[4] = {qi.x - qv[0], qi.y - qv[1], qi.z - qv[2], qi.w - qv[3]};
+        const D2 r = s_nb[li], qa = s_nb[S + li], qb = s_nb[2 * S + li];
+        const double dx = r.x - r0.x, dy = r.y - r0.y;
+        double dq[4] = {qa.x - qv[0], qa.y - qv[1], qb.x - qv[2], qb.y - qv[3]};
         if (LIMIT) {
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                dmax[v] = fmax(dmax[v], dq[v]);
-                dmin[v] = fmin(dmin[v], dq[v]);
+                dmax[v] = max_f64(dmax[v], dq[v]);
+                dmin[v] = min_f64(dmin[v], dq[v]);
             }
         }
         if (INNER) {
-            const D4 gxi = {s_g[li], s_g[hmax + li], s_g[2 * hmax + li], s_g[3 * hmax + li]};
-            const D4 gyi = {s_g[4 * hmax + li], s_g[5 * hmax + li], s_g[6 * hmax + li],
-                            s_g[7 * hmax + li]};
-            dq[0] -= 0.5 * (dx * (gxi.x - gx0.x) + dy * (gyi.x - gy0.x));
-            dq[1] -= 0.5 * (dx * (gxi.y - gx0.y) + dy * (gyi.y - gy0.y));
-            dq[2] -= 0.5 * (dx * (gxi.z - gx0.z) + dy * (gyi.z - gy0.z));
-            dq[3] -= 0.5 * (dx * (gxi.w - gx0.w) + dy * (gyi.w - gy0.w));
+            const D2 xa = s_nb[3 * S + li], xb = s_nb[4 * S + li];
+            const D2 ya = s_nb[5 * S + li], yb = s_nb[6 * S + li];
+            dq[0] -= 0.5 * (dx * (xa.x - gx0.x) + dy * (ya.x - gy0.x));
+            dq[1] -= 0.5 * (dx * (xa.y - gx0.y) + dy * (ya.y - gy0.y));
+            dq[2] -= 0.5 * (dx * (xb.x - gx0.z) + dy * (yb.x - gy0.z));
+            dq[3] -= 0.5 * (dx * (xb.y - gx0.w) + dy * (yb.y - gy0.w));
         }
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
@@ -589,59 +666,39 @@ __global__ void __launch_bounds__(kBlock, 4) k_qgrad_tiled(
     for (int k = 0; k < kLnPre; ++k)
         if (e0 + lane + 4 * k < e1) first_walk(lpre[k]);
     for (int32_t e = e0 + lane + 4 * kLnPre; e < e1; e += 4) first_walk(lnbr[e]);
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        bx[v] = lane_sum<4>(bx[v]);
-        by[v] = lane_sum<4>(by[v]);
-    }
-    double gx[4], gy[4];
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        gx[v] = L.x * bx[v] + L.y * by[v];
-        gy[v] = L.y * bx[v] + L.z * by[v];
-    }
-    if (lane == 0 && (!LIMIT || qx_out)) {  // the limited pass writes them on request only
-        qx_out[p] = {gx[0], gx[1], gx[2], gx[3]};
-        qy_out[p] = {gy[0], gy[1], gy[2], gy[3]};
+    // component `lane` from here on
+    const double sx = scatter_sum<4>(bx, bx, lane), sy = scatter_sum<4>(by, by, lane);
+    const double gx = L.x * sx + L.y * sy, gy = L.y * sx + L.z * sy;
+    auto component = [lane](D4* f, int64_t i) { return reinterpret_cast<double*>(f + i) + lane; };
+    if (!LIMIT || qx_out) {  // the limited pass writes them on request only
+        *component(qx_out, p) = gx;
+        *component(qy_out, p) = gy;
     }
     if (!LIMIT) return;
-#pragma unroll
-    for (int v = 0; v < 4; ++v)
-#pragma unroll
-        for (int o = 2; o > 0; o >>= 1) {
-            dmax[v] = fmax(dmax[v], __shfl_xor(dmax[v], o, 64));
-            dmin[v] = fmin(dmin[v], __shfl_xor(dmin[v], o, 64));
-        }
+    const double hi = scatter_extreme<true>(dmax, lane), lo = scatter_extreme<false>(dmin, lane);
     const double kh = K * L.w;
     const double eps2 = kh * kh * kh;
+    const double ax[4] = {quad_bcast<0>(gx), quad_bcast<1>(gx), quad_bcast<2>(gx), quad_bcast<3>(gx)};
+    const double ay[4] = {quad_bcast<0>(gy), quad_bcast<1>(gy), quad_bcast<2>(gy), quad_bcast<3>(gy)};
     double tlo[4] = {0, 0, 0, 0}, thi[4] = {0, 0, 0, 0};  // extremes of dx qx + dy qy
     auto second_walk = [&](int li) {
-        const double dx = s_x[li] - r0.x, dy = s_y[li] - r0.y;
+        const D2 r = s_nb[li];
+        const double dx = r.x - r0.x, dy = r.y - r0.y;
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            const double t = dx * gx[v] + dy * gy[v];
-            tlo[v] = fmin(tlo[v], t);
-            thi[v] = fmax(thi[v], t);
+            const double t = dx * ax[v] + dy * ay[v];
+            tlo[v] = min_f64(tlo[v], t);
+            thi[v] = max_f64(thi[v], t);
         }
     };
 #pragma unroll
     for (int k = 0; k < kLnPre; ++k)
         if (e0 + lane + 4 * k < e1) second_walk(lpre[k]);
     for (int32_t e = e0 + lane + 4 * kLnPre; e < e1; e += 4) second_walk(lnbr[e]);
-#pragma unroll
-    for (int v = 0; v < 4; ++v)
-#pragma unroll
-        for (int o = 2; o > 0; o >>= 1) {
-            tlo[v] = fmin(tlo[v], __shfl_xor(tlo[v], o, 64));
-            thi[v] = fmax(thi[v], __shfl_xor(thi[v], o, 64));
-        }
-    if (lane == 0) {
-        double phi[4];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) phi[v] = venkat_phi(tlo[v], thi[v], dmax[v], dmin[v], eps2);
-        qxl[p] = {phi[0] * gx[0], phi[1] * gx[1], phi[2] * gx[2], phi[3] * gx[3]};
-        qyl[p] = {phi[0] * gy[0], phi[1] * gy[1], phi[2] * gy[2], phi[3] * gy[3]};
-    }
+    const double phi = venkat_phi(scatter_extreme<false>(tlo, lane),
+                                  scatter_extreme<true>(thi, lane), hi, lo, eps2);
+    *component(qxl, p) = phi * gx;
+    *component(qyl, p) = phi * gy;
 }
 
 // Unsplit Euler flux Jacobian product A_d(U) dU along unit direction d
@@ -778,10 +835,6 @@ __device__ __forceinline__ D4 reconstruct(const D4& q, const D4& gx, const D4& g
             fma(hy, gy.z, fma(hx, gx.z, q.z)), fma(hy, gy.w, fma(hx, gx.w, q.w))};
 }
 
-// The longest tile list that the tiled residual stages: 18 KiB per block, so
-// that a CU holds seven blocks; a 16 x 4 block of points with 5 x 5 stencils
-// lists 160 points.
-constexpr int kResidualTile = 160;
 constexpr int kResidualMinTiles = 256;  // one block per CU
 
 // Everything a residual launch reads and writes.
@@ -794,6 +847,7 @@ struct ResidualArgs {
     const int8_t* type;
     const int32_t* off;
     const int32_t* idx;
+    const D4* lsq;
     const PointGeom* geom;
     const int32_t* comp;
     const int32_t* active;
@@ -955,7 +1009,7 @@ __device__ __forceinline__ void residual_finish(int64_t p, int8_t ty, const Resi
         double Gf[4], G0[4];
         split_flux<2>(wf, -t.y, t.x, -1.0, inv_gm1, Gf);
         split_flux<2>(w0, -t.y, t.x, -1.0, inv_gm1, G0);
-        const double ih = 1.0 / gload(&A.geom[p].lsq, 0).w;
+        const double ih = 1.0 / gload(A.lsq, p).w;
 #pragma unroll
         for (int v = 0; v < 4; ++v) Rp[v] += (Gf[v] - G0[v]) * ih;
     }
@@ -971,9 +1025,8 @@ __device__ __forceinline__ void residual_finish(int64_t p, int8_t ty, const Resi
     const double beta = 0.5 * rho / pr;
     const D4 j0 = {rho, u1, u2, pr};
     const double a = sqrt(A.gamma * pr / rho);
-    const PointGeom& Gp = A.geom[p];
-    const double hn = gload(&Gp.lsq, 0).w;  // nearest-neighbour distance
-    const D4 ls1 = gload(&Gp.ls1, 0);
+    const double hn = gload(A.lsq, p).w;  // nearest-neighbour distance
+    const D4 ls1 = gload(&A.geom[p].ls1, 0);
     const double dt = gload(A.cfl, A.comp ? gload(A.comp, p) : 0) * hn / (sqrt(usq) + a);
     double Dp = 1.0 / dt;
     if (A.variant == 0) {
@@ -1541,52 +1594,6 @@ __device__ __forceinline__ void sweep_entry(uint8_t cd, const D2& t, const W2<T>
     }
 }
 
-// Cross-lane moves by data-parallel primitives (vector instructions; shuffles
-// go through LDS): xor 1 and 2 within a quad, the mirror of 8 lanes, which
-// takes a quad's lanes to the other quad's, and lane l of 16 to l + 8.
-constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppMirror8 = 0x141, kDppRotate8 = 0x128;
-constexpr int kDppQuad1 = 0x55, kDppQuad2 = 0xAA;  // broadcast of a quad's lane 1, 2
-
-template <int CTRL>
-__device__ __forceinline__ float dpp(float v) {
-    return __int_as_float(
-        __builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
-}
-template <int CTRL>
-__device__ __forceinline__ double dpp(double v) {
-    return __hiloint2double(
-        __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true),
-        __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true));
-}
-
-// Sums of four values over a point's LANES (4, 8, 16) lanes, scattered: lane l
-// gets the sum of value l % 4.  Sixteen lanes come as (first, rest), a lane's
-// first entry and the sum of its others, and add up in the order of eight
-// lanes: entry l, then l + 8, l + 16, l + 24.  Lists of up to 32 entries thus
-// give the same bits with either.
-template <int LANES, class T>
-__device__ __forceinline__ T scatter_sum(T a[4], const T rest[4], int lane) {
-    if constexpr (LANES == 16) {
-        const bool low = lane < 8;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const T other = dpp<kDppRotate8>(rest[v]);
-            const T f = dpp<kDppRotate8>(a[v]);
-            a[v] += f;
-            a[v] += low ? rest[v] : other;
-            a[v] += low ? other : rest[v];
-        }
-    }
-#pragma unroll
-    for (int v = 0; v < 4; ++v)
-        if (LANES >= 8) a[v] += dpp<kDppMirror8>(a[v]);
-    const bool hi = lane & 2, odd = lane & 1;
-    T x0 = hi ? a[2] : a[0], x1 = hi ? a[3] : a[1];
-    x0 += dpp<kDppXor2>(hi ? a[0] : a[2]);
-    x1 += dpp<kDppXor2>(hi ? a[1] : a[3]);
-    return (odd ? x1 : x0) + dpp<kDppXor1>(odd ? x0 : x1);
-}
-
 // One colour phase of a sweep (eq. 27).  FWD: dU*_0 = -(R_0 + sum_lower w A dU*) / D_0;
 // backward: dU_0 = dU*_0 - (sum_upper w A dU) / D_0.  MODE 0 exact tangent,
 // 1 flux difference.  T is the arithmetic of the products and increments.
@@ -1757,7 +1764,7 @@ __global__ void __launch_bounds__(kBlock) k_update(int64_t n, double gamma, D4* 
 // unless the kinetic far field gives them a residual.
 __global__ void __launch_bounds__(kBlock) k_explicit_update(
     int64_t n, double gamma, const double* __restrict__ cfl, const int8_t* __restrict__ type,
-    const PointGeom* __restrict__ geom, const int32_t* __restrict__ comp,
+    const D4* __restrict__ lsq, const int32_t* __restrict__ comp,
     const int32_t* __restrict__ active, const D4* __restrict__ R, D4* __restrict__ U,
     D4* __restrict__ q, int32_t* __restrict__ flags, int farfield) {
     const int64_t p = (int64_t)xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
@@ -1768,7 +1775,7 @@ __global__ void __launch_bounds__(kBlock) k_explicit_update(
     const double usq = u1 * u1 + u2 * u2;
     const double pr = (gamma - 1.0) * (u.w - 0.5 * rho * usq);
     const double a = sqrt(gamma * pr / rho);
-    const double dt = cfl[comp ? comp[p] : 0] * geom[p].lsq.w / (sqrt(usq) + a);
+    const double dt = cfl[comp ? comp[p] : 0] * lsq[p].w / (sqrt(usq) + a);
     const D4 r = R[p];
     u.x -= dt * r.x;
     u.y -= dt * r.y;
@@ -1863,7 +1870,7 @@ hipError_t launch_precompute(Cloud& c, hipStream_t st) {
     e = hipMemsetAsync(d_cnt, 0, 2 * sizeof(unsigned long long), st);
     if (e == hipSuccess && c.n > 0) {
         hipLaunchKernelGGL(k_precompute, dim3(grid_for(c.n)), dim3(kBlock), 0, st, c.n, c.xy,
-                           c.frame, c.type, c.off, c.idx, c.geom, d_cnt);
+                           c.frame, c.type, c.off, c.idx, c.geom, c.lsq, d_cnt);
         e = hipGetLastError();
     }
     if (e == hipSuccess) e = hipMemcpyAsync(h, d_cnt, sizeof(h), hipMemcpyDeviceToHost, st);
@@ -1911,59 +1918,58 @@ static void qgrad_lanes(State& s, bool keep) {
     // pass 0 (first order), then m inner passes; the limiter rides on the last
     if (m == 0 && lim)
         hipLaunchKernelGGL((k_qgrad<false, true, LANES>), g, b, 0, s.stream, c.n, K, c.xy, c.off,
-                           c.idx, c.geom, c.comp, s.active, s.q, nullptr, nullptr,
+                           c.idx, c.lsq, c.comp, s.active, s.q, nullptr, nullptr,
                            keep ? s.qx[0] : nullptr, keep ? s.qy[0] : nullptr, s.qxl, s.qyl);
     else
         hipLaunchKernelGGL((k_qgrad<false, false, LANES>), g, b, 0, s.stream, c.n, K, c.xy, c.off,
-                           c.idx, c.geom, c.comp, s.active, s.q, nullptr, nullptr, s.qx[0],
+                           c.idx, c.lsq, c.comp, s.active, s.q, nullptr, nullptr, s.qx[0],
                            s.qy[0], nullptr, nullptr);
     int cur = 0;
     for (int it = 0; it < m; ++it) {
         if (it == m - 1 && lim)
             hipLaunchKernelGGL((k_qgrad<true, true, LANES>), g, b, 0, s.stream, c.n, K, c.xy,
-                               c.off, c.idx, c.geom, c.comp, s.active, s.q, s.qx[cur], s.qy[cur],
+                               c.off, c.idx, c.lsq, c.comp, s.active, s.q, s.qx[cur], s.qy[cur],
                                keep ? s.qx[1 - cur] : nullptr, keep ? s.qy[1 - cur] : nullptr,
                                s.qxl, s.qyl);
         else
             hipLaunchKernelGGL((k_qgrad<true, false, LANES>), g, b, 0, s.stream, c.n, K, c.xy,
-                               c.off, c.idx, c.geom, c.comp, s.active, s.q, s.qx[cur], s.qy[cur],
+                               c.off, c.idx, c.lsq, c.comp, s.active, s.q, s.qx[cur], s.qy[cur],
                                s.qx[1 - cur], s.qy[1 - cur], nullptr, nullptr);
         cur = 1 - cur;
     }
     s.qsel = cur;
 }
 
-// Tiled passes (LDS-staged neighbours): block = tile, dynamic LDS sized by
-// the cloud's largest tile neighbour list.
+// Tiled passes (LDS-staged neighbours): block = tile, staged arrays of stride
+// S.
+template <int S>
 static void qgrad_tiled(State& s, bool keep) {
     const Cloud& c = *s.cloud;
     const dim3 g((unsigned)c.ntile), b(kBlock);
     const double K = s.prm.limiter_k;
     const int m = s.prm.inner_iters;
     const bool lim = s.prm.limiter != 0;
-    const size_t lds0 = (size_t)c.tile_hmax * 6 * sizeof(double);
-    const size_t lds1 = (size_t)c.tile_hmax * 14 * sizeof(double);
     if (m == 0 && lim)
-        hipLaunchKernelGGL((k_qgrad_tiled<false, true>), g, b, lds0, s.stream, K, c.xy, c.off,
-                           c.tile_pts, c.lnbr, c.tile_off, c.tile_idx, c.tile_hmax, c.geom,
+        hipLaunchKernelGGL((k_qgrad_tiled<false, true, S>), g, b, 0, s.stream, K, c.xy, c.off,
+                           c.tile_pts, c.lnbr, c.tile_off, c.tile_idx, c.lsq,
                            c.comp, s.active, s.q, nullptr, nullptr, keep ? s.qx[0] : nullptr,
                            keep ? s.qy[0] : nullptr, s.qxl, s.qyl);
     else
-        hipLaunchKernelGGL((k_qgrad_tiled<false, false>), g, b, lds0, s.stream, K, c.xy, c.off,
-                           c.tile_pts, c.lnbr, c.tile_off, c.tile_idx, c.tile_hmax, c.geom,
+        hipLaunchKernelGGL((k_qgrad_tiled<false, false, S>), g, b, 0, s.stream, K, c.xy, c.off,
+                           c.tile_pts, c.lnbr, c.tile_off, c.tile_idx, c.lsq,
                            c.comp, s.active, s.q, nullptr, nullptr, s.qx[0], s.qy[0], nullptr,
                            nullptr);
     int cur = 0;
     for (int it = 0; it < m; ++it) {
         if (it == m - 1 && lim)
-            hipLaunchKernelGGL((k_qgrad_tiled<true, true>), g, b, lds1, s.stream, K, c.xy, c.off,
-                               c.tile_pts, c.lnbr, c.tile_off, c.tile_idx, c.tile_hmax, c.geom,
+            hipLaunchKernelGGL((k_qgrad_tiled<true, true, S>), g, b, 0, s.stream, K, c.xy, c.off,
+                               c.tile_pts, c.lnbr, c.tile_off, c.tile_idx, c.lsq,
                                c.comp, s.active, s.q, s.qx[cur], s.qy[cur],
                                keep ? s.qx[1 - cur] : nullptr, keep ? s.qy[1 - cur] : nullptr,
                                s.qxl, s.qyl);
         else
-            hipLaunchKernelGGL((k_qgrad_tiled<true, false>), g, b, lds1, s.stream, K, c.xy, c.off,
-                               c.tile_pts, c.lnbr, c.tile_off, c.tile_idx, c.tile_hmax, c.geom,
+            hipLaunchKernelGGL((k_qgrad_tiled<true, false, S>), g, b, 0, s.stream, K, c.xy, c.off,
+                               c.tile_pts, c.lnbr, c.tile_off, c.tile_idx, c.lsq,
                                c.comp, s.active, s.q, s.qx[cur], s.qy[cur], s.qx[1 - cur],
                                s.qy[1 - cur], nullptr, nullptr);
         cur = 1 - cur;
@@ -1973,7 +1979,8 @@ static void qgrad_tiled(State& s, bool keep) {
 
 hipError_t launch_q_derivatives(State& s, bool keep_unlimited) {
     if (s.qgrad_tiled && s.cloud->ntile > 0) {
-        qgrad_tiled(s, keep_unlimited);
+        if (s.cloud->tile_hmax <= kTileStride) qgrad_tiled<kTileStride>(s, keep_unlimited);
+        else qgrad_tiled<kQTileMax>(s, keep_unlimited);
         return hipGetLastError();
     }
     switch (s.qgrad_lanes) {
@@ -1995,7 +2002,7 @@ static void residual_lanes(State& s, bool in_step) {
     const Cloud& c = *s.cloud;
     const ResidualArgs A{c.n,        s.prm.gamma, s.cfl,      c.xy,
                          c.frame,    c.type,      c.off,      c.idx,
-                         c.geom,     c.comp,      s.active,   c.tile_pts,
+                         c.lsq,      c.geom,      c.comp,     s.active,   c.tile_pts,
                          c.lnbr,     c.tile_off,  c.tile_idx, s.U,
                          s.q,        s.prm.limiter ? s.qxl : s.qx[s.qsel],
                          s.prm.limiter ? s.qyl : s.qy[s.qsel], s.R,
@@ -2008,8 +2015,8 @@ static void residual_lanes(State& s, bool in_step) {
     // long as one block, and the staging and its barriers lengthen that (FP64,
     // 6,400 points: 18.5 us gathered, 23.5 us tiled; 40,250 points: 28.5 and
     // 26.8; 2,621,440 points: 712 and 665).  Both forms give the same bits.
-    if (s.qgrad_tiled && c.ntile >= kResidualMinTiles && c.tile_hmax <= kResidualTile)
-        hipLaunchKernelGGL((k_residual_tiled<MIXED, LANES, kResidualTile>), dim3((unsigned)c.ntile),
+    if (s.qgrad_tiled && c.ntile >= kResidualMinTiles && c.tile_hmax <= kTileStride)
+        hipLaunchKernelGGL((k_residual_tiled<MIXED, LANES, kTileStride>), dim3((unsigned)c.ntile),
                            dim3(kQTile * LANES), 0, s.stream, A);
     else
         hipLaunchKernelGGL((k_residual<MIXED, LANES>), dim3(grid_for(c.n * LANES)), dim3(kBlock), 0,
@@ -2152,7 +2159,7 @@ hipError_t launch_sweeps(State& s) {
 hipError_t launch_explicit_update(State& s) {
     const Cloud& c = *s.cloud;
     hipLaunchKernelGGL(k_explicit_update, dim3(grid_for(c.n)), dim3(kBlock), 0, s.stream, c.n,
-                       s.prm.gamma, s.cfl, c.type, c.geom, c.comp, s.active, s.R, s.U, s.q,
+                       s.prm.gamma, s.cfl, c.type, c.lsq, c.comp, s.active, s.R, s.U, s.q,
                        s.flags, s.prm.farfield);
     return hipGetLastError();
 }

@@ -32,15 +32,15 @@ struct alignas(8) F2 {
 template <class T>
 using W2 = std::conditional_t<std::is_same_v<T, float>, F2, D2>;
 
-// Geometry precomputed once per cloud (one record per point).
-//   lsq:   inverse of the full-stencil LS normal matrix, (a11, a12, a22, rmin)
+// Geometry precomputed once per cloud, per point.
+//   lsq (an array of its own, which the q-derivative passes read densely):
+//          inverse of the full-stencil LS normal matrix, (a11, a12, a22, rmin)
 //          so that q_x = a11 bx + a12 by, q_y = a12 bx + a22 by, and rmin the
 //          distance to the nearest neighbour (time-step rule).
 //   split: for split k (interior x+, x-, y+, y-; wall t+, t-, n-), the
 //          weight coefficients (cb, cab): w_i = cb * da_i + cab * db_i.
 //   ls1:   LS_k(1), the weight sums of the four splits.
 struct alignas(32) PointGeom {
-    D4 lsq;
     D2 split[4];
     D4 ls1;
 };
@@ -117,6 +117,7 @@ struct Cloud {
     std::vector<double> h_x, h_y, h_tx, h_ty;
     std::vector<int8_t> h_type;
     std::vector<int32_t> h_off, h_idx;
+    D4* lsq = nullptr;
     PointGeom* geom = nullptr;
     // LDS tiles of the q-derivative passes (lskum_tiles.h): tile b holds the
     // points tile_pts[b kQTile ...] (-1 past its end), either kQTile

@@ -95,15 +95,41 @@ def test_sweeps_with_long_lists(lk, lanes):
     the suite's bar of 1e-11."""
     cloud = _ring(cg.box(15, 14, wall_bottom=True), 4)
     kw = dict(cfl=5.0, inner_iters=0)
-    o = O.Oracle(cloud, mach=0.4, aoa_deg=0.0, **kw)
+    o = O.Oracle(cloud, mach=0.4, aoa_deg=5.0, **kw)
     rng = np.random.default_rng(5)
     U = o.free_stream() * (1.0 + 0.01 * rng.uniform(-1, 1, (4, cloud.n)))
     U[2, cloud.type == 0] = 0.0
     _, _, dUo, _ = o.iteration(U)
-    st = lk.State(lk.Cloud(cloud), 0.4, 0.0, lk.default_params(sweep_lanes=lanes, **kw))
+    st = lk.State(lk.Cloud(cloud), 0.4, 5.0, lk.default_params(sweep_lanes=lanes, **kw))
     st.set_U(U)
     st.step()
     dU = st.get_dU()
     e = max(np.abs(dU[v] - dUo[v]).max() / np.abs(dUo[v]).max() for v in range(4))
     print(f"long lists, {lanes} lanes: {e:.2e}")
-    assert e < 1e-11
+    assert np.isfinite(e) and e < 1e-11
+
+
+@pytest.mark.parametrize("r,inner", [(1, 0), (2, 1), (3, 2), (4, 1), (4, 0)])
+def test_q_derivatives_by_list_length(lk, r, inner):
+    """Stencils of 8 to 80 neighbours on a 40 x 20 box: tile lists below and
+    above the staged arrays' usual stride (160), entries beyond the 32 whose
+    positions a point's lanes hold; q-derivatives and the limited residual
+    against the oracle, the suite's bar of 1e-11."""
+    cloud = _ring(cg.box(40, 20, wall_bottom=True), r)
+    kw = dict(cfl=5.0, inner_iters=inner, limiter=1, limiter_k=5.0)
+    o = O.Oracle(cloud, mach=0.4, aoa_deg=5.0, **kw)
+    rng = np.random.default_rng(6)
+    x, y = cloud.x, cloud.y
+    bump = np.stack([np.sin(2 * x + y), np.cos(x - 2 * y), np.sin(x * y), np.cos(3 * x)])
+    U = o.free_stream() * (1.0 + 0.05 * bump + 0.001 * rng.uniform(-1, 1, (4, cloud.n)))
+    U[2, cloud.type == 0] = 0.0
+    st = lk.State(lk.Cloud(cloud), 0.4, 5.0, lk.default_params(**kw))
+    st.set_U(U)
+    R, _ = st.residual()
+    qx, qy = st.q_derivatives()
+    ox, oy = o.q_derivatives(O.q_from_U(U))
+    Ro, _ = o.residual(U)
+    errs = [max(np.abs(a[v] - b[v]).max() / np.abs(b[v]).max() for v in range(4))
+            for a, b in ((qx, ox), (qy, oy), (R, Ro))]
+    print(f"radius {r}, {inner} inner: {errs}")
+    assert np.isfinite(errs).all() and max(errs) < 1e-11
