@@ -59,7 +59,7 @@ hipError_t upload(T* dst, const T* src, size_t count) {
 
 void free_cloud(lskum::Cloud& c) {
     void* ptrs[] = {c.xy,     c.frame,     c.type,   c.off,      c.idx,      c.colour,
-                    c.col_perm, c.wall_list, c.geom, c.lsq, c.lo_off,   c.lo_idx,   c.up_off,
+                    c.col_perm, c.wall_list, c.wall_box, c.wall_xy, c.wall_run_off, c.geom, c.lsq, c.lo_off,   c.lo_idx,   c.up_off,
                     c.up_idx, c.lo_w,      c.up_w,     c.lo_code,  c.up_code,  c.comp, c.qcomp,
                     c.lo_wf, c.up_wf,
                     c.comp_off, c.wall_off, c.comp_inv_active,
@@ -205,6 +205,24 @@ int upload_cloud(lskum::Cloud& c) {
         comp_off32[k] = (int32_t)c.h_comp_off[k];
         wall_off32[k] = (int32_t)c.h_wall_off[k];
     }
+    // runs of wall points and their bounding boxes (nearest-wall search)
+    std::vector<lskum::D4> wall_box;
+    std::vector<lskum::D2> wall_xy;
+    std::vector<int32_t> wall_run_off(1, 0);
+    for (int32_t k = 0; k < c.ncomp; ++k) {
+        for (int64_t w = c.h_wall_off[k]; w < c.h_wall_off[k + 1]; w += lskum::kWallRun) {
+            const int64_t end = std::min(w + lskum::kWallRun, c.h_wall_off[k + 1]);
+            lskum::D4 b{HUGE_VAL, -HUGE_VAL, HUGE_VAL, -HUGE_VAL};
+            for (int64_t j = w; j < w + lskum::kWallRun; ++j) {
+                const int32_t p = wall[std::min(j, end - 1)];  // the last point fills the run
+                const double x = c.h_x[p], y = c.h_y[p];
+                wall_xy.push_back({x, y});
+                b = {std::min(b.x, x), std::max(b.y, x), std::min(b.z, y), std::max(b.w, y)};
+            }
+            wall_box.push_back(b);
+        }
+        wall_run_off.push_back((int32_t)wall_box.size());
+    }
     c.n_wall = (int64_t)wall.size();
     c.wall_orient = c.h_comp_orient[0];
     c.n_active = 0;
@@ -247,6 +265,9 @@ int upload_cloud(lskum::Cloud& c) {
     chk(dalloc(&c.colour, n));
     chk(dalloc(&c.col_perm, n));
     chk(dalloc(&c.wall_list, wall.size()));
+    chk(dalloc(&c.wall_box, wall_box.size()));
+    chk(dalloc(&c.wall_xy, wall_xy.size()));
+    chk(dalloc(&c.wall_run_off, wall_run_off.size()));
     chk(dalloc(&c.geom, n));
     chk(dalloc(&c.lsq, n));
     if (c.ntile) {
@@ -313,6 +334,9 @@ int upload_cloud(lskum::Cloud& c) {
         chk(upload(c.lo_idx, lo_idx.data(), lo_idx.size()));
         chk(upload(c.up_idx, up_idx.data(), up_idx.size()));
         chk(upload(c.wall_list, wall.data(), wall.size()));
+        chk(upload(c.wall_box, wall_box.data(), wall_box.size()));
+        chk(upload(c.wall_xy, wall_xy.data(), wall_xy.size()));
+        chk(upload(c.wall_run_off, wall_run_off.data(), wall_run_off.size()));
         chk(upload(c.comp_off, comp_off32.data(), c.ncomp + 1));
         chk(upload(c.wall_off, wall_off32.data(), c.ncomp + 1));
         chk(upload(c.comp_inv_active, c.h_comp_inv_active.data(), c.ncomp));

@@ -45,6 +45,8 @@ struct alignas(32) PointGeom {
     D4 ls1;
 };
 
+constexpr int kWallRun = 32;
+
 constexpr uint8_t kSwA = 1, kSwNegA = 2, kSwB = 4, kSwNegB = 8, kSwWall = 16;
 
 // q-derivative tiles: points per tile (one per four lanes of a 256-thread
@@ -75,6 +77,13 @@ struct Cloud {
     int32_t* colour = nullptr;
     int32_t* col_perm = nullptr;   // points sorted by colour, then index
     int32_t* wall_list = nullptr;  // wall points in storage order
+    // Runs of kWallRun consecutive wall points of one component: the run's
+    // bounding box (xmin, xmax, ymin, ymax) and its kWallRun coordinates (a
+    // short run repeats its last point); component k owns the runs
+    // [wall_run_off[k], ...+1).
+    D4* wall_box = nullptr;
+    D2* wall_xy = nullptr;
+    int32_t* wall_run_off = nullptr;
     // Sweep lists: the neighbours of each point split by colour -- lower
     // colours (read by the forward sweep) and higher colours (backward) --
     // with CSR order kept, laid out in colour-sorted point order (list of the

@@ -133,3 +133,27 @@ def test_q_derivatives_by_list_length(lk, r, inner):
             for a, b in ((qx, ox), (qy, oy), (R, Ro))]
     print(f"radius {r}, {inner} inner: {errs}")
     assert np.isfinite(errs).all() and max(errs) < 1e-11
+
+
+def test_features_nearest_wall(lk):
+    """The nearest-wall search by runs of wall points: a wall of many runs with
+    a short last one (330 points), clouds without a wall, and a batch of
+    25-point clouds whose conditions share wavefronts, against the brute force
+    of the oracle (float32 features: 1e-6)."""
+    from oracle import mlp as OM
+    c = cg.ogrid(330, 24, jitter_p=0.05, seed=2)
+    st = lk.State(lk.Cloud(c), 0.7, 1.0, lk.default_params())
+    X = st.features().cpu().numpy()
+    assert np.abs(X - OM.features(c.x, c.y, c.type, 0.7, 1.0)).max() <= 1e-6
+    st.close()
+    clouds = [cg.box(5, 5, wall_bottom=True), cg.box(5, 5), c]
+    which = [0, 1, 0, 1, 0, 2, 1]
+    mach = [0.3 + 0.05 * k for k in range(7)]
+    b = lk.Batch([lk.Cloud(x) for x in clouds], which, mach, [0.0] * 7, lk.default_params())
+    X = b.features().cpu().numpy()
+    o = 0
+    for k, w in enumerate(which):
+        ref = OM.features(clouds[w].x, clouds[w].y, clouds[w].type, mach[k], 0.0)
+        assert np.abs(X[o:o + clouds[w].n] - ref).max() <= 1e-6, k
+        o += clouds[w].n
+    b.close()
