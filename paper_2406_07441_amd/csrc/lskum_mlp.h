@@ -21,34 +21,33 @@ constexpr int kOffW4 = kOffB3 + kWidth;
 constexpr int kOffB4 = kOffW4 + kOut * kWidth;
 constexpr int kParams = kOffB4 + kOut;
 static_assert(kParams == 34308, "parameter count");
-constexpr int kChunk = 256;   // rows per partial sum of the gradients (multiple of 32)
-constexpr int kRowAlign = 32; // workspace rows are padded to a multiple of this
-constexpr int kMaxSumJobs = 8; // sums over rows in one backward pass
-constexpr int kMaxColJobs = 6; // of which column sums computed without matrix cores
+constexpr int kMaxParts = 256;  // blocks (and partial gradients) of a training pass
+constexpr int kW1Rows = kWidth * 8;  // W1 as [unit][8]: five weights, the bias, two unused
+constexpr int kW4Frag = 4 * 64 * 8;  // bf16 of W4 (four outputs padded to 16)
+
+// Rounded copies of the weights: W1 as fp32 rows with the bias, the others as
+// matrix-core operand fragments, W2f, W3f as the forward pass multiplies by them,
+// W2t, W3t transposed for the backward pass.  The padding of W4f is zero.
+struct WeightCopies {
+    float* W1f;
+    __bf16 *W2f, *W3f, *W4f, *W2t, *W3t;
+};
 
 struct Net {
     int device = 0;
     hipStream_t stream = nullptr;
     bool own_stream = false;
-    int64_t capacity = 0;  // workspace rows (multiple of kRowAlign)
+    int64_t capacity = 0;  // workspace rows
     int64_t step = 0;      // Adam steps taken
     float* theta = nullptr;  // fp32 master weights
-    float* grad = nullptr;
     float* m = nullptr;
     float* v = nullptr;
-    __bf16 *W1b = nullptr, *W2b = nullptr, *W3b = nullptr, *W4b = nullptr;
+    WeightCopies copies{};
     // workspace, capacity rows
-    float* Xin = nullptr;   // [cap][5] staged features
-    float* Tin = nullptr;   // [cap][4] staged targets
+    float* Xin = nullptr;   // [cap][5] staged features (warm start)
     float* Yout = nullptr;  // [cap][4] predictions
-    __bf16* Xb = nullptr;
-    float *Z1 = nullptr, *Z2 = nullptr, *Z3 = nullptr;
-    __bf16 *H1 = nullptr, *H2 = nullptr, *H3 = nullptr;
-    float* dY = nullptr;
-    float* se = nullptr;
-    __bf16 *dZ3 = nullptr, *dZ2 = nullptr;
-    float* dZ1 = nullptr;
-    float* part = nullptr;  // gradient partials of one backward pass, part_floats(capacity)
+    float* part = nullptr;  // gradient partials of a training pass, part_count(cap) x kParams
+    double* loss_part = nullptr;  // kMaxParts
     double* d_loss = nullptr;
     int32_t* d_bad = nullptr;      // per component: 1 if the prediction is unusable
     double* d_res_fs = nullptr;    // per component free-stream residual (residual check)
@@ -56,19 +55,22 @@ struct Net {
     hipEvent_t ev[2] = {};
 };
 
-// Forward over workspace rows [0, M) (M a multiple of kRowAlign, Mvalid <= M);
-// X [Mvalid][5]; with T ([Mvalid][4]) also the loss terms for backward;
-// with Y ([Mvalid][4]) the predictions.
-hipError_t forward(Net& net, const float* X, int M, int Mvalid, const float* T, float* Y);
-hipError_t backward(Net& net, int M);
-// Floats of gradient partials a workspace of cap rows needs (Net::part).
-int64_t part_floats(int64_t cap);
-hipError_t loss(Net& net, int M, double* d_out);
-hipError_t adam_step(Net& net, float lr);
+// Once per process and device, before the first launch: the training kernel
+// uses more LDS than a launch may by default.
+hipError_t prepare_kernels();
+// Predictions Y [m][4] of features X [m][5].
+hipError_t forward(Net& net, const float* X, int m, float* Y);
+// Partial gradients of a training pass over so many rows.
+int part_count(int64_t rows);
+// Loss (sum of squared errors, device) and gradient (device, may be NULL) of m
+// rows; with lr also one Adam step.
+hipError_t gradient(Net& net, const float* X, const float* T, int m, float* grad, double* loss,
+                    const float* lr);
+// One Adam step on B rows drawn from a data set of n: row r is
+// floor(h(seed, step, r) * n / 2^64).
+hipError_t minibatch_step(Net& net, int64_t n, const float* X, const float* T, int B, uint64_t seed,
+                          int64_t step, double* loss, float lr);
 hipError_t refresh_weights(Net& net);
-// Rows r of a minibatch: row idx(r) = floor(h(seed, step, r) * n / 2^64) of X, T.
-hipError_t gather(Net& net, int64_t n, const float* X, const float* T, int B, uint64_t seed,
-                  int64_t step);
 // Features of points [p0, p0 + m) of a state (into Xin) and, optionally,
 // targets from its U (into Tout, [m][4]).
 hipError_t features(const State& s, int64_t p0, int64_t m, float* Xout, float* Tout);

@@ -2,18 +2,25 @@
 // form) on the hidden layers, bfloat16 weights/activations with fp32
 // accumulation, Adam on fp32 master weights.
 //
-// The two 128 x 128 layers and their backward products are dense
-// contractions and run on the matrix cores (v_mfma_f32_16x16x32_bf16): one
-// wavefront computes one 16 x 16 output tile, K is walked 32 at a time.
-// Operand registers: lane l holds row (A) or column (B) l % 16 and the eight
-// consecutive K entries 8 (l / 16) .. 8 (l / 16) + 7; the accumulator lane l
-// holds column l % 16 of rows 4 (l / 16) .. 4 (l / 16) + 3.  The thin 5 -> 128
-// and 128 -> 4 layers run on the vector ALUs.
+// Every product of bf16 operands runs on the matrix cores
+// (v_mfma_f32_16x16x32_bf16): one wavefront computes one 16 x 16 output tile,
+// K is walked 32 at a time.  Operand registers: lane l holds row (A) or column
+// (B) l % 16 and the eight K entries of group g = l / 16; the accumulator lane
+// l holds column l % 16 of rows 4 g .. 4 g + 3.
+//
+// Layers are evaluated transposed, Z^T = W H^T: units along the matrix rows,
+// data rows along its columns.  A lane then holds units 16 c + 4 g + 0..3 of
+// data row l % 16 for every 16-unit tile c, and the next layer's B operand (units
+// 32 s + 8 g + 0..7 of the same row) is one exchange between the four lanes of a
+// row.  Weights are kept operand by operand (64 lanes x 16 bytes, "fragments").
 //
 // Quantisation points (shared with the float64 reference of the tests):
 // bf16 copies of W1..W4, of the input features and of each hidden activation;
 // the backward pass rounds the pre-activation gradients of layers 3 and 2 to
-// bf16 before their products; everything else is fp32.
+// bf16 before their products; everything else is fp32.  What is rounded is
+// computed in one order everywhere (K ascending from zero, then the bias; layer
+// 1 and the gradient of layer 4 term by term), because one activation rounded
+// the other way moves a row's outputs by up to a percent.
 #include "lskum_mlp.h"
 
 #include <cmath>
@@ -26,6 +33,8 @@ namespace {
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 
+inline unsigned nblk(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
+
 constexpr float kInvSqrt2 = 0.70710678118654752f;
 constexpr float kInvSqrt2Pi = 0.39894228040143268f;
 
@@ -34,367 +43,197 @@ __device__ __forceinline__ float gelu_prime(float z) {
     return 0.5f * (1.0f + erff(z * kInvSqrt2)) + z * expf(-0.5f * z * z) * kInvSqrt2Pi;
 }
 
-// One 16 x 16 tile of C = A B over K range [k0, k1) (k1 - k0 a multiple of 32).
-// a(r, k) = A[r * a_rs + k * a_ks], b(k, c) = B[k * b_ks + c * b_cs].
-__device__ __forceinline__ f32x4 tile_mma(const __bf16* __restrict__ A, int64_t a_rs,
-                                          int64_t a_ks, const __bf16* __restrict__ B,
-                                          int64_t b_ks, int64_t b_cs, int r0, int c0, int k0,
-                                          int k1) {
-    const int l = threadIdx.x & 63;
-    const int rr = r0 + (l & 15), cc = c0 + (l & 15), kq = 8 * (l >> 4);
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    for (int k = k0; k < k1; k += 32) {
-        bf16x8 a, b;
-#pragma unroll
-        for (int t = 0; t < 8; ++t) {
-            a[t] = A[rr * a_rs + (int64_t)(k + kq + t) * a_ks];
-            b[t] = B[(int64_t)(k + kq + t) * b_ks + cc * b_cs];
-        }
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc, 0, 0, 0);
-    }
-    return acc;
+typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
+
+// Phi(-a) for a >= 0 (the normal CDF's lower half) as 2^P(a), P a degree-10
+// fit of log2 Phi(-a) on [0, 6], minimax in the error of a Phi(-a) where a
+// exceeds 1.5 and in the relative error below; beyond 6, P falls on and 2^P is
+// below 1e-9.  (Degree 9 turns upwards there.)
+__device__ __forceinline__ float phi_lower(float a) {
+    float p = -2.508991770e-08f;
+    p = fmaf(p, a, 7.670555533e-07f);
+    p = fmaf(p, a, -1.002338104e-05f);
+    p = fmaf(p, a, 7.115060725e-05f);
+    p = fmaf(p, a, -2.618829894e-04f);
+    p = fmaf(p, a, -3.622323129e-05f);
+    p = fmaf(p, a, 6.990640890e-03f);
+    p = fmaf(p, a, -5.247051269e-02f);
+    p = fmaf(p, a, -4.592113495e-01f);
+    p = fmaf(p, a, -1.151105285e+00f);
+    p = fmaf(p, a, -1.0f);
+    return __builtin_amdgcn_exp2f(p);
 }
 
-// Whole forward pass of 128 rows per workgroup (8 waves x 16 rows).  W2, then
-// W3, is staged in one LDS buffer with rows padded to kLdsW bf16 (a 16-byte operand read
-// by 16 lanes of different rows then hits distinct banks).  Layer 1 is
-// evaluated directly in the matrix-core operand layout (each lane computes the
-// 32 hidden units its A fragments hold); the 128 x 128 layers run on the
-// matrix cores, their outputs going back through a per-wave LDS tile to the
-// operand layout of the next layer; layer 4 sums each lane's 8 columns and
-// then across the 16 lanes of a row group with shuffles (fixed order).
-// TRAIN also writes what the backward pass reads (Xb, Z1-3, H1-3) and the
-// loss terms dY, se; otherwise Y.
-constexpr int kLdsW = kWidth + 8;
+// bf16(gelu(z)) of four values, mostly without erff but with its bits:
+// max(z, 0) - |z| Phi(-|z|) is within 1.8e-7 |z| of gelu(z) (the largest
+// difference over all floats is 1.763e-7 |z|), so where both ends of that
+// interval round to the same bf16, gelu(z) does too.  Elsewhere (one value in
+// 10,000 at z = 1, in 300 at z = -2, all below -5 or so) the lane takes gelu
+// itself, and so does the whole wave where no |z| exceeds kNear: there erff
+// is the quicker one (1,000,003 rows: 221 against 257 us; with inputs that
+// spread z beyond, 297 against 260 us).  |z| is bounded at 1e4 in the interval,
+// so that infinities have one; NaNs pass through Phi.  (Zeros may differ in sign.)
+// (Medians in place of maximum and minimum: those functions would first bring
+// their operands to a canonical form, two instructions more.)
+__device__ __forceinline__ bf16x4 gelu_bf16(const f32x4& z) {
+    constexpr float kDiff = 1.8e-7f, kNear = 1.4f;
+    bf16x4 up, down;
+    const float far = fmaxf(fmaxf(fabsf(z[0]), fabsf(z[1])), fmaxf(fabsf(z[2]), fabsf(z[3])));
+    bool exact = true;
+    if (__any(far > kNear)) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const float relu = __builtin_amdgcn_fmed3f(z[k], 0.0f, __builtin_inff());
+            const float a = __builtin_amdgcn_fmed3f(fabsf(z[k]), 0.0f, 1e4f);
+            const float v = fmaf(-a, phi_lower(fabsf(z[k])), relu);
+            up[k] = (__bf16)fmaf(kDiff, a, v);
+            down[k] = (__bf16)fmaf(-kDiff, a, v);
+        }
+        exact = __builtin_bit_cast(uint64_t, up) != __builtin_bit_cast(uint64_t, down);
+    }
+    if (exact)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) up[k] = (__bf16)gelu(z[k]);
+    return up;
+}
+
+// Place of W[row][k] (a 128 x 128 matrix used as A operand, contraction over
+// k) in its fragments: tile row / 16, K block k / 32, lane, place.
+__device__ __forceinline__ int fragment(int row, int k) {
+    return ((row / 16 * 4 + k / 32) * 64 + k % 32 / 8 * 16 + row % 16) * 8 + k % 8;
+}
+
+__device__ __forceinline__ f32x4 mfma(bf16x8 a, bf16x8 b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+
+// W fragments (c, s) times the four K blocks of a B operand, onto z.
+__device__ __forceinline__ f32x4 row_tile(const __bf16* frag, int c, int l, const bf16x8 h[4],
+                                          f32x4 z) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) z = mfma(*(const bf16x8*)&frag[((c * 4 + s) * 64 + l) * 8], h[s], z);
+    return z;
+}
+
+// A row's features, rounded.
+__device__ __forceinline__ void load_row(const float* __restrict__ X, float x[kIn]) {
+#pragma unroll
+    for (int f = 0; f < kIn; ++f) x[f] = (float)(__bf16)X[f];
+}
+
+// Layer 1 for one unit, w its weights and bias.
+__device__ __forceinline__ float layer1(const float w[8], const float x[kIn]) {
+    float z = w[kIn];
+#pragma unroll
+    for (int f = 0; f < kIn; ++f) z = fmaf(x[f], w[f], z);
+    return z;
+}
+
+// The accumulator tiles c = 2 s, 2 s + 1 of a row, as bf16, to K block s of the
+// next layer's B operand: of the row's four lanes, g receives what lanes
+// 2 (g % 2) and 2 (g % 2) + 1 hold of tile 2 s + g / 2.
+__device__ __forceinline__ bf16x8 to_operand(bf16x4 even, bf16x4 odd) {
+    typedef __attribute__((__vector_size__(2 * sizeof(unsigned)))) unsigned u32x2;
+    typedef __attribute__((__vector_size__(4 * sizeof(unsigned)))) unsigned u32x4;
+    const u32x2 e = __builtin_bit_cast(u32x2, even), o = __builtin_bit_cast(u32x2, odd);
+    u32x4 h;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const auto a = __builtin_amdgcn_permlane32_swap(e[q], o[q], false, false);
+        const auto b = __builtin_amdgcn_permlane16_swap(a[0], a[1], false, false);
+        h[q] = b[0];
+        h[2 + q] = b[1];
+    }
+    return __builtin_bit_cast(bf16x8, h);
+}
+
+// Whole forward pass: W2 and W3 in LDS as fragments (a wave's 1 KiB operand
+// reads are then linear), blocks of eight waves walking over the rows 16 at a
+// time per wave; the four outputs, padded to one tile, run on the matrix cores
+// too.  Layer 1 is evaluated in the operand's own order, its weights as fp32 rows
+// in LDS (one address for 16 lanes).
+// Bound by the vector instructions of GELU (384 a row): 1,000,003 rows take 260
+// us with the call, 370 with activations passed through LDS between layers, one
+// weight buffer for both layers and layer 4 on the vector units.  Layers unrolled
+// (twice the code), other occupancy, two tiles a wave: the same to 5% more.
 constexpr int kFwdWaves = 8;
 
-template <bool TRAIN>
-__global__ void __launch_bounds__(64 * kFwdWaves) k_mlp_forward(
-    int M, int Mvalid, const float* __restrict__ X, const __bf16* __restrict__ W1,
-    const float* __restrict__ b1, const __bf16* __restrict__ W2, const float* __restrict__ b2,
-    const __bf16* __restrict__ W3, const float* __restrict__ b3, const __bf16* __restrict__ W4,
-    const float* __restrict__ b4, const float* __restrict__ T, float* __restrict__ Y,
-    __bf16* __restrict__ Xb, float* __restrict__ Z1, float* __restrict__ Z2,
-    float* __restrict__ Z3, __bf16* __restrict__ H1, __bf16* __restrict__ H2,
-    __bf16* __restrict__ H3, float* __restrict__ dY, float* __restrict__ se) {
-    // one weight buffer: W2 for layer 2, then W3 for layer 3 (70 KB of LDS
-    // per block instead of 104 KB, so that two blocks share a CU)
-    __shared__ __attribute__((aligned(16))) __bf16 sW[kWidth * kLdsW];
-    __shared__ __attribute__((aligned(16))) __bf16 sH[kFwdWaves][16 * kLdsW];
-    auto stage = [&](const __bf16* __restrict__ Wg) {  // 16-byte chunks
-        for (int ch = threadIdx.x; ch < kWidth * kWidth / 8; ch += blockDim.x) {
-            const int row = ch / (kWidth / 8), c8 = (ch % (kWidth / 8)) * 8;
-            *(bf16x8*)&sW[row * kLdsW + c8] = *(const bf16x8*)&Wg[row * kWidth + c8];
-        }
+__global__ void __launch_bounds__(64 * kFwdWaves, 4) k_mlp_forward(
+    int M, const float* __restrict__ X, const float* __restrict__ W1f,
+    const __bf16* __restrict__ W2f, const float* __restrict__ b2,
+    const __bf16* __restrict__ W3f, const float* __restrict__ b3, const __bf16* __restrict__ W4f,
+    const float* __restrict__ b4, float* __restrict__ Y) {
+    __shared__ __attribute__((aligned(16))) __bf16 sW[2][kWidth * kWidth];
+    __shared__ __attribute__((aligned(16))) __bf16 sW4[kW4Frag];
+    __shared__ __attribute__((aligned(16))) float sW1[kWidth][8], sB[2][kWidth];
+    auto stage = [](__bf16* dst, const __bf16* __restrict__ src, int n) {  // 16-byte chunks
+        for (int k = 8 * threadIdx.x; k < n; k += 8 * 64 * kFwdWaves)
+            *(bf16x8*)&dst[k] = *(const bf16x8*)&src[k];
     };
-    stage(W2);
+    stage(sW[0], W2f, kWidth * kWidth);
+    stage(sW[1], W3f, kWidth * kWidth);
+    stage(sW4, W4f, kW4Frag);
+    for (int k = threadIdx.x; k < kWidth * 8; k += 64 * kFwdWaves) (&sW1[0][0])[k] = W1f[k];
+    for (int k = threadIdx.x; k < kWidth; k += 64 * kFwdWaves) {
+        sB[0][k] = b2[k];
+        sB[1][k] = b3[k];
+    }
     __syncthreads();
-    const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-    const int row0 = (blockIdx.x * kFwdWaves + w) * 16;
-    // a wave past the last row does no work but takes part in the barriers
-    const bool act = row0 < M;
-    const int r = l & 15, g = l >> 4, kq = 8 * g;
-    const int64_t m = row0 + r;
-    __bf16* hs = sH[w];
-    // ---- layer 1 (5 -> 128) in the A-operand layout
-    float x[kIn];
+    const int w = threadIdx.x >> 6, l = threadIdx.x & 63, r = l & 15, g = l >> 4;
+    const f32x4 out0 = g == 0 ? f32x4{b4[0], b4[1], b4[2], b4[3]} : f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int64_t row0 = ((int64_t)blockIdx.x * kFwdWaves + w) * 16; row0 < M;
+         row0 += (int64_t)gridDim.x * kFwdWaves * 16) {
+        const int64_t m = row0 + r;
+        // an opaque zero in the LDS addresses: the weights' operands are read
+        // where they are used, not all held in registers across the row loop
+        int at = 0;
+        asm volatile("" : "+v"(at));
+        bf16x8 h[4];
+        // ---- layer 1, in the operand's order
+        float x[kIn];
+        load_row(X + (m < M ? m : 0) * kIn, x);
 #pragma unroll
-    for (int f = 0; f < kIn; ++f) {
-        const __bf16 xb = (__bf16)(act && m < Mvalid ? X[m * kIn + f] : 0.0f);
-        x[f] = (float)xb;
-        if (TRAIN && act && g == 0) Xb[m * kIn + f] = xb;
-    }
-    bf16x8 a[4];
+        for (int s = 0; s < 4; ++s)
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-        float zz[8];
+            for (int j = 0; j < 2; ++j) {
+                f32x4 z;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int n = 32 * s + kq + j;
-            float z = b1[n];
+                for (int k = 0; k < 4; ++k)
+                    z[k] = layer1(&sW1[0][0] + at + (32 * s + 8 * g + 4 * j + k) * 8, x);
+                const bf16x4 v = gelu_bf16(z);
 #pragma unroll
-            for (int f = 0; f < kIn; ++f) z += x[f] * (float)W1[n * kIn + f];
-            zz[j] = z;
-            a[s][j] = (__bf16)gelu(z);
-        }
-        if (TRAIN && act) {
-            float* z1 = Z1 + m * kWidth + 32 * s + kq;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) z1[j] = zz[j];
-            *(bf16x8*)(H1 + m * kWidth + 32 * s + kq) = a[s];
-        }
-    }
-    // ---- layers 2 and 3 (128 -> 128) on the matrix cores
-#pragma unroll
-    for (int layer = 0; layer < 2; ++layer) {
-        if (layer == 1) {
-            // every wave has read W2: replace it by W3
-            __syncthreads();
-            stage(W3);
-            __syncthreads();
-        }
-        if (!act) continue;
-        const float* bias = layer == 0 ? b2 : b3;
-        float* Zg = layer == 0 ? Z2 : Z3;
-        __bf16* Hg = layer == 0 ? H2 : H3;
-        f32x4 acc[8];
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+                for (int k = 0; k < 4; ++k) h[s][4 * j + k] = v[k];
+            }
+#pragma unroll 1
+        for (int n = 0; n < 2; ++n) {
+            bf16x8 hn[4];
 #pragma unroll
             for (int s = 0; s < 4; ++s) {
-                const bf16x8 b = *(const bf16x8*)&sW[(16 * c + r) * kLdsW + 32 * s + kq];
-                acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[s], b, acc[c], 0, 0, 0);
+                bf16x4 v[2];
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const int c = 2 * s + i;
+                    const f32x4 bias = *(const f32x4*)&sB[n][at + 16 * c + 4 * g];
+                    const f32x4 z = row_tile(sW[n] + at, c, l, h, f32x4{0.f, 0.f, 0.f, 0.f});
+                    v[i] = gelu_bf16(z + bias);
+                }
+                hn[s] = to_operand(v[0], v[1]);
             }
+#pragma unroll
+            for (int s = 0; s < 4; ++s) h[s] = hn[s];
         }
-        // bias + GELU in the accumulator layout: lane holds rows 4g..4g+3 of column 16c + r
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            const int col = 16 * c + r;
-            const float bc = bias[col];
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const int rr = 4 * g + t;
-                const float z = acc[c][t] + bc;
-                const __bf16 h = (__bf16)gelu(z);
-                acc[c][t] = (float)h;  // keep the rounded activation for layer 4
-                hs[rr * kLdsW + col] = h;
-                if (TRAIN) {
-                    const int64_t mm = row0 + rr;
-                    Zg[mm * kWidth + col] = z;
-                    Hg[mm * kWidth + col] = h;
-                }
-            }
-        }
-        if (layer == 0) {
-            // back to the A-operand layout for layer 3 (wave-local tile; LDS
-            // operations of one wave complete in order)
-            __builtin_amdgcn_s_waitcnt(0xc07f);
-            __builtin_amdgcn_wave_barrier();
-#pragma unroll
-            for (int s = 0; s < 4; ++s) a[s] = *(const bf16x8*)&hs[r * kLdsW + 32 * s + kq];
-        } else {
-            // ---- layer 4 (128 -> 4): lane partial sums over its 8 columns
-            float ysum[4][kOut];
-#pragma unroll
-            for (int t = 0; t < 4; ++t)
-#pragma unroll
-                for (int o = 0; o < kOut; ++o) {
-                    float sacc = 0.0f;
-#pragma unroll
-                    for (int c = 0; c < 8; ++c)
-                        sacc += acc[c][t] * (float)W4[o * kWidth + 16 * c + r];
-                    ysum[t][o] = sacc;
-                }
-#pragma unroll
-            for (int off = 8; off > 0; off >>= 1)
-#pragma unroll
-                for (int t = 0; t < 4; ++t)
-#pragma unroll
-                    for (int o = 0; o < kOut; ++o) ysum[t][o] += __shfl_xor(ysum[t][o], off, 64);
-            if (r < kOut) {
-                const int o = r;
-#pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    const int64_t mm = row0 + 4 * g + t;
-                    float yv = 0.0f;
-#pragma unroll
-                    for (int oo = 0; oo < kOut; ++oo)
-                        if (oo == o) yv = ysum[t][oo];
-                    yv += b4[o];
-                    if (TRAIN) {
-                        const float res = mm < Mvalid ? yv - T[mm * kOut + o] : 0.0f;
-                        dY[mm * kOut + o] = 2.0f * res / (4.0f * (float)Mvalid);
-                        se[mm * kOut + o] = res * res;
-                    } else if (mm < Mvalid) {
-                        Y[mm * kOut + o] = yv;
-                    }
-                }
-            }
+        // ---- layer 4: outputs 0..3 of a row are the accumulators of its lane g = 0
+        const f32x4 y = row_tile(sW4 + at, 0, l, h, out0);
+        if (g == 0 && m < M) {
+            float* o = Y + m * kOut;  // the caller's pointer: four-byte alignment
+            o[0] = y[0];
+            o[1] = y[1];
+            o[2] = y[2];
+            o[3] = y[3];
         }
     }
 }
 
-// Backward through a dense layer: dH = dZn W (dZn [M][128] bf16, W [out][in]),
-// then dZ = dH * GELU'(Zprev); stored as bf16 (ROUND) or fp32.
-template <bool ROUND>
-__global__ void __launch_bounds__(64) k_dense_bwd_data(int M, const __bf16* __restrict__ dZn,
-                                                       const __bf16* __restrict__ W,
-                                                       const float* __restrict__ Zprev,
-                                                       __bf16* __restrict__ dZb,
-                                                       float* __restrict__ dZf) {
-    const int tile = blockIdx.x;
-    const int r0 = 16 * (tile >> 3), c0 = 16 * (tile & 7);
-    if (r0 >= M) return;
-    // C[m][i] = sum_o dZn[m][o] W[o][i]: A row stride 128, B k stride 128
-    const f32x4 acc = tile_mma(dZn, kWidth, 1, W, kWidth, 1, r0, c0, 0, kWidth);
-    const int l = threadIdx.x;
-    const int c = c0 + (l & 15);
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        const int64_t o = (int64_t)(r0 + 4 * (l >> 4) + t) * kWidth + c;
-        const float v = acc[t] * gelu_prime(Zprev[o]);
-        if (ROUND) dZb[o] = (__bf16)v;
-        else dZf[o] = v;
-    }
-}
-
-// Weight gradient partials: P[chunk][o][i] = sum_{m in chunk} dZ[m][o] H[m][i]
-// (both [M][128] bf16).  Grid: (64 tiles, nchunks).
-__global__ void __launch_bounds__(64) k_dense_wgrad(int M, int mchunk, const __bf16* __restrict__ dZ,
-                                                    const __bf16* __restrict__ H,
-                                                    float* __restrict__ P) {
-    const int tile = blockIdx.x, ch = blockIdx.y;
-    const int r0 = 16 * (tile >> 3), c0 = 16 * (tile & 7);
-    const int k0 = ch * mchunk, k1 = min(M, k0 + mchunk);
-    if (k0 >= k1) return;
-    // C[o][i] = sum_m A[o][m] B[m][i]: A = dZ^T (row stride 1, k stride 128)
-    const f32x4 acc = tile_mma(dZ, 1, kWidth, H, kWidth, 1, r0, c0, k0, k1);
-    const int l = threadIdx.x;
-    const int c = c0 + (l & 15);
-    float* out = P + (int64_t)ch * kWidth * kWidth;
-#pragma unroll
-    for (int t = 0; t < 4; ++t) out[(r0 + 4 * (l >> 4) + t) * kWidth + c] = acc[t];
-}
-
-// Layer 4 backward: dZ3 = bf16((dY W4) * GELU'(Z3)).
-__global__ void __launch_bounds__(256) k_layer_out_bwd(int M, const float* __restrict__ dY,
-                                                       const __bf16* __restrict__ W4,
-                                                       const float* __restrict__ Z3,
-                                                       __bf16* __restrict__ dZ3) {
-    const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (g >= (int64_t)M * kWidth) return;
-    const int m = (int)(g / kWidth), k = (int)(g % kWidth);
-    float s = 0.0f;
-#pragma unroll
-    for (int o = 0; o < kOut; ++o) s += dY[(int64_t)m * kOut + o] * (float)W4[o * kWidth + k];
-    dZ3[g] = (__bf16)(s * gelu_prime(Z3[g]));
-}
-
-// Partial sums of small products over one chunk of rows, one thread per
-// output, rows in fixed order: part[chunk][r][c] = sum_{m in chunk} P[m][r]
-// Q[m][c] (no Q: P[m][r]).  All such sums of a backward pass in one launch:
-// grid.y = chunk, grid.z = job.
-struct ColJobs {
-    int32_t R[kMaxColJobs], Cn[kMaxColJobs], ldp[kMaxColJobs], ldq[kMaxColJobs];
-    int32_t p_bf16[kMaxColJobs];  // P stored as bf16, else fp32
-    const void* P[kMaxColJobs];
-    const __bf16* Q[kMaxColJobs];  // nullptr: plain column sums of P
-    float* part[kMaxColJobs];
-};
-
-template <class TP>
-__device__ __forceinline__ float colsum_rows(const TP* __restrict__ P, int ldp,
-                                             const __bf16* __restrict__ Q, int ldq, int r, int c,
-                                             int m0, int m1) {
-    float s = 0.0f;
-    if (Q) {
-        for (int m = m0; m < m1; ++m)
-            s += (float)P[(int64_t)m * ldp + r] * (float)Q[(int64_t)m * ldq + c];
-    } else {
-        for (int m = m0; m < m1; ++m) s += (float)P[(int64_t)m * ldp + r];
-    }
-    return s;
-}
-
-__global__ void __launch_bounds__(256) k_colsum_jobs(int M, int mchunk, ColJobs J) {
-    const int y = blockIdx.z;
-    const int R = J.R[y], Cn = J.Cn[y];
-    const int g = blockIdx.x * blockDim.x + threadIdx.x;
-    if (g >= R * Cn) return;
-    const int r = g / Cn, c = g % Cn;
-    const int m0 = blockIdx.y * mchunk, m1 = min(M, m0 + mchunk);
-    const float s =
-        J.p_bf16[y]
-            ? colsum_rows((const __bf16*)J.P[y], J.ldp[y], J.Q[y], J.ldq[y], r, c, m0, m1)
-            : colsum_rows((const float*)J.P[y], J.ldp[y], J.Q[y], J.ldq[y], r, c, m0, m1);
-    J.part[y][(int64_t)blockIdx.y * R * Cn + g] = s;
-}
-
-// All second-stage sums of one backward pass in one launch: out_y[k] =
-// sum_ch P_y[ch][k], where the partials of sum y start at P + off[y] (nch[y]
-// chunks of n[y] values).  Block (x, y) covers outputs [64 x, 64 x + 64) of
-// sum y with 4 thread groups, group g adding chunks g, g + 4, ... in order;
-// the four group sums are then added in group order (a fixed order throughout).
-struct SumJobs {
-    int32_t n[kMaxSumJobs];
-    int32_t nch[kMaxSumJobs];
-    int64_t off[kMaxSumJobs];
-    float* out[kMaxSumJobs];
-};
-
-__global__ void __launch_bounds__(256) k_sum_jobs(SumJobs J, const float* __restrict__ P) {
-    __shared__ float part[4][64];
-    const int y = blockIdx.y;
-    const int n = J.n[y], nch = J.nch[y];
-    if ((int)blockIdx.x * 64 >= n) return;  // uniform over the block
-    const float* Py = P + J.off[y];
-    const int j = threadIdx.x & 63, g = threadIdx.x >> 6;
-    const int k = blockIdx.x * 64 + j;
-    float s = 0.0f;
-    if (k < n)
-        for (int c = g; c < nch; c += 4) s += Py[(int64_t)c * n + k];
-    part[g][j] = s;
-    __syncthreads();
-    if (g == 0 && k < n) J.out[y][k] = ((part[0][j] + part[1][j]) + part[2][j]) + part[3][j];
-}
-
-// One block of 1024 threads; fixed-order partial sums then a fixed tree.
-__global__ void __launch_bounds__(1024) k_sum_all(int n, const float* __restrict__ v,
-                                                  double* __restrict__ out) {
-    __shared__ double red[16];
-    double s = 0.0;
-    for (int k = threadIdx.x; k < n; k += blockDim.x) s += v[k];
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double t = 0.0;
-        for (int w = 0; w < 16; ++w) t += red[w];
-        out[0] = t;
-    }
-}
-
-// bf16 copies of the weights (and the transposes are not needed: the MFMA
-// operands address W through strides).
-__global__ void __launch_bounds__(256) k_refresh(const float* __restrict__ theta,
-                                                 __bf16* __restrict__ W1, __bf16* __restrict__ W2,
-                                                 __bf16* __restrict__ W3, __bf16* __restrict__ W4) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < kWidth * kIn) W1[k] = (__bf16)theta[kOffW1 + k];
-    if (k < kWidth * kWidth) {
-        W2[k] = (__bf16)theta[kOffW2 + k];
-        W3[k] = (__bf16)theta[kOffW3 + k];
-    }
-    if (k < kOut * kWidth) W4[k] = (__bf16)theta[kOffW4 + k];
-}
-
-// Adam (fp32): m = b1 m + (1-b1) g, v = b2 v + (1-b2) g^2,
-// theta -= lr * (m / (1 - b1^t)) / (sqrt(v / (1 - b2^t)) + eps).
-__global__ void __launch_bounds__(256) k_adam(int n, float lr, float b1, float b2, float eps,
-                                              float c1, float c2, const float* __restrict__ g,
-                                              float* __restrict__ m, float* __restrict__ v,
-                                              float* __restrict__ theta, __bf16* __restrict__ W1,
-                                              __bf16* __restrict__ W2, __bf16* __restrict__ W3,
-                                              __bf16* __restrict__ W4) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= n) return;
-    const float gk = g[k];
-    const float mk = b1 * m[k] + (1.0f - b1) * gk;
-    const float vk = b2 * v[k] + (1.0f - b2) * gk * gk;
-    m[k] = mk;
-    v[k] = vk;
-    const float t = theta[k] - lr * (mk / c1) / (sqrtf(vk / c2) + eps);
-    theta[k] = t;
-    // the bf16 copy the forward and backward kernels read (as k_refresh makes it)
-    if (k >= kOffW1 && k < kOffW1 + kWidth * kIn) W1[k - kOffW1] = (__bf16)t;
-    else if (k >= kOffW2 && k < kOffW2 + kWidth * kWidth) W2[k - kOffW2] = (__bf16)t;
-    else if (k >= kOffW3 && k < kOffW3 + kWidth * kWidth) W3[k - kOffW3] = (__bf16)t;
-    else if (k >= kOffW4 && k < kOffW4 + kOut * kWidth) W4[k - kOffW4] = (__bf16)t;
-}
-
-// Minibatch gather: row r takes dataset row floor(h * n / 2^64), h the
-// splitmix64 hash of seed + step * B + r.
 __device__ __forceinline__ uint64_t splitmix64(uint64_t z) {
     z += 0x9E3779B97F4A7C15ull;
     z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
@@ -402,18 +241,385 @@ __device__ __forceinline__ uint64_t splitmix64(uint64_t z) {
     return z ^ (z >> 31);
 }
 
-__global__ void __launch_bounds__(256) k_gather(int64_t n, int B, uint64_t seed, int64_t step,
-                                                const float* __restrict__ X,
-                                                const float* __restrict__ T,
-                                                float* __restrict__ Xo, float* __restrict__ To) {
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= B) return;
-    const uint64_t h = splitmix64(seed + (uint64_t)step * (uint64_t)B + (uint64_t)r);
-    const int64_t i = (int64_t)__umul64hi(h, (uint64_t)n);
+// The rows of a training pass: row r of a given array, or of a data set of n
+// rows the row floor(h n / 2^64), h the splitmix64 hash of seed + step batch + r.
+struct Rows {
+    const float* X;
+    const float* T;
+    int64_t n;  // 0: the arrays hold the rows themselves
+    uint64_t first;  // seed + step * batch
+};
+__device__ __forceinline__ int64_t data_row(const Rows& R, int64_t r) {
+    return R.n ? (int64_t)__umul64hi(splitmix64(R.first + (uint64_t)r), (uint64_t)R.n) : r;
+}
+
+// Forward and backward of kTrainRows rows a turn in one block, blocks walking
+// over the rows: loss and the gradient's partial sums over the block's rows,
+// part[block][parameter].  Wave w takes the 16 units of tile w of every layer
+// and all rows of the turn, so that a block reads each weight fragment once.
+// Activations and pre-activation gradients pass from layer to layer as operand
+// fragments in LDS (two buffers in turn, one barrier a layer) and are kept as
+// [unit][row] for the products over rows at the end;
+// GELU' of the three layers stays in registers.  The 128 x 128 weight gradients
+// accumulate in registers over the block's turns, one row of 16 x 16 tiles a
+// wave and matrix; the sums that have fp32 factors (W1, W4, biases) run on the
+// vector units, four threads a unit.
+// Bound by the path of one wave: 30 KB of code met once, eight barriers, 24
+// GELU evaluations a lane.  A training step of 8,192 rows (one turn, a block on
+// every CU) takes 32 us, 9 of them for the 35 MB of partial sums; with a launch
+// for each product and sum it took 103 us.  64 rows a turn (half the partial sums,
+// half of the CUs): 5 us more.
+constexpr int kTrainRows = 32;
+constexpr int kTrainThreads = 512;
+constexpr int kLdB = kTrainRows + 8;  // row strides: 16-byte reads of neighbouring units fall in
+constexpr int kLdF = kTrainRows + 4;  // distinct banks
+
+struct TrainLds {
+    __bf16 H[3][kWidth * kLdB];
+    __bf16 dZ[2][kWidth * kLdB];  // layers 3, 2
+    union {
+        __bf16 pass[2][kTrainRows * kWidth];  // fragments between layers
+        float dZ1[kWidth * kLdF];             // then layer 1's gradient
+        float col[3][12][kWidth];             // at the end: sums of the unit's other threads
+    };
+    float x[kTrainRows][8];
+    float dY[kTrainRows][kOut];
+    float W1[kWidth][8], W4[kWidth][kOut], B[2][kWidth];
+    double loss[kTrainRows];
+};
+static_assert(sizeof(TrainLds) <= 160 * 1024, "the LDS of a CU");
+
+__global__ void __launch_bounds__(kTrainThreads, 2) k_mlp_train(
+    int Mvalid, Rows R, const float* __restrict__ W1f, const __bf16* __restrict__ W2f, const float* __restrict__ b2, const __bf16* __restrict__ W3f,
+    const float* __restrict__ b3, const __bf16* __restrict__ W4f, const float* __restrict__ b4,
+    const __bf16* __restrict__ W2t, const __bf16* __restrict__ W3t, float* __restrict__ part,
+    double* __restrict__ loss_part) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
+    TrainLds& L = *reinterpret_cast<TrainLds*>(lds_raw);
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    for (int k = threadIdx.x; k < kWidth; k += kTrainThreads) {
+        L.B[0][k] = b2[k];
+        L.B[1][k] = b3[k];
+    }
+    for (int k = threadIdx.x; k < kWidth * 8; k += kTrainThreads) (&L.W1[0][0])[k] = W1f[k];
+    for (int k = threadIdx.x; k < kWidth * kOut; k += kTrainThreads)
+        L.W4[k / kOut][k % kOut] = (float)W4f[fragment(k % kOut, k / kOut)];
+    __syncthreads();
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    f32x4 dW[2][8];  // layers 3, 2: tiles (w, c)
 #pragma unroll
-    for (int k = 0; k < kIn; ++k) Xo[(int64_t)r * kIn + k] = X[i * kIn + k];
+    for (int n = 0; n < 2; ++n)
 #pragma unroll
-    for (int k = 0; k < kOut; ++k) To[(int64_t)r * kOut + k] = T[i * kOut + k];
+        for (int c = 0; c < 8; ++c) dW[n][c] = zero;
+    float col[12];  // per unit: W4 (4), b3, b2, W1 (5), b1
+#pragma unroll
+    for (int k = 0; k < 12; ++k) col[k] = 0.0f;
+    f32x4 db4 = zero;  // and the loss: of the rows whose outputs the thread sums
+    double loss = 0.0;
+    const f32x4 bias4 = {b4[0], b4[1], b4[2], b4[3]};
+    const int part_u = w >> 1;  // sums over rows: unit threadIdx.x % 128, a quarter of the rows
+    for (int64_t row0 = (int64_t)blockIdx.x * kTrainRows; row0 < Mvalid;
+         row0 += (int64_t)gridDim.x * kTrainRows) {
+        // Nothing that depends on the lane is computed once for all turns: the
+        // many LDS addresses would fill the registers.
+        int lane = threadIdx.x & 63;
+        asm volatile("" : "+v"(lane));
+        const int l = lane, r = l & 15, g = l >> 4, u = 64 * (w & 1) + l;
+        // Operands of one layer, read a layer ahead of their use: the opaque zero
+        // in their addresses keeps them from being read all at once, or once for
+        // all rows, which the registers have no room for.
+        int at = 0;
+        bf16x8 wf[4];
+        auto ahead = [&](const __bf16* __restrict__ W) {
+            asm volatile("" : "+v"(at));
+#pragma unroll
+            for (int s = 0; s < 4; ++s) wf[s] = *(const bf16x8*)&W[at + ((4 * w + s) * 64 + l) * 8];
+        };
+        float x[2][kIn];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const int64_t m = row0 + 16 * t + r;
+            load_row(R.X + (m < Mvalid ? data_row(R, m) : 0) * kIn, x[t]);
+            if (w == 0 && g == 0)
+#pragma unroll
+                for (int f = 0; f < kIn; ++f) L.x[16 * t + r][f] = x[t][f];
+        }
+        // the row whose outputs this thread sums over units u % 16 == r
+        const int my = 4 * w + g;
+        const bool valid = row0 + my < Mvalid;
+        const float* target = R.T + (valid ? data_row(R, row0 + my) : 0) * kOut;
+        f32x4 t4;
+#pragma unroll
+        for (int o = 0; o < kOut; ++o) t4[o] = target[o];
+        bf16x8 h[2][4];
+        // values v of units 16 w + 4 g + 0..3, row 16 t + r
+        auto keep = [&](__bf16* rows, __bf16* pass, int t, bf16x4 v) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) rows[(16 * w + 4 * g + k) * kLdB + 16 * t + r] = v[k];
+            *(bf16x4*)&pass[((4 * t + (w >> 1)) * 64 + (2 * (w & 1) + (g >> 1)) * 16 + r) * 8 + 4 * (g & 1)] = v;
+        };
+        auto take = [&](const __bf16* pass) {
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int s = 0; s < 4; ++s)
+                    h[t][s] = *(const bf16x8*)&pass[((4 * t + s) * 64 + l) * 8];
+        };
+        auto product = [&](int t) {
+            f32x4 z = zero;
+#pragma unroll
+            for (int s = 0; s < 4; ++s) z = mfma(wf[s], h[t][s], z);
+            return z;
+        };
+        f32x4 gp[3][2];
+        // ---- forward, keeping GELU'
+        auto activate = [&](int n, int t, const f32x4& z) {
+            bf16x4 v;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                v[k] = (__bf16)gelu(z[k]);
+                gp[n][t][k] = gelu_prime(z[k]);
+            }
+            keep(L.H[n], L.pass[n % 2], t, v);
+        };
+        ahead(W2f);
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            f32x4 z;
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                z[k] = layer1(&L.W1[0][0] + at + (16 * w + 4 * g + k) * 8, x[t]);
+            activate(0, t, z);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int n = 1; n < 3; ++n) {
+            take(L.pass[n - 1]);
+            f32x4 z[2];
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+                z[t] = product(t) + *(const f32x4*)&L.B[n - 1][at + 16 * w + 4 * g];
+            ahead(n == 1 ? W3f : W3t);
+#pragma unroll
+            for (int t = 0; t < 2; ++t) activate(n, t, z[t]);
+            __syncthreads();
+        }
+        // ---- outputs, loss and its gradient: 16 threads a row, eight units each
+        f32x4 y = zero;
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            const float h3 = (float)L.H[2][(16 * c + r) * kLdB + my];
+            const f32x4 w4 = *(const f32x4*)L.W4[at + 16 * c + r];
+#pragma unroll
+            for (int o = 0; o < kOut; ++o) y[o] = fmaf(h3, w4[o], y[o]);
+        }
+#pragma unroll
+        for (int step = 8; step > 0; step >>= 1)
+#pragma unroll
+            for (int o = 0; o < kOut; ++o) y[o] += __shfl_xor(y[o], step, 64);
+        if (r == 0) {
+            f32x4 e;
+#pragma unroll
+            for (int o = 0; o < kOut; ++o) {
+                const float d = valid ? y[o] + bias4[o] - t4[o] : 0.0f;
+                loss += (double)(d * d);
+                e[o] = 2.0f * d / (4.0f * (float)Mvalid);
+                db4[o] += e[o];
+            }
+            *(f32x4*)L.dY[my] = e;
+        }
+        __syncthreads();
+        // ---- dZ3 = bf16((dY W4) GELU'), then down through W3 and W2
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const f32x4 dy = *(const f32x4*)L.dY[16 * t + r];
+            bf16x4 v;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const f32x4 w4 = *(const f32x4*)L.W4[at + 16 * w + 4 * g + k];
+                float s = 0.0f;
+#pragma unroll
+                for (int o = 0; o < kOut; ++o) s = fmaf(dy[o], w4[o], s);
+                v[k] = (__bf16)(s * gp[2][t][k]);
+            }
+            keep(L.dZ[0], L.pass[1], t, v);
+        }
+        __syncthreads();
+        take(L.pass[1]);
+        f32x4 d[2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) d[t] = product(t);
+        ahead(W2t);
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            bf16x4 v;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) v[k] = (__bf16)(d[t][k] * gp[1][t][k]);
+            keep(L.dZ[1], L.pass[0], t, v);
+        }
+        __syncthreads();
+        take(L.pass[0]);
+        __syncthreads();  // dZ1 takes the place of the fragments
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            d[t] = product(t);
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                L.dZ1[(16 * w + 4 * g + k) * kLdF + 16 * t + r] = d[t][k] * gp[0][t][k];
+        }
+        __syncthreads();
+        // ---- weight gradients over the block's rows: dZ^T H, K = rows
+#pragma unroll
+        for (int n = 0; n < 2; ++n) {
+            const bf16x8 a = *(const bf16x8*)&L.dZ[n][(16 * w + r) * kLdB + 8 * g];
+#pragma unroll
+            for (int c = 0; c < 8; ++c)
+                dW[n][c] = mfma(a, *(const bf16x8*)&L.H[1 - n][(16 * c + r) * kLdB + 8 * g], dW[n][c]);
+        }
+        // ---- sums over rows with fp32 factors: unit u, a quarter of the rows
+        {
+            const int m0 = part_u * 8;
+            const bf16x8 h3 = *(const bf16x8*)&L.H[2][u * kLdB + m0];
+            const bf16x8 z3 = *(const bf16x8*)&L.dZ[0][u * kLdB + m0];
+            const bf16x8 z2 = *(const bf16x8*)&L.dZ[1][u * kLdB + m0];
+            const f32x4 za = *(const f32x4*)&L.dZ1[u * kLdF + m0];
+            const f32x4 zb = *(const f32x4*)&L.dZ1[u * kLdF + m0 + 4];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const f32x4 d = *(const f32x4*)L.dY[m0 + k];
+                const f32x4 xa = *(const f32x4*)L.x[m0 + k];
+                const float x4 = L.x[m0 + k][4], z1 = k < 4 ? za[k % 4] : zb[k % 4];
+#pragma unroll
+                for (int o = 0; o < kOut; ++o) col[o] += d[o] * (float)h3[k];
+                col[4] += (float)z3[k];
+                col[5] += (float)z2[k];
+#pragma unroll
+                for (int f = 0; f < 4; ++f) col[6 + f] += z1 * xa[f];
+                col[10] += z1 * x4;
+                col[11] += z1;
+            }
+        }
+        __syncthreads();
+    }
+    // ---- the block's partial sums
+    const int l = threadIdx.x & 63, r = l & 15, g = l >> 4, u = threadIdx.x & (kWidth - 1);
+    float* P = part + (int64_t)blockIdx.x * kParams;
+#pragma unroll
+    for (int n = 0; n < 2; ++n)
+#pragma unroll
+        for (int c = 0; c < 8; ++c)
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                P[(n == 0 ? kOffW3 : kOffW2) + (16 * w + 4 * g + k) * kWidth + 16 * c + r] =
+                    dW[n][c][k];
+    if (part_u > 0)
+#pragma unroll
+        for (int k = 0; k < 12; ++k) L.col[part_u - 1][k][u] = col[k];
+    if (r == 0) {
+        L.loss[4 * w + g] = loss;
+        *(f32x4*)L.dY[4 * w + g] = db4;
+    }
+    __syncthreads();
+    if (part_u == 0) {
+#pragma unroll
+        for (int k = 0; k < 12; ++k) col[k] += (L.col[0][k][u] + L.col[1][k][u]) + L.col[2][k][u];
+#pragma unroll
+        for (int o = 0; o < kOut; ++o) P[kOffW4 + o * kWidth + u] = col[o];
+        P[kOffB3 + u] = col[4];
+        P[kOffB2 + u] = col[5];
+#pragma unroll
+        for (int f = 0; f < kIn; ++f) P[kOffW1 + u * kIn + f] = col[6 + f];
+        P[kOffB1 + u] = col[11];
+    }
+    if (threadIdx.x < kOut) {
+        float s = 0.0f;
+        for (int m = 0; m < kTrainRows; ++m) s += L.dY[m][threadIdx.x];
+        P[kOffB4 + threadIdx.x] = s;
+    }
+    if (threadIdx.x == 64) {
+        double s = 0.0;
+        for (int m = 0; m < kTrainRows; ++m) s += L.loss[m];
+        loss_part[blockIdx.x] = s;
+    }
+}
+
+// The bf16 copies of parameter k with value t that the kernels read: weights
+// as operand fragments, W2 and W3 in both orientations.
+__device__ __forceinline__ void store_copies(int k, float t, const WeightCopies& C) {
+    const __bf16 q = (__bf16)t;
+    if (k >= kOffW1 && k < kOffW1 + kWidth * kIn) {
+        const int row = (k - kOffW1) / kIn, f = (k - kOffW1) % kIn;
+        C.W1f[row * 8 + f] = (float)q;
+    } else if (k >= kOffB1 && k < kOffB1 + kWidth) {
+        C.W1f[(k - kOffB1) * 8 + kIn] = t;
+    } else if (k >= kOffW2 && k < kOffW2 + kWidth * kWidth) {
+        const int o = (k - kOffW2) / kWidth, i = (k - kOffW2) % kWidth;
+        C.W2f[fragment(o, i)] = q;
+        C.W2t[fragment(i, o)] = q;
+    } else if (k >= kOffW3 && k < kOffW3 + kWidth * kWidth) {
+        const int o = (k - kOffW3) / kWidth, i = (k - kOffW3) % kWidth;
+        C.W3f[fragment(o, i)] = q;
+        C.W3t[fragment(i, o)] = q;
+    } else if (k >= kOffW4 && k < kOffW4 + kOut * kWidth) {
+        const int o = (k - kOffW4) / kWidth, i = (k - kOffW4) % kWidth;
+        C.W4f[fragment(o, i)] = q;
+    }
+}
+
+__global__ void __launch_bounds__(256) k_refresh(const float* __restrict__ theta, WeightCopies C) {
+    const int k = blockIdx.x * blockDim.x + threadIdx.x;
+    if (k < kParams) store_copies(k, theta[k], C);
+}
+
+// Adam (fp32): m = b1 m + (1-b1) g, v = b2 v + (1-b2) g^2,
+// theta -= lr * (m / (1 - b1^t)) / (sqrt(v / (1 - b2^t)) + eps).
+struct Adam {
+    float lr, b1, b2, eps, c1, c2;
+    float* m;
+    float* v;
+    float* theta;
+};
+
+// The gradient from the blocks' partial sums: block b covers parameters
+// [64 b, 64 b + 64) with four thread groups, group g adding parts g, g + 4, ...
+// in order, the four group sums in group order (fixed throughout); the last
+// block adds the loss.  Into grad (may be NULL), and with STEP into an Adam
+// step of the parameters and their copies.
+template <bool STEP>
+__global__ void __launch_bounds__(256) k_grad_sum(int nparts, const float* __restrict__ part,
+                                                  const double* __restrict__ loss_part,
+                                                  float* __restrict__ grad,
+                                                  double* __restrict__ loss, Adam A,
+                                                  WeightCopies C) {
+    __shared__ float group[4][64];
+    const int j = threadIdx.x & 63, g = threadIdx.x >> 6;
+    if (blockIdx.x == gridDim.x - 1) {
+        if (g != 0) return;
+        double t = 0.0;
+        for (int b = j; b < nparts; b += 64) t += loss_part[b];
+        for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o, 64);
+        if (j == 0) loss[0] = t;
+        return;
+    }
+    const int k = blockIdx.x * 64 + j;
+    float s = 0.0f;
+    if (k < kParams)
+#pragma unroll 8
+        for (int b = g; b < nparts; b += 4) s += part[(int64_t)b * kParams + k];
+    group[g][j] = s;
+    __syncthreads();
+    if (g != 0 || k >= kParams) return;
+    const float gk = ((group[0][j] + group[1][j]) + group[2][j]) + group[3][j];
+    if (grad) grad[k] = gk;
+    if (STEP) {
+        const float mk = A.b1 * A.m[k] + (1.0f - A.b1) * gk;
+        const float vk = A.b2 * A.v[k] + (1.0f - A.b2) * gk * gk;
+        A.m[k] = mk;
+        A.v[k] = vk;
+        const float t = A.theta[k] - A.lr * (mk / A.c1) / (sqrtf(vk / A.c2) + A.eps);
+        A.theta[k] = t;
+        store_copies(k, t, C);
+    }
 }
 
 // Squared distance from c to the nearest wall point of component k, by runs of
@@ -584,146 +790,69 @@ __global__ void k_vet(int ncomp, const double* __restrict__ res, const double* _
     if (!(res[k] < res_fs[k])) bad[k] = 1;
 }
 
-inline unsigned nblk(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
-
 }  // namespace
 
 hipError_t refresh_weights(Net& net) {
-    hipLaunchKernelGGL(k_refresh, dim3(nblk(kWidth * kWidth, 256)), dim3(256), 0, net.stream,
-                       net.theta, net.W1b, net.W2b, net.W3b, net.W4b);
+    hipLaunchKernelGGL(k_refresh, dim3(nblk(kParams, 256)), dim3(256), 0, net.stream, net.theta,
+                       net.copies);
     return hipGetLastError();
 }
 
-// Forward over rows [0, M) of the workspace (M a multiple of 16, Mvalid <= M).
-hipError_t forward(Net& net, const float* X, int M, int Mvalid, const float* T, float* Y) {
-    hipStream_t st = net.stream;
+// Blocks for rows: all of them while there is a CU for each, then two a CU
+// that walk over the rows.
+hipError_t forward(Net& net, const float* X, int M, float* Y) {
     const float* th = net.theta;
-    const dim3 grid(nblk(M, 16 * kFwdWaves)), block(64 * kFwdWaves);
-    if (T)
-        hipLaunchKernelGGL(k_mlp_forward<true>, grid, block, 0, st, M, Mvalid, X, net.W1b,
-                           th + kOffB1, net.W2b, th + kOffB2, net.W3b, th + kOffB3, net.W4b,
-                           th + kOffB4, T, (float*)nullptr, net.Xb, net.Z1, net.Z2, net.Z3,
-                           net.H1, net.H2, net.H3, net.dY, net.se);
-    else
-        hipLaunchKernelGGL(k_mlp_forward<false>, grid, block, 0, st, M, Mvalid, X, net.W1b,
-                           th + kOffB1, net.W2b, th + kOffB2, net.W3b, th + kOffB3, net.W4b,
-                           th + kOffB4, (const float*)nullptr, Y, net.Xb, net.Z1, net.Z2,
-                           net.Z3, net.H1, net.H2, net.H3, net.dY, net.se);
+    const WeightCopies& C = net.copies;
+    const unsigned nb = std::min(nblk(M, 16 * kFwdWaves), 512u);
+    hipLaunchKernelGGL(k_mlp_forward, dim3(nb), dim3(64 * kFwdWaves), 0, net.stream, M, X,
+                       C.W1f, C.W2f, th + kOffB2, C.W3f, th + kOffB3, C.W4f,
+                       th + kOffB4, Y);
     return hipGetLastError();
 }
 
-// Backward after a forward with targets: gradient (flat, fp32) into net.grad.
-// Two-stage sum over rows: chunk partials, then a fixed-order sum of the chunks.
-// The sums over rows of one backward pass: each first stage writes its chunk
-// partials to its own region of net.part (sized by part_floats for the
-// workspace), and one launch adds them all at the end.
-struct SumPlan {
-    SumJobs jobs{};
-    int njobs = 0;
-    int nmax = 0;
-    int64_t off = 0;
-    // registers a sum of nch chunk partials of n values; returns where its
-    // partials start in net.part
-    ColJobs cols{};
-    int ncols = 0;
-    int colmax = 0;
-    int64_t add(int n, int nch, float* out) {
-        jobs.n[njobs] = n;
-        jobs.nch[njobs] = nch;
-        jobs.off[njobs] = off;
-        jobs.out[njobs] = out;
-        nmax = std::max(nmax, n);
-        const int64_t at = off;
-        off += (int64_t)nch * n;
-        ++njobs;
-        return at;
+int part_count(int64_t rows) {
+    return (int)std::min<int64_t>((rows + kTrainRows - 1) / kTrainRows, kMaxParts);
+}
+
+// Gradient (fp32, into grad) and sum of squared errors of m rows, two launches;
+// lr: also an Adam step.
+static hipError_t gradient_rows(Net& net, const Rows& R, int m, float* grad, double* loss,
+                                const float* lr) {
+    const float* th = net.theta;
+    const WeightCopies& C = net.copies;
+    const int nparts = part_count(m);
+    hipLaunchKernelGGL(k_mlp_train, dim3(nparts), dim3(kTrainThreads), sizeof(TrainLds), net.stream, m, R,
+                       C.W1f, C.W2f, th + kOffB2, C.W3f, th + kOffB3, C.W4f,
+                       th + kOffB4, C.W2t, C.W3t, net.part, net.loss_part);
+    const dim3 g(nblk(kParams, 64) + 1), b(256);
+    if (lr) {
+        net.step += 1;
+        const float b1 = 0.9f, b2 = 0.999f;
+        const Adam A{*lr, b1, b2, 1e-8f, 1.0f - std::pow(b1, (float)net.step),
+                     1.0f - std::pow(b2, (float)net.step), net.m, net.v, net.theta};
+        hipLaunchKernelGGL(k_grad_sum<true>, g, b, 0, net.stream, nparts, net.part, net.loss_part,
+                           grad, loss, A, C);
+    } else {
+        hipLaunchKernelGGL(k_grad_sum<false>, g, b, 0, net.stream, nparts, net.part, net.loss_part,
+                           grad, loss, Adam{}, C);
     }
-};
-
-constexpr int kColRows = 64;  // rows per thread in a column-sum first stage
-
-// Registers the column sums of P (times Q when given) over rows; their first
-// stage runs with the others at the end of the backward pass.
-static void colsum(Net& net, SumPlan& plan, int M, int R, int Cn, const void* P, bool p_bf16,
-                   int ldp, const __bf16* Q, int ldq, float* out) {
-    const int nch = (M + kColRows - 1) / kColRows;
-    const int k = plan.ncols++;
-    plan.cols.R[k] = R;
-    plan.cols.Cn[k] = Cn;
-    plan.cols.ldp[k] = ldp;
-    plan.cols.ldq[k] = ldq;
-    plan.cols.p_bf16[k] = p_bf16;
-    plan.cols.P[k] = P;
-    plan.cols.Q[k] = Q;
-    plan.cols.part[k] = net.part + plan.add(R * Cn, nch, out);
-    plan.colmax = std::max(plan.colmax, R * Cn);
-}
-
-static void wgrad(Net& net, SumPlan& plan, int M, const __bf16* dZ, const __bf16* H, float* out) {
-    const int nch = (M + kChunk - 1) / kChunk;
-    float* dst = net.part + plan.add(kWidth * kWidth, nch, out);
-    hipLaunchKernelGGL(k_dense_wgrad, dim3(64, nch), dim3(64), 0, net.stream, M, kChunk, dZ, H,
-                       dst);
-}
-
-int64_t part_floats(int64_t cap) {
-    const int64_t nw = (cap + kChunk - 1) / kChunk, nc = (cap + kColRows - 1) / kColRows;
-    return 2 * nw * kWidth * kWidth +
-           nc * (kOut * kWidth + kOut + kWidth + kWidth + kWidth * kIn + kWidth);
-}
-
-hipError_t backward(Net& net, int M) {
-    hipStream_t st = net.stream;
-    float* g = net.grad;
-    SumPlan plan;
-    // layer 4
-    colsum(net, plan, M, kOut, kWidth, net.dY, false, kOut, net.H3, kWidth, g + kOffW4);
-    colsum(net, plan, M, kOut, 1, net.dY, false, kOut, nullptr, 0, g + kOffB4);
-    hipLaunchKernelGGL(k_layer_out_bwd, dim3(nblk((int64_t)M * kWidth, 256)), dim3(256), 0, st, M,
-                       net.dY, net.W4b, net.Z3, net.dZ3);
-    // layer 3
-    wgrad(net, plan, M, net.dZ3, net.H2, g + kOffW3);
-    colsum(net, plan, M, kWidth, 1, net.dZ3, true, kWidth, nullptr, 0, g + kOffB3);
-    hipLaunchKernelGGL(k_dense_bwd_data<true>, dim3((M / 16) * 8), dim3(64), 0, st, M, net.dZ3,
-                       net.W3b, net.Z2, net.dZ2, (float*)nullptr);
-    // layer 2
-    wgrad(net, plan, M, net.dZ2, net.H1, g + kOffW2);
-    colsum(net, plan, M, kWidth, 1, net.dZ2, true, kWidth, nullptr, 0, g + kOffB2);
-    hipLaunchKernelGGL(k_dense_bwd_data<false>, dim3((M / 16) * 8), dim3(64), 0, st, M, net.dZ2,
-                       net.W2b, net.Z1, (__bf16*)nullptr, net.dZ1);
-    // layer 1
-    colsum(net, plan, M, kWidth, kIn, net.dZ1, false, kWidth, net.Xb, kIn, g + kOffW1);
-    colsum(net, plan, M, kWidth, 1, net.dZ1, false, kWidth, nullptr, 0, g + kOffB1);
-    // the column sums' first stage, then every second stage
-    hipLaunchKernelGGL(k_colsum_jobs, dim3(nblk(plan.colmax, 256), (M + kColRows - 1) / kColRows,
-                                           plan.ncols),
-                       dim3(256), 0, st, M, kColRows, plan.cols);
-    hipLaunchKernelGGL(k_sum_jobs, dim3(nblk(plan.nmax, 64), plan.njobs), dim3(256), 0, st,
-                       plan.jobs, net.part);
     return hipGetLastError();
 }
 
-hipError_t loss(Net& net, int M, double* d_out) {
-    hipLaunchKernelGGL(k_sum_all, dim3(1), dim3(1024), 0, net.stream, M * kOut, net.se, d_out);
-    return hipGetLastError();
+hipError_t gradient(Net& net, const float* X, const float* T, int m, float* grad, double* loss,
+                    const float* lr) {
+    return gradient_rows(net, Rows{X, T, 0, 0}, m, grad, loss, lr);
 }
 
-hipError_t adam_step(Net& net, float lr) {
-    net.step += 1;
-    const float b1 = 0.9f, b2 = 0.999f;
-    const float c1 = 1.0f - std::pow(b1, (float)net.step);
-    const float c2 = 1.0f - std::pow(b2, (float)net.step);
-    hipLaunchKernelGGL(k_adam, dim3(nblk(kParams, 256)), dim3(256), 0, net.stream, kParams, lr, b1,
-                       b2, 1e-8f, c1, c2, net.grad, net.m, net.v, net.theta, net.W1b, net.W2b,
-                       net.W3b, net.W4b);
-    return hipGetLastError();
+hipError_t minibatch_step(Net& net, int64_t n, const float* X, const float* T, int B, uint64_t seed,
+                          int64_t step, double* loss, float lr) {
+    return gradient_rows(net, Rows{X, T, n, seed + (uint64_t)step * (uint64_t)B}, B, nullptr, loss,
+                         &lr);
 }
 
-hipError_t gather(Net& net, int64_t n, const float* X, const float* T, int B, uint64_t seed,
-                  int64_t step) {
-    hipLaunchKernelGGL(k_gather, dim3(nblk(B, 256)), dim3(256), 0, net.stream, n, B, seed, step, X,
-                       T, net.Xin, net.Tin);
-    return hipGetLastError();
+hipError_t prepare_kernels() {
+    return hipFuncSetAttribute((const void*)k_mlp_train, hipFuncAttributeMaxDynamicSharedMemorySize,
+                               (int)sizeof(TrainLds));
 }
 
 hipError_t features(const State& s, int64_t p0, int64_t m, float* Xout, float* Tout) {

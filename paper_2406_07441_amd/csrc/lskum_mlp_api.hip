@@ -38,10 +38,9 @@ hipError_t dalloc(T** p, size_t count) {
 int64_t round_up(int64_t m, int64_t a) { return (m + a - 1) / a * a; }
 
 void free_net(M::Net& n) {
-    void* ptrs[] = {n.theta, n.grad, n.m,  n.v,  n.W1b, n.W2b, n.W3b, n.W4b, n.Xin,
-                    n.Tin,   n.Yout, n.Xb, n.Z1, n.Z2,  n.Z3,  n.H1,  n.H2,  n.H3,
-                    n.dY,    n.se,   n.dZ3, n.dZ2, n.dZ1, n.part, n.d_loss, n.d_bad,
-                    n.d_res_fs};
+    void* ptrs[] = {n.theta, n.m, n.v, n.copies.W1f, n.copies.W2f, n.copies.W3f, n.copies.W4f,
+                    n.copies.W2t, n.copies.W3t, n.Xin, n.Yout, n.part, n.loss_part, n.d_loss,
+                    n.d_bad, n.d_res_fs};
     for (void* p : ptrs) (void)hipFree(p);
     for (hipEvent_t e : n.ev)
         if (e) (void)hipEventDestroy(e);
@@ -81,15 +80,7 @@ int reset_moments(M::Net& n) {
     return LSKUM_OK;
 }
 
-// Forward (and, with T, loss terms) of m rows staged in the workspace.
-int run_forward(M::Net& n, const float* X, int64_t m, const float* T, float* Y) {
-    const int64_t M_ = round_up(m, M::kRowAlign);
-    HIPCHK(M::forward(n, X, (int)M_, (int)m, T, Y));
-    return LSKUM_OK;
-}
-
 int read_loss(M::Net& n, int64_t m, double* loss) {
-    HIPCHK(M::loss(n, (int)round_up(m, M::kRowAlign), n.d_loss));
     double s = 0.0;
     HIPCHK(hipMemcpyAsync(&s, n.d_loss, sizeof(double), hipMemcpyDeviceToHost, n.stream));
     HIPCHK(hipStreamSynchronize(n.stream));
@@ -137,7 +128,7 @@ int warm_start(M::Net& n, lskum::State& s, int32_t* fallback, double* res_warm) 
         const int64_t m = std::min<int64_t>(n.capacity, c.n - p0);
         HIPCHK(M::features(s, p0, m, n.Xin, nullptr));
         if (int r = join(n.stream, s.stream, n.ev[0])) return r;
-        if (int r = run_forward(n, n.Xin, m, nullptr, n.Yout)) return r;
+        HIPCHK(M::forward(n, n.Xin, (int)m, n.Yout));
         if (int r = join(s.stream, n.stream, n.ev[1])) return r;
         HIPCHK(M::pred_to_U(n, s, p0, m, n.Yout));
     }
@@ -195,37 +186,26 @@ int lskum_mlp_create(uint64_t seed, int64_t max_rows, void* hip_stream, lskum_ml
         if (e != hipSuccess) return bail(hip_err(e, "hipStreamCreateWithFlags"));
         n.own_stream = true;
     }
-    const int64_t cap = round_up(max_rows, M::kChunk);
+    const int64_t cap = round_up(max_rows, 256);
     n.capacity = cap;
     const int64_t W = M::kWidth;
-    hipError_t e = hipSuccess;
+    hipError_t e = M::prepare_kernels();
     auto chk = [&](hipError_t r) {
         if (e == hipSuccess) e = r;
     };
     chk(dalloc(&n.theta, M::kParams));
-    chk(dalloc(&n.grad, M::kParams));
     chk(dalloc(&n.m, M::kParams));
     chk(dalloc(&n.v, M::kParams));
-    chk(dalloc(&n.W1b, W * M::kIn));
-    chk(dalloc(&n.W2b, W * W));
-    chk(dalloc(&n.W3b, W * W));
-    chk(dalloc(&n.W4b, M::kOut * W));
+    chk(dalloc(&n.copies.W1f, M::kW1Rows));
+    chk(dalloc(&n.copies.W4f, M::kW4Frag));
+    for (__bf16** p : {&n.copies.W2f, &n.copies.W3f, &n.copies.W2t, &n.copies.W3t})
+        chk(dalloc(p, W * W));
+    if (e == hipSuccess) chk(hipMemsetAsync(n.copies.W1f, 0, M::kW1Rows * sizeof(float), n.stream));
+    if (e == hipSuccess) chk(hipMemsetAsync(n.copies.W4f, 0, M::kW4Frag * sizeof(__bf16), n.stream));
     chk(dalloc(&n.Xin, cap * M::kIn));
-    chk(dalloc(&n.Tin, cap * M::kOut));
     chk(dalloc(&n.Yout, cap * M::kOut));
-    chk(dalloc(&n.Xb, cap * M::kIn));
-    chk(dalloc(&n.Z1, cap * W));
-    chk(dalloc(&n.Z2, cap * W));
-    chk(dalloc(&n.Z3, cap * W));
-    chk(dalloc(&n.H1, cap * W));
-    chk(dalloc(&n.H2, cap * W));
-    chk(dalloc(&n.H3, cap * W));
-    chk(dalloc(&n.dY, cap * M::kOut));
-    chk(dalloc(&n.se, cap * M::kOut));
-    chk(dalloc(&n.dZ3, cap * W));
-    chk(dalloc(&n.dZ2, cap * W));
-    chk(dalloc(&n.dZ1, cap * W));
-    chk(dalloc(&n.part, M::part_floats(cap)));
+    chk(dalloc(&n.part, (size_t)M::part_count(cap) * M::kParams));
+    chk(dalloc(&n.loss_part, M::kMaxParts));
     chk(dalloc(&n.d_loss, 1));
     for (hipEvent_t& ev : n.ev) chk(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
     if (e != hipSuccess) return bail(hip_err(e, "network allocation"));
@@ -275,7 +255,7 @@ int lskum_mlp_forward(lskum_mlp* h, int64_t m, const float* X, float* Y) {
     const int64_t step = (int64_t)1 << 30;
     for (int64_t r0 = 0; r0 < m; r0 += step) {
         const int64_t k = std::min<int64_t>(step, m - r0);
-        if (int r = run_forward(n, X + r0 * M::kIn, k, nullptr, Y + r0 * M::kOut)) return r;
+        HIPCHK(M::forward(n, X + r0 * M::kIn, (int)k, Y + r0 * M::kOut));
     }
     HIPCHK(hipStreamSynchronize(n.stream));
     return LSKUM_OK;
@@ -286,11 +266,7 @@ int lskum_mlp_gradient(lskum_mlp* h, int64_t m, const float* X, const float* T, 
     if (!h || !X || !T) return api_error(LSKUM_ERR_ARG, "NULL argument");
     M::Net& n = h->n;
     if (m < 1 || m > n.capacity) return api_error(LSKUM_ERR_ARG, "m must be in [1, max_rows]");
-    if (int r = run_forward(n, X, m, T, nullptr)) return r;
-    HIPCHK(M::backward(n, (int)round_up(m, M::kRowAlign)));
-    if (grad)
-        HIPCHK(hipMemcpyAsync(grad, n.grad, M::kParams * sizeof(float), hipMemcpyDeviceToDevice,
-                              n.stream));
+    HIPCHK(M::gradient(n, X, T, (int)m, grad, n.d_loss, nullptr));
     return read_loss(n, m, loss);
 }
 
@@ -300,15 +276,8 @@ int lskum_mlp_train_step(lskum_mlp* h, int64_t m, const float* X, const float* T
     M::Net& n = h->n;
     if (m < 1 || m > n.capacity) return api_error(LSKUM_ERR_ARG, "m must be in [1, max_rows]");
     if (!(lr > 0.0f)) return api_error(LSKUM_ERR_ARG, "lr must be > 0");
-    if (int r = run_forward(n, X, m, T, nullptr)) return r;
-    HIPCHK(M::backward(n, (int)round_up(m, M::kRowAlign)));
-    HIPCHK(M::loss(n, (int)round_up(m, M::kRowAlign), n.d_loss));
-    HIPCHK(M::adam_step(n, lr));
-    double s = 0.0;
-    HIPCHK(hipMemcpyAsync(&s, n.d_loss, sizeof(double), hipMemcpyDeviceToHost, n.stream));
-    HIPCHK(hipStreamSynchronize(n.stream));
-    if (loss) *loss = s / (4.0 * (double)m);
-    return LSKUM_OK;
+    HIPCHK(M::gradient(n, X, T, (int)m, nullptr, n.d_loss, &lr));
+    return read_loss(n, m, loss);
 }
 
 int lskum_mlp_train(lskum_mlp* h, int64_t nrows, const float* X, const float* T, int32_t steps,
@@ -321,18 +290,13 @@ int lskum_mlp_train(lskum_mlp* h, int64_t nrows, const float* X, const float* T,
         return api_error(LSKUM_ERR_ARG, "invalid training arguments");
     double* d_hist = nullptr;
     HIPCHK(dalloc(&d_hist, steps));
-    const int Mp = (int)round_up(batch, M::kRowAlign);
     const auto t0 = std::chrono::steady_clock::now();
     hipError_t e = hipSuccess;
     for (int32_t t = 0; t < steps && e == hipSuccess; ++t) {
         const double frac = steps > 1 ? (double)t / (double)(steps - 1) : 0.0;
         const float lr_t =
             (float)(lr_final + 0.5 * (lr - lr_final) * (1.0 + std::cos(3.14159265358979323846 * frac)));
-        e = M::gather(n, nrows, X, T, batch, seed, t);
-        if (e == hipSuccess) e = M::forward(n, n.Xin, Mp, batch, n.Tin, nullptr);
-        if (e == hipSuccess) e = M::backward(n, Mp);
-        if (e == hipSuccess) e = M::loss(n, Mp, d_hist + t);
-        if (e == hipSuccess) e = M::adam_step(n, lr_t);
+        e = M::minibatch_step(n, nrows, X, T, batch, seed, t, d_hist + t, lr_t);
     }
     if (e == hipSuccess) e = hipStreamSynchronize(n.stream);
     const double secs =

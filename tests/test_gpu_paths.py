@@ -157,3 +157,39 @@ def test_features_nearest_wall(lk):
         assert np.abs(X[o:o + clouds[w].n] - ref).max() <= 1e-6, k
         o += clouds[w].n
     b.close()
+
+
+@pytest.mark.parametrize("m", [1, 15, 16, 17, 32, 33, 8193, 16417])
+def test_mlp_rows_at_tile_edges(lk, m):
+    """Forward (16 rows a wave, 128 a block) and gradient (32 rows a turn, at
+    most 256 blocks: 8,193 rows are the first second turn) against the oracle.
+    One activation rounded to bfloat16 the other way moves a gradient by about
+    2^-8 / sqrt(128) = 3.5e-4 of its norm; few are: 2e-3."""
+    import torch
+    from oracle import mlp as OM
+    rng = np.random.default_rng(m)
+    th = np.concatenate([rng.uniform(-1, 1, int(np.prod(s))) * (0.15 if len(s) > 1 else 0.1)
+                         for _, s in OM.SHAPES]).astype(np.float32)
+    X = rng.uniform(-1, 1, (m, 5)).astype(np.float32)
+    T = (0.3 * np.sin(np.pi * X[:, :4]) * X[:, 4:5]).astype(np.float32)
+    dX, dT = torch.from_numpy(X).cuda(), torch.from_numpy(T).cuda()
+    net = lk.MLP(max_rows=m)
+    net.set_params(th)
+    Y = net.forward(dX).cpu().numpy()
+    loss, g = net.gradient(dX, dT)
+    # rows do not depend on their place: the same bits for the rows alone
+    cut = m // 2
+    assert np.array_equal(Y, np.concatenate([net.forward(dX[k]).cpu().numpy()
+                                             for k in (slice(0, cut), slice(cut, m))]))
+    net.close()
+    th, X, T = th.astype(np.float64), X.astype(np.float64), T.astype(np.float64)
+    ref, _ = OM.forward(th, X)
+    err = np.abs(Y - ref) / np.abs(ref).max()
+    assert np.quantile(err, 0.99) <= 1e-3 and err.max() <= 2e-2, err.max()
+    rl, rg = OM.loss_and_grad(th, X, T)
+    assert abs(loss - rl) <= 1e-3 * rl
+    o = 0
+    for name, shape in OM.SHAPES:
+        k = int(np.prod(shape))
+        assert np.linalg.norm(g[o:o + k] - rg[o:o + k]) <= 2e-3 * np.linalg.norm(rg[o:o + k]), name
+        o += k
