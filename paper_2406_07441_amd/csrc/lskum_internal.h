@@ -163,6 +163,8 @@ struct Params {
 };
 
 // Device work arrays of one flow state.
+constexpr int kSlots = 3;
+
 struct State {
     const Cloud* cloud = nullptr;
     Params prm{};
@@ -219,6 +221,9 @@ struct State {
     int graph_iters = 0;
     hipEvent_t ev[8] = {};
     bool have_events = false;
+    // pinned slots for fields on their way to and from host arrays (first use)
+    double* slots = nullptr;
+    hipEvent_t slot_ev[kSlots] = {};
 };
 
 // Residual-driven CFL control of a batch (lskum_batch_set_cfl_control): a

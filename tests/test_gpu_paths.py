@@ -193,3 +193,28 @@ def test_mlp_rows_at_tile_edges(lk, m):
         k = int(np.prod(shape))
         assert np.linalg.norm(g[o:o + k] - rg[o:o + k]) <= 2e-3 * np.linalg.norm(rg[o:o + k]), name
         o += k
+
+
+@pytest.mark.parametrize("nx,ny", [(5, 5), (4681, 7), (2048, 16), (331, 99), (5243, 25)])
+def test_host_fields_by_chunks(lk, nx, ny):
+    """Fields to and from host arrays cross in chunks of 32,768 points through
+    three slots (25, 32,767, 32,768, 32,769 and 4 x 32,768 + 3 points): every
+    value arrives, the same as by the device route."""
+    import torch
+    c = cg.box(nx, ny)
+    U = np.empty((4, c.n))
+    U[0] = 1.0 + 1e-3 * np.arange(c.n) / c.n
+    U[1], U[2] = 0.3, -0.1 * np.arange(c.n) / c.n
+    U[3] = 2.5 + 1e-4 * np.arange(c.n)[::-1] / c.n
+    st = lk.State(lk.Cloud(c), 0.5, 1.0, lk.default_params())
+    st.set_U(U)
+    assert np.array_equal(st.get_U(), U)
+    st.set_U(torch.from_numpy(U + 1e-3).cuda())
+    assert np.array_equal(st.get_U(), st.get_U(device=True).cpu().numpy())
+    st.close()
+    small = lk.Cloud(cg.box(5, 5))
+    b = lk.Batch([small, lk.Cloud(c)], [0, 1, 0], [0.5] * 3, [0.0] * 3, lk.default_params())
+    b.set_U(1, U)
+    assert np.array_equal(b.get_U(1), U)
+    assert np.array_equal(b.get_U(0), b.get_U(2))
+    b.close()
