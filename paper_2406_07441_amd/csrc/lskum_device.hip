@@ -836,6 +836,7 @@ __device__ __forceinline__ D4 reconstruct(const D4& q, const D4& gx, const D4& g
 }
 
 constexpr int kResidualMinTiles = 256;  // one block per CU
+constexpr int kSub4Tiles = 256, kSub2Tiles = 2560;  // one and ten blocks per CU
 
 // Everything a residual launch reads and writes.
 struct ResidualArgs {
@@ -923,17 +924,43 @@ __device__ __forceinline__ ResidualSum residual_walks(int8_t ty, bool g14, Walk 
     return walk(std::true_type{}, std::false_type{});
 }
 
-// Sum over the lanes of a point, by every lane.
-template <int LANES>
+// Sum over the lanes of a point, by every lane; SUB neighbouring threads hold
+// the same sums of a lane.
+template <int LANES, int SUB = 1>
 __device__ __forceinline__ void residual_lane_sum(ResidualSum& R) {
 #pragma unroll
     for (int o = LANES / 2; o > 0; o >>= 1) {
-        R.x += __shfl_xor(R.x, o, 64);
-        R.y += __shfl_xor(R.y, o, 64);
-        R.z += __shfl_xor(R.z, o, 64);
-        R.w += __shfl_xor(R.w, o, 64);
-        R.bad |= __shfl_xor((int)R.bad, o, 64) != 0;
+        R.x += __shfl_xor(R.x, o * SUB, 64);
+        R.y += __shfl_xor(R.y, o * SUB, 64);
+        R.z += __shfl_xor(R.z, o * SUB, 64);
+        R.w += __shfl_xor(R.w, o * SUB, 64);
     }
+#pragma unroll
+    for (int o = LANES * SUB / 2; o > 0; o >>= 1) R.bad |= __shfl_xor((int)R.bad, o, 64) != 0;
+}
+
+// The contributions of SUB neighbouring threads added to R in thread order, by
+// each of them.
+template <int SUB>
+__device__ __forceinline__ void add_in_turn(ResidualSum& R, const ResidualSum& c) {
+    static_assert(SUB == 2 || SUB == 4);
+    auto turn = [&](auto ctrl) {
+        constexpr int C = decltype(ctrl)::value;
+        R.x += dpp<C>(c.x);
+        R.y += dpp<C>(c.y);
+        R.z += dpp<C>(c.z);
+        R.w += dpp<C>(c.w);
+    };
+    if constexpr (SUB == 2) {
+        turn(std::integral_constant<int, 0xA0>{});  // quad_perm 0 0 2 2
+        turn(std::integral_constant<int, 0xF5>{});  // 1 1 3 3
+    } else {
+        turn(std::integral_constant<int, 0x00>{});
+        turn(std::integral_constant<int, 0x55>{});
+        turn(std::integral_constant<int, 0xAA>{});
+        turn(std::integral_constant<int, 0xFF>{});
+    }
+    R.bad |= c.bad;
 }
 
 // ---------------------------------------------------------------------------
@@ -1231,19 +1258,21 @@ __global__ void __launch_bounds__(kBlock) k_residual(ResidualArgs A) {
 // position, q and derivatives of the tile's listed points once (112 bytes
 // each, about 2.5 listed points per point) and every pair reads its neighbour
 // there.  S is the stride of the staged arrays, at least the longest list of
-// the cloud.  The lanes' sums meet in LDS, and the first wavefront finishes
-// the tile's points, one per lane.  The arithmetic and the order of the sums
-// are those of k_residual.
+// the cloud.  SUB neighbouring threads form one lane: they evaluate the next SUB
+// pairs of its walk together and add them in the walk's order.  The lanes' sums
+// meet in LDS, and the first wavefront finishes the tile's points, one per lane.
+// The arithmetic and the order of the sums are those of k_residual.
 // Bound by vector instruction issue: about 260 per pair after sharing the two
 // directions' work (end_sum), 430 before.  2,621,440 points, two lanes per
 // point: 854 us with separate fluxes per direction, 665 us now (FP64); a bound
 // of four wavefronts per SIMD spills 56 bytes and takes 1,055 us.
-template <bool MIXED, int LANES, int S>
-__global__ void __launch_bounds__(kQTile * LANES) k_residual_tiled(ResidualArgs A) {
+template <bool MIXED, int LANES, int S, int SUB>
+__global__ void __launch_bounds__(kQTile * LANES * SUB) k_residual_tiled(ResidualArgs A) {
     __shared__ D2 s_nb[7 * S];  // (x, y), q, q_x, q_y in pairs of components
     __shared__ D2 s_coef[4 * kQTile];
     const int tile = xcd_block(blockIdx.x, gridDim.x);
-    const int pt = threadIdx.x / LANES, lane = threadIdx.x % LANES;
+    constexpr int kThreads = kQTile * LANES * SUB, kStep = LANES * SUB;
+    const int pt = threadIdx.x / kStep, sub = threadIdx.x % SUB, lane = threadIdx.x / SUB % LANES;
     const int64_t p = A.tile_pts[(int64_t)tile * kQTile + pt];
     const double inv_gm1 = 1.0 / (A.gamma - 1.0);
     const bool g14 = A.gamma == 1.4;
@@ -1262,14 +1291,15 @@ __global__ void __launch_bounds__(kQTile * LANES) k_residual_tiled(ResidualArgs 
         gy0 = A.qy[p];
         eb = A.off[p] + lane;
         e1 = A.off[p + 1];
-        for (int k = lane; k < 4; k += LANES) s_coef[k * kQTile + pt] = A.geom[p].split[k];
+        for (int k = threadIdx.x % kStep; k < 4; k += kStep)
+            s_coef[k * kQTile + pt] = A.geom[p].split[k];
     }
     // a pointer of its own, so that the loop holds it and not its neighbours among the arguments
     auto* lnbr = (const __attribute__((address_space(1))) uint16_t*)A.lnbr;
     asm volatile("" : "+s"(lnbr));
-    int li = eb < e1 ? lnbr[eb] : 0;
+    int li = eb < e1 ? lnbr[min(eb + LANES * sub, e1 - 1)] : 0;
     const int32_t h0 = A.tile_off[tile], nh = A.tile_off[tile + 1] - h0;
-    for (int32_t k = threadIdx.x; k < nh; k += kQTile * LANES) {
+    for (int32_t k = threadIdx.x; k < nh; k += kThreads) {
         const int32_t i = A.tile_idx[h0 + k];
         const D4 a = A.q[i], b = A.qx[i], c = A.qy[i];
         s_nb[k] = A.xy[i];
@@ -1288,29 +1318,37 @@ __global__ void __launch_bounds__(kQTile * LANES) k_residual_tiled(ResidualArgs 
             ResidualSum R{};
             constexpr bool FRAME = decltype(frame)::value, G14 = decltype(is14)::value;
             const D2 t = FRAME ? A.frame[p] : D2{1.0, 0.0};
-            for (int32_t e = eb; e < e1; e += LANES) {
+            for (int32_t e = eb; e < e1; e += kStep) {
                 const D2 r = s_nb[li], qa = s_nb[S + li], qb = s_nb[2 * S + li];
                 const D2 xa = s_nb[3 * S + li], xb = s_nb[4 * S + li];
                 const D2 ya = s_nb[5 * S + li], yb = s_nb[6 * S + li];
-                li = lnbr[min(e + LANES, e1 - 1)];  // the next entry's position
+                li = lnbr[min(e + kStep + LANES * sub, e1 - 1)];  // the next entry's position
                 const double dx = r.x - r0.x, dy = r.y - r0.y;
                 const double hx = -0.5 * dx, hy = -0.5 * dy;
                 const D4 qti = reconstruct({qa.x, qa.y, qb.x, qb.y}, {xa.x, xa.y, xb.x, xb.y},
                                            {ya.x, ya.y, yb.x, yb.y}, hx, hy);
                 const D4 qt0 = reconstruct(q0, gx0, gy0, hx, hy);
-                pair_add<FRAME, G14>(dx, dy, qti, qt0, t, ty, coef, kQTile, inv_gm1, lead, R);
+                if constexpr (SUB == 1) {
+                    pair_add<FRAME, G14>(dx, dy, qti, qt0, t, ty, coef, kQTile, inv_gm1, lead, R);
+                } else {
+                    ResidualSum one{};
+                    if (e + LANES * sub < e1)
+                        pair_add<FRAME, G14>(dx, dy, qti, qt0, t, ty, coef, kQTile, inv_gm1, lead,
+                                             one);
+                    add_in_turn<SUB>(R, one);
+                }
             }
             return R;
         });
     }
-    residual_lane_sum<LANES>(sum);
+    residual_lane_sum<LANES, SUB>(sum);
     if (LANES > 1) {
         // hand the sums to the first wavefront through the staging area
         __syncthreads();
         double* s_R = reinterpret_cast<double*>(s_nb);
         int32_t* s_bad = reinterpret_cast<int32_t*>(s_nb + 2 * kQTile);
         int32_t* s_p = s_bad + kQTile;
-        if (lane == 0) {
+        if (threadIdx.x % kStep == 0) {
             s_R[pt] = sum.x;
             s_R[kQTile + pt] = sum.y;
             s_R[2 * kQTile + pt] = sum.z;
@@ -2011,16 +2049,38 @@ static void residual_lanes(State& s, bool in_step) {
                          s.prm.variant, s.prm.jvp_mode, s.dU, s.dUf,
                          s.Rs,       c.colour,    in_step && fused_first_colour(s),
                          s.prm.farfield, s.vinf};
-    // Tiles pay once there is a block for every CU: below, a launch lasts as
-    // long as one block, and the staging and its barriers lengthen that (FP64,
-    // 6,400 points: 18.5 us gathered, 23.5 us tiled; 40,250 points: 28.5 and
-    // 26.8; 2,621,440 points: 712 and 665).  Both forms give the same bits.
-    if (s.qgrad_tiled && c.ntile >= kResidualMinTiles && c.tile_hmax <= kTileStride)
-        hipLaunchKernelGGL((k_residual_tiled<MIXED, LANES, kTileStride>), dim3((unsigned)c.ntile),
-                           dim3(kQTile * LANES), 0, s.stream, A);
-    else
+    // Few tiles leave a launch as long as one lane's walk: four threads to a
+    // lane up to a block for every CU, two up to ten, one beyond, where the
+    // threads that wait for each other's turn cost more than they bring (FP64,
+    // one / two / four threads: 1,024 points 16 / 12 / 11 us, 16,384 points 21 /
+    // 13 / 12, 40,250 points 24 / 20 / 27, 163,840 points 57 / 55 / 81, 640,000
+    // points 169 / 189 / 322).  With lanes asked for, and small clouds without
+    // tiles, neighbours are gathered: 1,024 points 16 us, 6,400 points 16, 40,250
+    // points 26, 2,621,440 points 712 against 640.  All forms give the same bits.
+    if (s.qgrad_tiled && c.tile_hmax <= kTileStride && c.ntile > 0) {
+        const dim3 g((unsigned)c.ntile);
+        if constexpr (LANES == 2) {
+            if (!s.prm.residual_lanes && c.ntile <= kSub4Tiles) {
+                hipLaunchKernelGGL((k_residual_tiled<MIXED, 2, kTileStride, 4>), g, dim3(kQTile * 8),
+                                   0, s.stream, A);
+                return;
+            }
+            if (!s.prm.residual_lanes && c.ntile <= kSub2Tiles) {
+                hipLaunchKernelGGL((k_residual_tiled<MIXED, 2, kTileStride, 2>), g, dim3(kQTile * 4),
+                                   0, s.stream, A);
+                return;
+            }
+        }
+        if (c.ntile >= kResidualMinTiles) {
+            hipLaunchKernelGGL((k_residual_tiled<MIXED, LANES, kTileStride, 1>), g,
+                               dim3(kQTile * LANES), 0, s.stream, A);
+            return;
+        }
+    }
+    {
         hipLaunchKernelGGL((k_residual<MIXED, LANES>), dim3(grid_for(c.n * LANES)), dim3(kBlock), 0,
                            s.stream, A);
+    }
 }
 
 template <bool MIXED>

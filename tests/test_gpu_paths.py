@@ -218,3 +218,22 @@ def test_host_fields_by_chunks(lk, nx, ny):
     assert np.array_equal(b.get_U(1), U)
     assert np.array_equal(b.get_U(0), b.get_U(2))
     b.close()
+
+
+@pytest.mark.parametrize("nw,nk", [(20, 6), (160, 40), (160, 110)])
+@pytest.mark.parametrize("kw", [dict(), dict(precision=1), dict(farfield=1, gamma=1.3)])
+def test_residual_threads_per_lane_bitwise(lk, nw, nk, kw):
+    """Four threads to a lane (2 and 100 tiles), two (275 and more) and the
+    forms that two asked-for lanes take (gathered, tiled): the same bits."""
+    c = lk.Cloud(cg.ogrid(nw, nk, jitter_p=0.03, seed=4))
+    out = []
+    for lanes in (0, 2):
+        st = lk.State(c, 0.7, 2.0, lk.default_params(cfl=20.0, limiter=1, residual_lanes=lanes, **kw))
+        for _ in range(3):
+            st.step(want_res=False)
+        out.append((st.residual(), st.get_U()))
+        st.close()
+    (a, ra), ua = out[0]
+    (b, rb), ub = out[1]
+    assert np.isfinite(a).all() and ra == rb
+    assert np.array_equal(a, b) and np.array_equal(ua, ub)
