@@ -1132,22 +1132,12 @@ int lskum_residual_noalloc(const lskum_cloud* cl, double mach, double aoa_deg,
     if ((size_t)(cv.p - base) > kScratchBytes)
         return fail(LSKUM_ERR_ARG, "cloud too large for the allocation-free residual");
     const double a = aoa_deg * kPi / 180.0;
-    // per-condition values by fill kernels (no memset and no host copy)
-    HIPCHK(lskum::launch_fill(s.cfl, nc, s.prm.cfl, s.stream));
-    HIPCHK(lskum::launch_fill(s.tol_abs, nc, 0.0, s.stream));
-    for (int k = 0; k < nc; ++k) {
-        HIPCHK(lskum::launch_fill(s.vinf + 2 * k, 1, mach * std::cos(a), s.stream));
-        HIPCHK(lskum::launch_fill(s.vinf + 2 * k + 1, 1, mach * std::sin(a), s.stream));
-    }
-    HIPCHK(lskum::launch_clear_flags(s.flags, s.stream));
-    HIPCHK(lskum::launch_reset_components(s));
-    HIPCHK(lskum::launch_soa_to_aos(U, s.U, n, s.stream));
-    HIPCHK(lskum::launch_q_from_U(s));
+    // per-condition values by a kernel (no memset and no host copy)
+    HIPCHK(lskum::launch_scratch_begin(s, mach * std::cos(a), mach * std::sin(a), U));
     HIPCHK(lskum::launch_q_derivatives(s));
     HIPCHK(lskum::launch_residual(s, 0));
     HIPCHK(lskum::launch_norm(s, 0));
-    if (R) HIPCHK(lskum::launch_aos_to_soa(s.R, R, n, s.stream));
-    HIPCHK(lskum::launch_residual_out(s.res_hist, s.flags, res, s.stream));
+    HIPCHK(lskum::launch_residual_out(s, R, res));
     return LSKUM_OK;
 }
 
