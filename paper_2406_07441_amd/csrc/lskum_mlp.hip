@@ -622,12 +622,14 @@ __global__ void __launch_bounds__(256) k_grad_sum(int nparts, const float* __res
     }
 }
 
-// Squared distance from c to the nearest wall point of component k, by runs of
-// kWallRun wall points (consecutive along the contour, so a run is compact):
-// the run whose box is nearest is searched first, then only runs whose box is
-// nearer than the best point found.  The box bound is lowered by far more than
-// its rounding, so no point that could be the nearest is passed over.  Runs,
-// boxes and points are read at wave-uniform addresses (scalar loads).
+// Squared distance from c to the nearest wall point, by runs of kWallRun wall
+// points (consecutive along the contour, so a run is compact).  The wavefront's
+// points share a bounding box.  Lane j bounds the distances between the box and
+// run j from both sides; the smallest upper bound rules out most runs at once,
+// its run is searched first, and of the others those that the box and then the
+// lane's own best point do not rule out.  Bounds are moved apart by far more than
+// their rounding, so no point that could be the nearest is passed over.  Runs,
+// boxes and points to search are read at wave-uniform addresses (scalar loads).
 typedef double f64x2 __attribute__((ext_vector_type(2)));
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 typedef const __attribute__((address_space(4))) f64x2 ConstD2;  // read by scalar loads
@@ -659,42 +661,69 @@ __device__ __forceinline__ double run_min(double d2, int r, ConstD2* wall_xy,
     return d2;
 }
 
-__device__ __forceinline__ double nearest_wall(int r0, int r1, const D2& c,
-                                               ConstD2* wall_xy,
-                                               ConstD4* wall_box) {
-    double lb = 1e300, d2 = 1e300;
-    int best = -1;
-#pragma unroll 8
-    for (int r = r0; r < r1; ++r) {
-        const double b = box_bound(wall_box[r], c);
-        if (b < lb) {
-            lb = b;
-            best = r;
+// Smallest (largest) value of the wavefront in fp32, rounded down (up).
+template <bool MAX>
+__device__ __forceinline__ float wave_extreme(double x) {
+    float v = MAX ? __double2float_ru(x) : __double2float_rd(x);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        const float w = __shfl_xor(v, o, 64);
+        v = MAX ? fmaxf(v, w) : fminf(v, w);
+    }
+    return v;
+}
+
+// Called by whole wavefronts; `mine` lanes ask, runs r0 .. r1 - 1.
+__device__ __forceinline__ double nearest_wall(bool mine, int r0, int r1, const D2& c,
+                                               const D4* wall_box, ConstD2* run_xy,
+                                               ConstD4* run_box) {
+    const int lane = threadIdx.x & 63;
+    const double x0 = wave_extreme<false>(mine ? c.x : HUGE_VAL);
+    const double x1 = wave_extreme<true>(mine ? c.x : -HUGE_VAL);
+    const double y0 = wave_extreme<false>(mine ? c.y : HUGE_VAL);
+    const double y1 = wave_extreme<true>(mine ? c.y : -HUGE_VAL);
+    // bounds of the distances between the box and run b + lane
+    auto bounds = [&](int b, double& lower, double& upper) {
+        const D4 w = wall_box[min(b + lane, r1 - 1)];
+        const double dx = fmax(fmax(w.x - x1, x0 - w.y), 0.0), ex = fmax(w.y - x0, x1 - w.x);
+        const double dy = fmax(fmax(w.z - y1, y0 - w.w), 0.0), ey = fmax(w.w - y0, y1 - w.z);
+        lower = (dx * dx + dy * dy) * (1.0 - 1e-12);
+        upper = (ex * ex + ey * ey) * (1.0 + 1e-12);
+    };
+    double lower, upper;
+    float most = HUGE_VALF;
+    int first = r0;
+    for (int b = r0; b < r1; b += 64) {
+        bounds(b, lower, upper);
+        const float u = wave_extreme<false>(upper);
+        if (u < most) {  // uniform
+            most = u;
+            first = b + __builtin_ctzll(__ballot(__double2float_rd(upper) == u));
         }
     }
-    // a wavefront's points mostly share their nearest run: one pass per
-    // distinct one
-    for (uint64_t todo = __ballot(best >= 0); todo;) {
-        const int r = __builtin_amdgcn_readlane(best, __builtin_ctzll(todo));
-        const int ru = uniform(r);
-        const bool mine = best == r;
-        if (mine) d2 = run_min(d2, ru, wall_xy, c);
-        todo &= ~__ballot(mine);
+    first = uniform(__builtin_amdgcn_readfirstlane(min(first, r1 - 1)));
+    double d2 = run_min(1e300, first, run_xy, c);
+    most = wave_extreme<true>(mine ? d2 : 0.0);
+    for (int b = r0; b < r1; b += 64) {
+        if (r1 - r0 > 64) bounds(b, lower, upper);
+        uint64_t todo = __ballot(lower <= most && b + lane < r1);
+        if (first >= b && first < b + 64) todo &= ~(1ull << (first - b));
+        for (; todo; todo &= todo - 1) {
+            const int r = uniform(__builtin_amdgcn_readfirstlane(b + __builtin_ctzll(todo)));
+            if (box_bound(run_box[r], c) < d2) d2 = run_min(d2, r, run_xy, c);
+        }
     }
-    // of the others, those that some lane's best point does not rule out
-#pragma unroll 8
-    for (int r = r0; r < r1; ++r)
-        if (r != best && box_bound(wall_box[r], c) < d2) d2 = run_min(d2, r, wall_xy, c);
     return d2;
 }
 
 // Features of a point: position squashed into the unit disc about mid-chord,
 // distance to the nearest wall point of its own cloud, Mach number and angle
 // of attack recovered from the free-stream velocity.
-// Bound by the search's vector instructions (two passes over the runs' boxes,
-// a few runs searched): 2,621,440 points about 2,560 wall points 343 us, 640,000
-// about 1,280 88 us with the call, against 3,725 and 580 us when every point
-// visited every wall point.
+// Bound by the search's vector instructions (about 20 boxes looked at and 5 runs
+// searched by a wavefront around 1,280 wall points): 2,621,440 points about 2,560
+// wall points 197 us, 640,000 about 1,280 62 us with the call.  Every point
+// visiting every wall point: 3,725 and 580 us; every point visiting every box:
+// 343 and 82 us.
 __global__ void __launch_bounds__(256) k_features(int64_t p0, int64_t m, const D2* __restrict__ xy,
                                                   const int32_t* __restrict__ comp,
                                                   const D2* __restrict__ wall_xy,
@@ -704,20 +733,24 @@ __global__ void __launch_bounds__(256) k_features(int64_t p0, int64_t m, const D
                                                   const D4* __restrict__ U, double gamma,
                                                   float* __restrict__ X, float* __restrict__ T) {
     const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= m) return;
-    const int64_t p = p0 + r;
+    const int64_t p = p0 + min(r, m - 1);  // whole wavefronts search
     const int k = comp ? comp[p] : 0;
     const D2 c = xy[p];
-    // wave-uniform component (a wavefront may straddle two or more)
+    // one component at a time (a wavefront may straddle two or more)
     double d2 = 1e300;
-    for (bool done = false; !done;) {
-        const int ku = __builtin_amdgcn_readfirstlane(k), kr = uniform(ku);
-        if (k == ku) {
-            ConstI32* ro = (ConstI32*)run_off;
-            d2 = nearest_wall(ro[kr], ro[kr + 1], c, (ConstD2*)wall_xy, (ConstD4*)wall_box);
-            done = true;
+    for (uint64_t todo = __ballot(true); todo;) {
+        const int ku = __builtin_amdgcn_readlane(k, __builtin_ctzll(todo)), kr = uniform(ku);
+        const bool mine = k == ku;
+        ConstI32* ro = (ConstI32*)run_off;
+        const int r0 = ro[kr], r1 = ro[kr + 1];
+        if (r1 > r0) {
+            const double t = nearest_wall(mine, r0, r1, c, wall_box, (ConstD2*)wall_xy,
+                                          (ConstD4*)wall_box);
+            if (mine) d2 = t;
         }
+        todo &= ~__ballot(mine);
     }
+    if (r >= m) return;
     const double d = run_off[k + 1] > run_off[k] ? sqrt(d2) : 1e3;
     const double ex = c.x - 0.5, rc = sqrt(ex * ex + c.y * c.y);
     const double u1 = vinf[2 * k], u2 = vinf[2 * k + 1];

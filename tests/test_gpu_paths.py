@@ -237,3 +237,15 @@ def test_residual_threads_per_lane_bitwise(lk, nw, nk, kw):
     (b, rb), ub = out[1]
     assert np.isfinite(a).all() and ra == rb
     assert np.array_equal(a, b) and np.array_equal(ua, ub)
+
+
+@pytest.mark.parametrize("nw", [64, 2048, 2100])
+def test_features_by_wall_runs(lk, nw):
+    """Walls of 2, 64 and 66 runs of 32 points (a wavefront bounds 64 runs at a
+    time), points near and far, a last wavefront that is not full."""
+    from oracle import mlp as OM
+    c = cg.ogrid(nw, 7, r=2.5, jitter_p=0.03, seed=5)
+    st = lk.State(lk.Cloud(c), 0.7, 1.0, lk.default_params())
+    X = st.features().cpu().numpy()
+    assert np.abs(X - OM.features(c.x, c.y, c.type, 0.7, 1.0)).max() <= 1e-6
+    st.close()
