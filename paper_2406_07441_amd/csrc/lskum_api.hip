@@ -421,14 +421,17 @@ lskum::Params to_params(const lskum_params* p) {
 // and 2 for the compute-bound residual (measured best on the 163,840-point
 // transonic cloud, FP64 and mixed).  Up to kSmallSweep points a colour phase
 // leaves most of the chip idle and lasts as long as one lane's walk: 16 lanes
-// then (the sums of 8 lanes bit for bit while no list exceeds 32 entries, so
-// the choice may depend on how many conditions share a launch).  Iteration at
-// 6,400 points with 8 and 16 lanes: 116.5 and 110.4 us; 40,250: 142.5 and
-// 141.6; 80,000: 173 and 176; 163,840: 227 and 229.
-constexpr int64_t kSmallSweep = 50000;
+// then, and 32, one entry each, up to kTinySweep (the sums of 8 lanes bit for
+// bit while no list exceeds 32 entries, so the choice may depend on how many
+// conditions share a launch).  Iteration at 6,400 points with 8 and 16 lanes:
+// 116.5 and 110.4 us; 40,250: 142.5 and 141.6; 80,000: 173 and 176; 163,840: 227
+// and 229.  With 16 and 32: 1,024 points 100.6 and 96.1, 6,400 points 101.2 and
+// 95.8, 16,384 points 119.8 and 112.4, 25,600 points 114 and 114, 40,250 points
+// (mixed) 114 and 118.
+constexpr int64_t kSmallSweep = 50000, kTinySweep = 20000;
 void apply_lanes(lskum::State& s) {
     const bool small = s.cloud->n <= kSmallSweep && s.cloud->max_list <= 32;
-    s.sweep_lanes = s.prm.sweep_lanes ? s.prm.sweep_lanes : (small ? 16 : 8);
+    s.sweep_lanes = s.prm.sweep_lanes ? s.prm.sweep_lanes : (small ? (s.cloud->n <= kTinySweep ? 32 : 16) : 8);
     s.residual_lanes = s.prm.residual_lanes ? s.prm.residual_lanes : 2;
     s.qgrad_tiled = s.prm.qgrad_lanes == 0;
     s.qgrad_lanes = s.prm.qgrad_lanes ? s.prm.qgrad_lanes : 4;

@@ -289,7 +289,8 @@ __device__ __forceinline__ double dpp(double v) {
 // gets the sum of value l % 4.  Sixteen lanes come as (first, rest), a lane's
 // first entry and the sum of its others, and add up in the order of eight
 // lanes: entry l, then l + 8, l + 16, l + 24.  Lists of up to 32 entries thus
-// give the same bits with either.
+// give the same bits with either, and with 32 lanes, where the second half's
+// entries first join the first half's lanes (from_second_half).
 template <int LANES, class T>
 __device__ __forceinline__ T scatter_sum(T a[4], const T rest[4], int lane) {
     if constexpr (LANES == 16) {
@@ -311,6 +312,19 @@ __device__ __forceinline__ T scatter_sum(T a[4], const T rest[4], int lane) {
     x0 += dpp<kDppXor2>(hi ? a[0] : a[2]);
     x1 += dpp<kDppXor2>(hi ? a[1] : a[3]);
     return (odd ? x1 : x0) + dpp<kDppXor1>(odd ? x0 : x1);
+}
+
+// For the first 16 of 32 lanes, the value that lane + 16 holds (rows of 16
+// lanes change places two by two).
+__device__ __forceinline__ int from_second_half(int v) {
+    return __builtin_amdgcn_permlane16_swap(v, v, false, false)[1];
+}
+__device__ __forceinline__ float from_second_half(float v) {
+    return __int_as_float(from_second_half(__float_as_int(v)));
+}
+__device__ __forceinline__ double from_second_half(double v) {
+    return __hiloint2double(from_second_half(__double2hiint(v)),
+                            from_second_half(__double2loint(v)));
 }
 
 // ---------------------------------------------------------------------------
@@ -1264,7 +1278,7 @@ __global__ void __launch_bounds__(kBlock) k_residual(ResidualArgs A) {
 // The arithmetic and the order of the sums are those of k_residual.
 // Bound by vector instruction issue: about 260 per pair after sharing the two
 // directions' work (end_sum), 430 before.  2,621,440 points, two lanes per
-// point: 854 us with separate fluxes per direction, 665 us now (FP64); a bound
+// point: 854 us with separate fluxes per direction, 640 us now (FP64); a bound
 // of four wavefronts per SIMD spills 56 bytes and takes 1,055 us.
 template <bool MIXED, int LANES, int S, int SUB>
 __global__ void __launch_bounds__(kQTile * LANES * SUB) k_residual_tiled(ResidualArgs A) {
@@ -1648,7 +1662,7 @@ __device__ __forceinline__ void sweep_entry(uint8_t cd, const D2& t, const W2<T>
 // 163,840 points 78 and 66 us; flux differences there 111 and 78 us; 640,000
 // points in mixed precision 145 and 119 us.
 template <class T, bool FWD, int MODE, int LANES>
-__global__ void __launch_bounds__(kBlock, MODE == 1 || LANES == 16 ? 4 : 5) k_sweep(
+__global__ void __launch_bounds__(kBlock, MODE == 1 || LANES >= 16 ? 4 : 5) k_sweep(
     int32_t start, int32_t count, const int32_t* __restrict__ col_perm,
     const D2* __restrict__ frame, const int8_t* __restrict__ type,
     const int32_t* __restrict__ loff, const int32_t* __restrict__ lidx,
@@ -1723,8 +1737,16 @@ __global__ void __launch_bounds__(kBlock, MODE == 1 || LANES == 16 ? 4 : 5) k_sw
         i = in;
         e = en;
     }
+    // lists of at most 32 entries: one each (in the loop's form all the same; cut
+    // down to one pass, the compiler lays out more code, and a phase takes longer)
+    if constexpr (LANES == 32)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            first[c] = acc[c];
+            acc[c] = from_second_half(acc[c]);
+        }
     if constexpr (SCATTER) {
-        const T sum = LANES == 16 ? scatter_sum<LANES>(first, acc, lane)
+        const T sum = LANES >= 16 ? scatter_sum<16>(first, acc, lane & 15)
                                   : scatter_sum<LANES>(acc, first, lane);
         T out = FWD ? -(own + sum) / dg : own - sum / dg;
         if (ty == kOuter && !farfield) {
@@ -2179,6 +2201,7 @@ static void sweep_t(State& s, bool forward, const Vec4<T>* jv0, const Vec4<T>* j
         case 2: sweep_lanes<T, MODE, 2>(s, forward, jv0, jv2, Dg, dU); break;
         case 8: sweep_lanes<T, MODE, 8>(s, forward, jv0, jv2, Dg, dU); break;
         case 16: sweep_lanes<T, MODE, 16>(s, forward, jv0, jv2, Dg, dU); break;
+        case 32: sweep_lanes<T, MODE, 32>(s, forward, jv0, jv2, Dg, dU); break;
         default: sweep_lanes<T, MODE, 4>(s, forward, jv0, jv2, Dg, dU); break;
     }
 }

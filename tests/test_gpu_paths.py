@@ -249,3 +249,21 @@ def test_features_by_wall_runs(lk, nw):
     X = st.features().cpu().numpy()
     assert np.abs(X - OM.features(c.x, c.y, c.type, 0.7, 1.0)).max() <= 1e-6
     st.close()
+
+
+@pytest.mark.parametrize("kw", [dict(), dict(precision=1), dict(jvp_mode=1), dict(farfield=1),
+                                dict(variant=1)])
+@pytest.mark.parametrize("nw,nk", [(16, 5), (160, 40), (160, 126)])
+def test_sweep_lanes_of_small_clouds_bitwise(lk, nw, nk, kw):
+    """Thirty-two lanes per point (80 and 6,400 points), sixteen (20,160) and the
+    eight that are asked for: the same bits."""
+    c = lk.Cloud(cg.ogrid(nw, nk, jitter_p=0.03, seed=6))
+    out = []
+    for lanes in (0, 8):
+        st = lk.State(c, 0.6, 2.0, lk.default_params(cfl=20.0, limiter=1, sweep_lanes=lanes, **kw))
+        for _ in range(3):
+            st.step(want_res=False)
+        out.append((st.get_U(), st.get_dU()))
+        st.close()
+    assert np.isfinite(out[0][0]).all() and np.any(out[0][1])
+    assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
