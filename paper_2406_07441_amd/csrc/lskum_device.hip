@@ -787,9 +787,13 @@ __device__ __forceinline__ double flip_by(double v, double s) {
                                           (~(uint64_t)__double_as_longlong(s) & sign)));
 }
 
+// erf and exp of S; the code of the unit range lies in the path's order and the
+// outer range's beside it (as the frame and general-gamma paths do elsewhere):
+// 2,621,440 points, residual 637 us with them in turn, 617 so, and 1% less for an
+// iteration at M 1.2 too.
 __device__ __forceinline__ void unit_or_outer(double S, double t, const PolyLead& lead, double& er,
                                               double& g) {  // g scaled by e^(1/2)
-    if (t < 1.0) {
+    if (__builtin_expect(t < 1.0, 1)) {
         erf_exp_unit(S, t, lead, er, g);
     } else {  // fast flow (or a non-physical state)
         erf_exp_outer(S, t, er, g);
@@ -930,8 +934,8 @@ __device__ __forceinline__ void pair_add(double dx, double dy, const D4& qti, co
 // registers for frames) and for gamma = 1.4: W<FRAME, G14>.
 template <class Walk>
 __device__ __forceinline__ ResidualSum residual_walks(int8_t ty, bool g14, Walk walk) {
-    if (g14) {
-        if (ty == kInterior) return walk(std::false_type{}, std::true_type{});
+    if (__builtin_expect(g14, 1)) {
+        if (__builtin_expect(ty == kInterior, 1)) return walk(std::false_type{}, std::true_type{});
         return walk(std::true_type{}, std::true_type{});
     }
     if (ty == kInterior) return walk(std::false_type{}, std::false_type{});
@@ -1278,7 +1282,7 @@ __global__ void __launch_bounds__(kBlock) k_residual(ResidualArgs A) {
 // The arithmetic and the order of the sums are those of k_residual.
 // Bound by vector instruction issue: about 260 per pair after sharing the two
 // directions' work (end_sum), 430 before.  2,621,440 points, two lanes per
-// point: 854 us with separate fluxes per direction, 640 us now (FP64); a bound
+// point: 854 us with separate fluxes per direction, 617 us now (FP64); a bound
 // of four wavefronts per SIMD spills 56 bytes and takes 1,055 us.
 template <bool MIXED, int LANES, int S, int SUB>
 __global__ void __launch_bounds__(kQTile * LANES * SUB) k_residual_tiled(ResidualArgs A) {
@@ -1719,7 +1723,7 @@ __global__ void __launch_bounds__(kBlock, MODE == 1 || LANES >= 16 ? 4 : 5) k_sw
         const uint8_t cdn = lcode[ec];
         const W2<T> wn = lw[ec];
         const int32_t in = lidx[ec];
-        if (cd & kSwWall)
+        if (__builtin_expect(cd & kSwWall, 0))
             sweep_entry<true, T, MODE>(cd, frame[p], w, i, jv0, jv2, U, dU, gm1, inv_gm1, lead, acc);
         else
             sweep_entry<false, T, MODE>(cd, D2{1.0, 0.0}, w, i, jv0, jv2, U, dU, gm1, inv_gm1, lead,
@@ -2078,7 +2082,7 @@ static void residual_lanes(State& s, bool in_step) {
     // 13 / 12, 40,250 points 24 / 20 / 27, 163,840 points 57 / 55 / 81, 640,000
     // points 169 / 189 / 322).  With lanes asked for, and small clouds without
     // tiles, neighbours are gathered: 1,024 points 16 us, 6,400 points 16, 40,250
-    // points 26, 2,621,440 points 712 against 640.  All forms give the same bits.
+    // points 26, 2,621,440 points 712 against 640 (617 since).  All forms give the same bits.
     if (s.qgrad_tiled && c.tile_hmax <= kTileStride && c.ntile > 0) {
         const dim3 g((unsigned)c.ntile);
         if constexpr (LANES == 2) {
