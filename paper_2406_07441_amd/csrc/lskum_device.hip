@@ -2176,13 +2176,23 @@ static const W2<T>* list_weights(const D2* w, const F2* wf) {
     else return w;
 }
 
+constexpr int64_t kThinPhase = 160 * 1024;  // threads: two or three wavefronts on every SIMD
+
 template <class T, int MODE, int LANES>
 static void sweep_lanes(State& s, bool forward, const Vec4<T>* jv0, const Vec4<T>* jv2,
                         const T* Dg, Vec4<T>* dU) {
     const Cloud& c = *s.cloud;
     for (const auto& [start, cnt] : sweep_phases(s, forward)) {
         if (!cnt) continue;
-        const dim3 g(grid_for((int64_t)cnt * LANES)), b(kBlock);
+        // one wavefront to a block while a phase has two or three for a SIMD at most:
+        // they spread over the CUs, where four to a block wait on one another's gathers
+        // (iteration with 256 and 64 threads: 1,024 points 95.2 and 89.9 us, 80,000
+        // points 158.5 and 154.1, 163,840 points, 146,000 threads, 209.7 and 207.6;
+        // 215,040 points, 191,000 threads, 210.4 and 211.7; 360,000 points in mixed
+        // precision 281 and 285)
+        const int64_t threads = (int64_t)cnt * LANES;
+        const int block = threads <= kThinPhase ? 64 : kBlock;
+        const dim3 g((unsigned)((threads + block - 1) / block)), b(block);
         if (forward)
             hipLaunchKernelGGL((k_sweep<T, true, MODE, LANES>), g, b, 0, s.stream, start, cnt,
                                c.col_perm, c.frame, c.type, c.lo_off, c.lo_idx,
