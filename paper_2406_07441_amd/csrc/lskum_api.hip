@@ -362,6 +362,13 @@ int upload_cloud(lskum::Cloud& c) {
     return LSKUM_OK;
 }
 
+void free_slots(lskum::HostSlots& h) {
+    (void)hipHostFree(h.mem);
+    for (hipEvent_t ev : h.ev)
+        if (ev) (void)hipEventDestroy(ev);
+    h = lskum::HostSlots{};
+}
+
 void free_state(lskum::State& s) {
     if (s.graph) (void)hipGraphExecDestroy(s.graph);
     if (s.have_events)
@@ -372,9 +379,9 @@ void free_state(lskum::State& s) {
                     s.res_hist, s.flags, s.active, s.status, s.iters, s.res_last, s.tol_abs, s.cfl,
                     s.vinf};
     for (void* p : ptrs) (void)hipFree(p);
-    if (s.slots) (void)hipHostFree(s.slots);
-    for (hipEvent_t ev : s.slot_ev)
-        if (ev) (void)hipEventDestroy(ev);
+    if (s.slots)
+        for (int k = 0; k < s.slots->n_idle; ++k) free_slots(s.slots->idle[k]);
+    delete s.slots;
     if (s.own_stream && s.stream) (void)hipStreamDestroy(s.stream);
     s = lskum::State{};
 }
@@ -479,16 +486,57 @@ int set_tolerances(lskum::State& s, bool on) {
 // One megabyte a slot: the link moves one in 20 us, five times a launch's cost.
 constexpr int64_t kSlotPoints = 1 << 15;
 
-int need_slots(lskum::State& s) {
-    if (s.slots) return LSKUM_OK;
-    const int64_t pts = std::min(s.cloud->n, kSlotPoints);
-    for (hipEvent_t& ev : s.slot_ev)
-        if (!ev)
-            HIPCHK(hipEventCreateWithFlags(&ev, hipEventDisableTiming | hipEventReleaseToSystem));
-    HIPCHK(hipHostMalloc((void**)&s.slots, lskum::kSlots * pts * sizeof(lskum::D4),
-                         hipHostMallocCoherent));
-    return LSKUM_OK;
-}
+// A call's own set of slots, returned at the end of its scope; work on the
+// stream that may still touch them is waited for first.
+class SlotLease {
+public:
+    explicit SlotLease(lskum::State& s) : s_(s) {}
+    SlotLease(const SlotLease&) = delete;
+    SlotLease& operator=(const SlotLease&) = delete;
+    ~SlotLease() {
+        if (!h_.mem) return;
+        if (busy) (void)hipStreamSynchronize(s_.stream);
+        {
+            std::lock_guard<std::mutex> lk(s_.slots->mu);
+            if (s_.slots->n_idle < lskum::kIdleSets) {
+                s_.slots->idle[s_.slots->n_idle++] = h_;
+                return;
+            }
+        }
+        free_slots(h_);
+    }
+    int take() {
+        {
+            std::lock_guard<std::mutex> lk(s_.slots->mu);
+            if (s_.slots->n_idle) {
+                h_ = s_.slots->idle[--s_.slots->n_idle];
+                return LSKUM_OK;
+            }
+        }
+        lskum::HostSlots h;
+        hipError_t e = hipSuccess;
+        for (hipEvent_t& ev : h.ev)
+            if (e == hipSuccess)
+                e = hipEventCreateWithFlags(&ev, hipEventDisableTiming | hipEventReleaseToSystem);
+        if (e == hipSuccess)
+            e = hipHostMalloc((void**)&h.mem, lskum::kSlots * points() * sizeof(lskum::D4),
+                              hipHostMallocCoherent);
+        if (e != hipSuccess) {
+            free_slots(h);
+            return hip_fail(e, "pinned memory for host fields");
+        }
+        h_ = h;
+        return LSKUM_OK;
+    }
+    int64_t points() const { return std::min(s_.cloud->n, kSlotPoints); }
+    double* slot(int64_t chunk) const { return h_.mem + chunk % lskum::kSlots * 4 * points(); }
+    hipEvent_t event(int64_t chunk) const { return h_.ev[chunk % lskum::kSlots]; }
+    bool busy = false;
+
+private:
+    lskum::State& s_;
+    lskum::HostSlots h_;
+};
 
 template <class V>
 int copy_field_out(lskum::State& s, const V* src, int64_t p0, int64_t n, double* dst,
@@ -504,40 +552,45 @@ int copy_field_out(lskum::State& s, const V* src, int64_t p0, int64_t n, double*
         HIPCHK(hipStreamSynchronize(s.stream));
         return LSKUM_OK;
     }
-    if (int r = need_slots(s)) return r;
-    const int64_t size = std::min(s.cloud->n, kSlotPoints), nchunk = (n + size - 1) / size;
+    SlotLease lease(s);
+    if (int r = lease.take()) return r;
+    lease.busy = true;
+    const int64_t size = lease.points(), nchunk = (n + size - 1) / size;
     for (int64_t k = 0; k < nchunk + lskum::kSlots; ++k) {
         if (const int64_t c = k - lskum::kSlots; c >= 0 && c < nchunk) {  // to the caller
             const int64_t o = c * size, m = std::min(size, n - o);
-            const double* slot = s.slots + c % lskum::kSlots * 4 * size;
-            HIPCHK(hipEventSynchronize(s.slot_ev[c % lskum::kSlots]));
+            HIPCHK(hipEventSynchronize(lease.event(c)));
             for (int v = 0; v < 4; ++v)
-                std::memcpy(dst + v * n + o, slot + v * m, m * sizeof(double));
+                std::memcpy(dst + v * n + o, lease.slot(c) + v * m, m * sizeof(double));
         }
         if (k < nchunk) {
             const int64_t o = k * size, m = std::min(size, n - o);
-            HIPCHK(transpose(o, s.slots + k % lskum::kSlots * 4 * size, m));
-            HIPCHK(hipEventRecord(s.slot_ev[k % lskum::kSlots], s.stream));
+            HIPCHK(transpose(o, lease.slot(k), m));
+            HIPCHK(hipEventRecord(lease.event(k), s.stream));
         }
     }
+    lease.busy = false;
     return LSKUM_OK;
 }
 
-int copy_U_in(lskum::State& s, const double* U, int64_t p0, int64_t n, int on_device) {
+// The device may still be reading the lease's slots on return; a caller that
+// waits for the stream clears lease.busy.
+int copy_U_in(lskum::State& s, const double* U, int64_t p0, int64_t n, int on_device,
+              SlotLease& lease) {
     if (on_device) {
         HIPCHK(lskum::launch_soa_to_aos(U, s.U + p0, n, s.stream));
         return LSKUM_OK;
     }
-    if (int r = need_slots(s)) return r;
-    const int64_t size = std::min(s.cloud->n, kSlotPoints), nchunk = (n + size - 1) / size;
+    if (int r = lease.take()) return r;
+    lease.busy = true;
+    const int64_t size = lease.points(), nchunk = (n + size - 1) / size;
     for (int64_t c = 0; c < nchunk; ++c) {
         const int64_t o = c * size, m = std::min(size, n - o);
-        double* slot = s.slots + c % lskum::kSlots * 4 * size;
-        hipEvent_t ev = s.slot_ev[c % lskum::kSlots];
-        HIPCHK(hipEventSynchronize(ev));  // at once if nothing was recorded
-        for (int v = 0; v < 4; ++v) std::memcpy(slot + v * m, U + v * n + o, m * sizeof(double));
-        HIPCHK(lskum::launch_soa_to_aos(slot, s.U + p0 + o, m, s.stream));
-        HIPCHK(hipEventRecord(ev, s.stream));
+        if (c >= lskum::kSlots) HIPCHK(hipEventSynchronize(lease.event(c)));
+        for (int v = 0; v < 4; ++v)
+            std::memcpy(lease.slot(c) + v * m, U + v * n + o, m * sizeof(double));
+        HIPCHK(lskum::launch_soa_to_aos(lease.slot(c), s.U + p0 + o, m, s.stream));
+        if (c + lskum::kSlots < nchunk) HIPCHK(hipEventRecord(lease.event(c), s.stream));
     }
     return LSKUM_OK;
 }
@@ -560,6 +613,8 @@ int init_state(lskum::State& s, const lskum::Cloud& c, const lskum_params* prm,
         HIPCHK(hipStreamCreateWithFlags(&s.stream, hipStreamNonBlocking));
         s.own_stream = true;
     }
+    s.slots = new (std::nothrow) lskum::SlotPool();
+    if (!s.slots) return fail(LSKUM_ERR_OOM, "host allocation");
     const int64_t n = c.n;
     const int nc = c.ncomp;
     s.res_cap = 4096;
@@ -1020,12 +1075,14 @@ int lskum_state_set_U(lskum_state* so, const double* U, int on_device) {
     if (!so || !U) return fail(LSKUM_ERR_ARG, "NULL argument");
     lskum::State& s = so->s;
     const int64_t n = s.cloud->n;
-    if (int r = copy_U_in(s, U, 0, n, on_device)) return r;
+    SlotLease lease(s);
+    if (int r = copy_U_in(s, U, 0, n, on_device, lease)) return r;
     HIPCHK(lskum::launch_clear_flags(s.flags, s.stream));
     HIPCHK(lskum::launch_q_from_U(s));
     HIPCHK(lskum::clear_increment(s, 0, n));
     int32_t f = 0;
     if (int r = read_flags(s, &f)) return r;
+    lease.busy = false;
     s.have_dU = false;
     if (f) return fail(LSKUM_ERR_NONPHYSICAL, "state has rho <= 0 or p <= 0");
     return LSKUM_OK;
@@ -1403,12 +1460,14 @@ int lskum_batch_set_U(lskum_batch* b, int32_t cond, const double* U, int on_devi
     if (cond < 0 || cond >= b->c.ncomp) return fail(LSKUM_ERR_ARG, "condition out of range");
     lskum::State& s = b->s;
     const int64_t p0 = b->c.h_comp_off[cond], n = b->c.h_comp_off[cond + 1] - p0;
-    if (int r = copy_U_in(s, U, p0, n, on_device)) return r;
+    SlotLease lease(s);
+    if (int r = copy_U_in(s, U, p0, n, on_device, lease)) return r;
     HIPCHK(lskum::launch_clear_flags(s.flags, s.stream));
     HIPCHK(lskum::launch_q_from_U(s));
     HIPCHK(lskum::clear_increment(s, p0, n));
     int32_t f = 0;
     if (int r = read_flags(s, &f)) return r;
+    lease.busy = false;
     if (f) return fail(LSKUM_ERR_NONPHYSICAL, "state has rho <= 0 or p <= 0");
     return LSKUM_OK;
 }

@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <mutex>
 #include <string>
 #include <type_traits>
 #include <vector>
@@ -162,9 +163,22 @@ struct Params {
     int qgrad_lanes;  // 0 LDS tiles (library choice), else direct gathers with these lanes
 };
 
-// Device work arrays of one flow state.
+// Pinned slots for one field on its way to or from host arrays.  A call takes a
+// set for itself: calls of several threads on one state run at the same time.
 constexpr int kSlots = 3;
+constexpr int kIdleSets = 2;  // kept for later calls
 
+struct HostSlots {
+    double* mem = nullptr;  // kSlots x [4][points]
+    hipEvent_t ev[kSlots] = {};
+};
+struct SlotPool {
+    std::mutex mu;
+    HostSlots idle[kIdleSets];
+    int n_idle = 0;
+};
+
+// Device work arrays of one flow state.
 struct State {
     const Cloud* cloud = nullptr;
     Params prm{};
@@ -221,9 +235,7 @@ struct State {
     int graph_iters = 0;
     hipEvent_t ev[8] = {};
     bool have_events = false;
-    // pinned slots for fields on their way to and from host arrays (first use)
-    double* slots = nullptr;
-    hipEvent_t slot_ev[kSlots] = {};
+    SlotPool* slots = nullptr;
 };
 
 // Residual-driven CFL control of a batch (lskum_batch_set_cfl_control): a

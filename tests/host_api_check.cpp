@@ -1,0 +1,143 @@
+// Host code of the C ABI (csrc/lskum_api.hip) compiled with g++ on a stand-in
+// for the HIP runtime (host_runtime/): the kernels that move fields really move
+// them, the others do nothing.  One check per command-line name; exit code 0 if
+// it holds.
+#include "../paper_2406_07441_amd/csrc/lskum_api.hip"
+
+#include <condition_variable>
+#include <thread>
+
+namespace lskum {
+static hipError_t ok() { return hipSuccess; }
+hipError_t launch_precompute(Cloud&, hipStream_t) { return ok(); }
+hipError_t launch_sweep_weights(Cloud&, hipStream_t) { return ok(); }
+hipError_t launch_free_stream(State&) { return ok(); }
+hipError_t launch_q_from_U(State&) { return ok(); }
+hipError_t launch_q_derivatives(State&, bool) { return ok(); }
+hipError_t launch_residual(State&, int, bool) { return ok(); }
+hipError_t launch_norm(State&, int) { return ok(); }
+hipError_t launch_reset_components(State&) { return ok(); }
+hipError_t launch_sweeps(State&) { return ok(); }
+hipError_t launch_sweep_dir(State&, bool) { return ok(); }
+hipError_t launch_update(State&) { return ok(); }
+hipError_t launch_explicit_update(State&) { return ok(); }
+hipError_t launch_forces(State&) { return ok(); }
+hipError_t launch_clear_flags(int32_t*, hipStream_t) { return ok(); }
+hipError_t clear_increment(State&, int64_t, int64_t) { return ok(); }
+hipError_t reset_cfl(State&) { return ok(); }
+hipError_t launch_scratch_begin(State&, double, double, const double*) { return ok(); }
+hipError_t launch_residual_out(State&, double*, double*) { return ok(); }
+hipError_t launch_soa_to_aos(const double* soa, D4* aos, int64_t n, hipStream_t) {
+    for (int64_t p = 0; p < n; ++p) aos[p] = {soa[p], soa[n + p], soa[2 * n + p], soa[3 * n + p]};
+    return ok();
+}
+template <class V>
+static hipError_t to_soa(const V* aos, double* soa, int64_t n) {
+    for (int64_t p = 0; p < n; ++p) {
+        soa[p] = aos[p].x;
+        soa[n + p] = aos[p].y;
+        soa[2 * n + p] = aos[p].z;
+        soa[3 * n + p] = aos[p].w;
+    }
+    return ok();
+}
+hipError_t launch_aos_to_soa(const D4* aos, double* soa, int64_t n, hipStream_t) {
+    return to_soa(aos, soa, n);
+}
+hipError_t launch_aosf_to_soa(const F4* aos, double* soa, int64_t n, hipStream_t) {
+    return to_soa(aos, soa, n);
+}
+}  // namespace lskum
+
+static int failures = 0;
+#define CHECK(cond)                                                  \
+    do {                                                             \
+        if (!(cond)) {                                               \
+            std::fprintf(stderr, "line %d: %s\n", __LINE__, #cond);  \
+            ++failures;                                              \
+        }                                                            \
+    } while (0)
+
+// A row of n points, each the neighbour of the next.
+static lskum_cloud* chain(int64_t n) {
+    std::vector<double> x(n), y(n, 0.0);
+    std::vector<int8_t> type(n, 1);
+    std::vector<int32_t> off(1, 0), idx;
+    for (int64_t p = 0; p < n; ++p) {
+        x[p] = (double)p;
+        if (p) idx.push_back((int32_t)p - 1);
+        if (p + 1 < n) idx.push_back((int32_t)p + 1);
+        off.push_back((int32_t)idx.size());
+    }
+    lskum_cloud* c = nullptr;
+    CHECK(lskum_cloud_create(n, x.data(), y.data(), type.data(), nullptr, nullptr, off.data(),
+                             idx.data(), nullptr, &c) == LSKUM_OK);
+    return c;
+}
+
+static std::vector<double> field(int64_t n, double base) {
+    std::vector<double> U(4 * n);
+    for (size_t k = 0; k < U.size(); ++k) U[k] = base + (double)k;
+    return U;
+}
+
+static lskum_params params() {
+    lskum_params p;
+    lskum_default_params(&p);
+    return p;
+}
+
+// Two threads read two conditions of one batch (and one state twice): the
+// second call runs while the first waits for its last transposition.
+static void concurrent_copies() {
+    for (int64_t n : {100, 40000, 140000}) {
+        lskum_cloud* c = chain(n);
+        const int32_t which[2] = {0, 0};
+        const double mach[2] = {0.5, 0.6}, aoa[2] = {0.0, 1.0};
+        const lskum_params p = params();
+        lskum_batch* b = nullptr;
+        CHECK(lskum_batch_create(1, &c, 2, which, mach, aoa, &p, nullptr, &b) == LSKUM_OK);
+        const std::vector<double> U0 = field(n, 1.0), U1 = field(n, -1e9);
+        CHECK(lskum_batch_set_U(b, 0, U0.data(), 0) == LSKUM_OK);
+        CHECK(lskum_batch_set_U(b, 1, U1.data(), 0) == LSKUM_OK);
+        std::mutex mu;
+        std::condition_variable cv;
+        bool go = false, done = false;
+        const std::thread::id first = std::this_thread::get_id();
+        std::vector<double> got0(4 * n), got1(4 * n);
+        std::thread other([&] {
+            {
+                std::unique_lock<std::mutex> lk(mu);
+                cv.wait(lk, [&] { return go; });
+            }
+            CHECK(lskum_batch_get_U(b, 1, got1.data(), 0) == LSKUM_OK);
+            std::lock_guard<std::mutex> lk(mu);
+            done = true;
+            cv.notify_all();
+        });
+        fake::on_wait = [&] {
+            if (std::this_thread::get_id() != first) return;
+            std::unique_lock<std::mutex> lk(mu);
+            go = true;
+            cv.notify_all();
+            // calls that take turns make the other one wait for this one
+            cv.wait_for(lk, std::chrono::milliseconds(300), [&] { return done; });
+        };
+        CHECK(lskum_batch_get_U(b, 0, got0.data(), 0) == LSKUM_OK);
+        other.join();
+        fake::on_wait = nullptr;
+        CHECK(got0 == U0);
+        CHECK(got1 == U1);
+        lskum_batch_destroy(b);
+        lskum_cloud_destroy(c);
+    }
+    CHECK(fake::pinned_live == 0);
+    CHECK(fake::events_live == 0);
+}
+
+int main(int argc, char** argv) {
+    const std::string name = argc > 1 ? argv[1] : "";
+    if (name == "concurrent_copies") concurrent_copies();
+    else return 2;
+    return failures ? 1 : 0;
+}
