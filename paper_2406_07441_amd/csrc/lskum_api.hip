@@ -486,8 +486,31 @@ int set_tolerances(lskum::State& s, bool on) {
 // One megabyte a slot: the link moves one in 20 us, five times a launch's cost.
 constexpr int64_t kSlotPoints = 1 << 15;
 
+// Makes a device current for a scope (the caller may have another one current).
+class DeviceScope {
+public:
+    DeviceScope() = default;
+    DeviceScope(const DeviceScope&) = delete;
+    DeviceScope& operator=(const DeviceScope&) = delete;
+    ~DeviceScope() {
+        if (back_ >= 0) (void)hipSetDevice(back_);
+    }
+    hipError_t enter(int device) {
+        int now = -1;
+        hipError_t e = hipGetDevice(&now);
+        if (e != hipSuccess || now == device) return e;
+        e = hipSetDevice(device);
+        if (e == hipSuccess) back_ = now;
+        return e;
+    }
+
+private:
+    int back_ = -1;
+};
+
 // A call's own set of slots, returned at the end of its scope; work on the
-// stream that may still touch them is waited for first.
+// stream that may still touch them is waited for first.  The state's device is
+// current meanwhile: events belong to the device that they are made on.
 class SlotLease {
 public:
     explicit SlotLease(lskum::State& s) : s_(s) {}
@@ -506,6 +529,7 @@ public:
         free_slots(h_);
     }
     int take() {
+        HIPCHK(device_.enter(s_.cloud->device));
         {
             std::lock_guard<std::mutex> lk(s_.slots->mu);
             if (s_.slots->n_idle) {
@@ -534,6 +558,7 @@ public:
     bool busy = false;
 
 private:
+    DeviceScope device_;  // left last
     lskum::State& s_;
     lskum::HostSlots h_;
 };

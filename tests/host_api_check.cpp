@@ -135,9 +135,31 @@ static void concurrent_copies() {
     CHECK(fake::events_live == 0);
 }
 
+// Host copies of a state while another device is current: its streams and
+// events stay those of its own device, and the caller's device stays current.
+static void other_device_current() {
+    const int64_t n = 140000;  // more chunks than slots: events both ways
+    lskum_cloud* c = chain(n);
+    const lskum_params p = params();
+    lskum_state* s = nullptr;
+    CHECK(lskum_state_create(c, 0.5, 0.0, &p, nullptr, &s) == LSKUM_OK);
+    const std::vector<double> U = field(n, 1.0);
+    std::vector<double> got(4 * n);
+    fake::device = 1;
+    CHECK(lskum_state_set_U(s, U.data(), 0) == LSKUM_OK);
+    CHECK(lskum_state_get_U(s, got.data(), 0) == LSKUM_OK);
+    CHECK(got == U);
+    CHECK(fake::foreign_events == 0);
+    CHECK(fake::device == 1);
+    fake::device = 0;
+    lskum_state_destroy(s);
+    lskum_cloud_destroy(c);
+}
+
 int main(int argc, char** argv) {
     const std::string name = argc > 1 ? argv[1] : "";
     if (name == "concurrent_copies") concurrent_copies();
+    else if (name == "other_device_current") other_device_current();
     else return 2;
     return failures ? 1 : 0;
 }
