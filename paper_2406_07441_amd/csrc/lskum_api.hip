@@ -58,7 +58,78 @@ hipError_t upload(T* dst, const T* src, size_t count) {
     return hipMemcpy(dst, src, count * sizeof(T), hipMemcpyHostToDevice);
 }
 
+// Pinned slots for one field on its way to or from host arrays.  A call takes a
+// set for itself, so calls of several threads run at the same time.  Two sets
+// of a device are kept for later calls, the largest that there have been, until
+// its last cloud goes: pinning memory takes 0.1 ms, many times a small field's
+// copy, and a state may be read only once.
+constexpr int kSlots = 3, kIdleSets = 2, kMaxDevices = 64;
+
+struct HostSlots {
+    double* mem = nullptr;  // kSlots x [4][points]
+    int64_t points = 0;
+    hipEvent_t ev[kSlots] = {};
+};
+
+struct SlotPool {
+    std::mutex mu;
+    int clouds = 0;
+    int n_idle = 0;
+    HostSlots idle[kIdleSets];  // by size, the largest last
+};
+
+SlotPool g_slots[kMaxDevices];
+
+SlotPool& slot_pool(int device) { return g_slots[std::clamp(device, 0, kMaxDevices - 1)]; }
+
+void free_slots(HostSlots& h) {
+    (void)hipHostFree(h.mem);
+    for (hipEvent_t ev : h.ev)
+        if (ev) (void)hipEventDestroy(ev);
+    h = HostSlots{};
+}
+
+// Takes the smallest idle set of at least `points` points; false if there is none.
+bool take_slots(SlotPool& pool, int64_t points, HostSlots& out) {
+    std::lock_guard<std::mutex> lk(pool.mu);
+    for (int k = 0; k < pool.n_idle; ++k)
+        if (pool.idle[k].points >= points) {
+            out = pool.idle[k];
+            for (--pool.n_idle; k < pool.n_idle; ++k) pool.idle[k] = pool.idle[k + 1];
+            return true;
+        }
+    return false;
+}
+
+void give_slots(SlotPool& pool, HostSlots h) {
+    {
+        std::lock_guard<std::mutex> lk(pool.mu);
+        if (pool.n_idle == kIdleSets && pool.idle[0].points < h.points) {
+            std::swap(h, pool.idle[0]);  // the smallest goes
+            for (int k = 0; k + 1 < kIdleSets && pool.idle[k].points > pool.idle[k + 1].points; ++k)
+                std::swap(pool.idle[k], pool.idle[k + 1]);
+        } else if (pool.n_idle < kIdleSets) {
+            int k = pool.n_idle++;
+            for (; k > 0 && pool.idle[k - 1].points > h.points; --k) pool.idle[k] = pool.idle[k - 1];
+            pool.idle[k] = h;
+            return;
+        }
+    }
+    free_slots(h);
+}
+
+void count_cloud(lskum::Cloud& c, bool in) {
+    if (c.uploaded == in) return;
+    c.uploaded = in;
+    SlotPool& pool = slot_pool(c.device);
+    std::lock_guard<std::mutex> lk(pool.mu);
+    pool.clouds += in ? 1 : -1;
+    if (pool.clouds) return;
+    while (pool.n_idle) free_slots(pool.idle[--pool.n_idle]);
+}
+
 void free_cloud(lskum::Cloud& c) {
+    count_cloud(c, false);
     void* ptrs[] = {c.xy,     c.frame,     c.type,   c.off,      c.idx,      c.colour,
                     c.col_perm, c.wall_list, c.wall_box, c.wall_xy, c.wall_run_off, c.geom, c.lsq, c.lo_off,   c.lo_idx,   c.up_off,
                     c.up_idx, c.lo_w,      c.up_w,     c.lo_code,  c.up_code,  c.comp, c.qcomp,
@@ -147,6 +218,7 @@ int validate_csr(int64_t n, const int32_t* off, const int32_t* idx) {
 // filled in c.h_*: colour permutation, lower/upper colour neighbour lists,
 // wall list, per-component tables, then the geometry precompute kernel.
 int upload_cloud(lskum::Cloud& c) {
+    count_cloud(c, true);
     const int64_t n = c.n, nnz = c.nnz;
     c.ncolour = 0;
     for (int64_t p = 0; p < n; ++p) c.ncolour = std::max(c.ncolour, c.h_colour[p] + 1);
@@ -362,13 +434,6 @@ int upload_cloud(lskum::Cloud& c) {
     return LSKUM_OK;
 }
 
-void free_slots(lskum::HostSlots& h) {
-    (void)hipHostFree(h.mem);
-    for (hipEvent_t ev : h.ev)
-        if (ev) (void)hipEventDestroy(ev);
-    h = lskum::HostSlots{};
-}
-
 void free_state(lskum::State& s) {
     if (s.graph) (void)hipGraphExecDestroy(s.graph);
     if (s.have_events)
@@ -379,9 +444,6 @@ void free_state(lskum::State& s) {
                     s.res_hist, s.flags, s.active, s.status, s.iters, s.res_last, s.tol_abs, s.cfl,
                     s.vinf};
     for (void* p : ptrs) (void)hipFree(p);
-    if (s.slots)
-        for (int k = 0; k < s.slots->n_idle; ++k) free_slots(s.slots->idle[k]);
-    delete s.slots;
     if (s.own_stream && s.stream) (void)hipStreamDestroy(s.stream);
     s = lskum::State{};
 }
@@ -519,31 +581,19 @@ public:
     ~SlotLease() {
         if (!h_.mem) return;
         if (busy) (void)hipStreamSynchronize(s_.stream);
-        {
-            std::lock_guard<std::mutex> lk(s_.slots->mu);
-            if (s_.slots->n_idle < lskum::kIdleSets) {
-                s_.slots->idle[s_.slots->n_idle++] = h_;
-                return;
-            }
-        }
-        free_slots(h_);
+        give_slots(slot_pool(s_.cloud->device), h_);
     }
     int take() {
         HIPCHK(device_.enter(s_.cloud->device));
-        {
-            std::lock_guard<std::mutex> lk(s_.slots->mu);
-            if (s_.slots->n_idle) {
-                h_ = s_.slots->idle[--s_.slots->n_idle];
-                return LSKUM_OK;
-            }
-        }
-        lskum::HostSlots h;
+        if (take_slots(slot_pool(s_.cloud->device), points(), h_)) return LSKUM_OK;
+        HostSlots h;
+        h.points = points();
         hipError_t e = hipSuccess;
         for (hipEvent_t& ev : h.ev)
             if (e == hipSuccess)
                 e = hipEventCreateWithFlags(&ev, hipEventDisableTiming | hipEventReleaseToSystem);
         if (e == hipSuccess)
-            e = hipHostMalloc((void**)&h.mem, lskum::kSlots * points() * sizeof(lskum::D4),
+            e = hipHostMalloc((void**)&h.mem, kSlots * h.points * sizeof(lskum::D4),
                               hipHostMallocCoherent);
         if (e != hipSuccess) {
             free_slots(h);
@@ -553,14 +603,14 @@ public:
         return LSKUM_OK;
     }
     int64_t points() const { return std::min(s_.cloud->n, kSlotPoints); }
-    double* slot(int64_t chunk) const { return h_.mem + chunk % lskum::kSlots * 4 * points(); }
-    hipEvent_t event(int64_t chunk) const { return h_.ev[chunk % lskum::kSlots]; }
+    double* slot(int64_t chunk) const { return h_.mem + chunk % kSlots * 4 * points(); }
+    hipEvent_t event(int64_t chunk) const { return h_.ev[chunk % kSlots]; }
     bool busy = false;
 
 private:
     DeviceScope device_;  // left last
     lskum::State& s_;
-    lskum::HostSlots h_;
+    HostSlots h_;
 };
 
 template <class V>
@@ -581,8 +631,8 @@ int copy_field_out(lskum::State& s, const V* src, int64_t p0, int64_t n, double*
     if (int r = lease.take()) return r;
     lease.busy = true;
     const int64_t size = lease.points(), nchunk = (n + size - 1) / size;
-    for (int64_t k = 0; k < nchunk + lskum::kSlots; ++k) {
-        if (const int64_t c = k - lskum::kSlots; c >= 0 && c < nchunk) {  // to the caller
+    for (int64_t k = 0; k < nchunk + kSlots; ++k) {
+        if (const int64_t c = k - kSlots; c >= 0 && c < nchunk) {  // to the caller
             const int64_t o = c * size, m = std::min(size, n - o);
             HIPCHK(hipEventSynchronize(lease.event(c)));
             for (int v = 0; v < 4; ++v)
@@ -611,11 +661,11 @@ int copy_U_in(lskum::State& s, const double* U, int64_t p0, int64_t n, int on_de
     const int64_t size = lease.points(), nchunk = (n + size - 1) / size;
     for (int64_t c = 0; c < nchunk; ++c) {
         const int64_t o = c * size, m = std::min(size, n - o);
-        if (c >= lskum::kSlots) HIPCHK(hipEventSynchronize(lease.event(c)));
+        if (c >= kSlots) HIPCHK(hipEventSynchronize(lease.event(c)));
         for (int v = 0; v < 4; ++v)
             std::memcpy(lease.slot(c) + v * m, U + v * n + o, m * sizeof(double));
         HIPCHK(lskum::launch_soa_to_aos(lease.slot(c), s.U + p0 + o, m, s.stream));
-        if (c + lskum::kSlots < nchunk) HIPCHK(hipEventRecord(lease.event(c), s.stream));
+        if (c + kSlots < nchunk) HIPCHK(hipEventRecord(lease.event(c), s.stream));
     }
     return LSKUM_OK;
 }
@@ -638,8 +688,6 @@ int init_state(lskum::State& s, const lskum::Cloud& c, const lskum_params* prm,
         HIPCHK(hipStreamCreateWithFlags(&s.stream, hipStreamNonBlocking));
         s.own_stream = true;
     }
-    s.slots = new (std::nothrow) lskum::SlotPool();
-    if (!s.slots) return fail(LSKUM_ERR_OOM, "host allocation");
     const int64_t n = c.n;
     const int nc = c.ncomp;
     s.res_cap = 4096;
@@ -875,7 +923,6 @@ void lskum::api_clear_error() { g_err.clear(); }
 namespace {
 
 constexpr size_t kScratchBytes = (size_t)64 << 20;
-constexpr int kMaxDevices = 64;
 __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 std::mutex g_scratch_mu;

@@ -5,7 +5,6 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
-#include <mutex>
 #include <string>
 #include <type_traits>
 #include <vector>
@@ -62,6 +61,7 @@ static_assert(kQTileJ * kQTileK <= kQTile, "a row block fits one tile");
 
 struct Cloud {
     int device = 0;
+    bool uploaded = false;     // counted among its device's clouds
     int64_t n = 0, nnz = 0;
     int32_t ncolour = 0;
     int64_t n_degenerate = 0;
@@ -163,21 +163,6 @@ struct Params {
     int qgrad_lanes;  // 0 LDS tiles (library choice), else direct gathers with these lanes
 };
 
-// Pinned slots for one field on its way to or from host arrays.  A call takes a
-// set for itself: calls of several threads on one state run at the same time.
-constexpr int kSlots = 3;
-constexpr int kIdleSets = 2;  // kept for later calls
-
-struct HostSlots {
-    double* mem = nullptr;  // kSlots x [4][points]
-    hipEvent_t ev[kSlots] = {};
-};
-struct SlotPool {
-    std::mutex mu;
-    HostSlots idle[kIdleSets];
-    int n_idle = 0;
-};
-
 // Device work arrays of one flow state.
 struct State {
     const Cloud* cloud = nullptr;
@@ -235,7 +220,6 @@ struct State {
     int graph_iters = 0;
     hipEvent_t ev[8] = {};
     bool have_events = false;
-    SlotPool* slots = nullptr;
 };
 
 // Residual-driven CFL control of a batch (lskum_batch_set_cfl_control): a

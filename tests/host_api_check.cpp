@@ -156,10 +156,38 @@ static void other_device_current() {
     lskum_cloud_destroy(c);
 }
 
+// Pinned memory outlives the states that it served: a program that makes a
+// state, reads it and drops it, again and again, pays for it once, also where
+// clouds of other sizes come between; all is given back with the last cloud.
+static void short_lived_states() {
+    lskum_cloud* c[3] = {chain(100), chain(40000), chain(140000)};
+    const lskum_params p = params();
+    for (int round = 0; round < 4; ++round)
+        for (lskum_cloud* cl : c) {
+            const int64_t n = cl->c.n;
+            lskum_state* s = nullptr;
+            CHECK(lskum_state_create(cl, 0.5, 0.0, &p, nullptr, &s) == LSKUM_OK);
+            const std::vector<double> U = field(n, round);
+            std::vector<double> got(4 * n);
+            const int before = fake::event_records;
+            CHECK(lskum_state_set_U(s, U.data(), 0) == LSKUM_OK);
+            CHECK(n > 98304 || fake::event_records == before);
+            CHECK(lskum_state_get_U(s, got.data(), 0) == LSKUM_OK);
+            CHECK(got == U);
+            lskum_state_destroy(s);
+        }
+    CHECK(fake::pinned_allocs <= 2);
+    CHECK(fake::pinned_live <= 2);
+    for (lskum_cloud* cl : c) lskum_cloud_destroy(cl);
+    CHECK(fake::pinned_live == 0);
+    CHECK(fake::events_live == 0);
+}
+
 int main(int argc, char** argv) {
     const std::string name = argc > 1 ? argv[1] : "";
     if (name == "concurrent_copies") concurrent_copies();
     else if (name == "other_device_current") other_device_current();
+    else if (name == "short_lived_states") short_lived_states();
     else return 2;
     return failures ? 1 : 0;
 }
