@@ -335,11 +335,16 @@ __global__ void __launch_bounds__(kTrainThreads, 2) k_mlp_train(
 #pragma unroll
             for (int s = 0; s < 4; ++s) wf[s] = *(const bf16x8*)&W[at + ((4 * w + s) * 64 + l) * 8];
         };
+        // Rows beyond the last are zeros (they read row 0): their gradient is zero, but
+        // zero times the infinities that a row of the data may give is not.
         float x[2][kIn];
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
             const int64_t m = row0 + 16 * t + r;
             load_row(R.X + (m < Mvalid ? data_row(R, m) : 0) * kIn, x[t]);
+            if (m >= Mvalid)
+#pragma unroll
+                for (int f = 0; f < kIn; ++f) x[t][f] = 0.0f;
             if (w == 0 && g == 0)
 #pragma unroll
                 for (int f = 0; f < kIn; ++f) L.x[16 * t + r][f] = x[t][f];
