@@ -553,10 +553,6 @@ __global__ void __launch_bounds__(kBlock, 4) k_qgrad(
 static_assert(kQTile * 4 == kBlock, "a q-derivative tile is one point per four lanes");
 constexpr int kLnPre = 8;  // list positions per lane held in registers (a whole stencil of <= 32)
 
-// The usual stride of the staged arrays: a 16 x 4 block of points with 5 x 5
-// stencils lists 160 points, 18 KiB with derivatives.
-constexpr int kTileStride = 160;
-
 template <int C>
 __device__ __forceinline__ double quad_bcast(double v) {  // component C's value, held by lane C
     return dpp<C * 0x55>(v);
@@ -852,9 +848,6 @@ __device__ __forceinline__ D4 reconstruct(const D4& q, const D4& gx, const D4& g
     return {fma(hy, gy.x, fma(hx, gx.x, q.x)), fma(hy, gy.y, fma(hx, gx.y, q.y)),
             fma(hy, gy.z, fma(hx, gx.z, q.z)), fma(hy, gy.w, fma(hx, gx.w, q.w))};
 }
-
-constexpr int kResidualMinTiles = 256;  // one block per CU
-constexpr int kSub4Tiles = 256, kSub2Tiles = 2560;  // one and ten blocks per CU
 
 // Everything a residual launch reads and writes.
 struct ResidualArgs {
@@ -2075,38 +2068,24 @@ static void residual_lanes(State& s, bool in_step) {
                          s.prm.variant, s.prm.jvp_mode, s.dU, s.dUf,
                          s.Rs,       c.colour,    in_step && fused_first_colour(s),
                          s.prm.farfield, s.vinf};
-    // Few tiles leave a launch as long as one lane's walk: four threads to a
-    // lane up to a block for every CU, two up to ten, one beyond, where the
-    // threads that wait for each other's turn cost more than they bring (FP64,
-    // one / two / four threads: 1,024 points 16 / 12 / 11 us, 16,384 points 21 /
-    // 13 / 12, 40,250 points 24 / 20 / 27, 163,840 points 57 / 55 / 81, 640,000
-    // points 169 / 189 / 322).  With lanes asked for, and small clouds without
-    // tiles, neighbours are gathered: 1,024 points 16 us, 6,400 points 16, 40,250
-    // points 26, 2,621,440 points 712 against 640 (617 since).  All forms give the same bits.
-    if (s.qgrad_tiled && c.tile_hmax <= kTileStride && c.ntile > 0) {
-        const dim3 g((unsigned)c.ntile);
-        if constexpr (LANES == 2) {
-            if (!s.prm.residual_lanes && c.ntile <= kSub4Tiles) {
-                hipLaunchKernelGGL((k_residual_tiled<MIXED, 2, kTileStride, 4>), g, dim3(kQTile * 8),
-                                   0, s.stream, A);
-                return;
-            }
-            if (!s.prm.residual_lanes && c.ntile <= kSub2Tiles) {
-                hipLaunchKernelGGL((k_residual_tiled<MIXED, 2, kTileStride, 2>), g, dim3(kQTile * 4),
-                                   0, s.stream, A);
-                return;
-            }
+    const ResidualForm form = residual_form(s);
+    if (!form.tiled) {
+        hipLaunchKernelGGL((k_residual<MIXED, LANES>), dim3(grid_for(c.n * LANES)), dim3(kBlock), 0,
+                           s.stream, A);
+        return;
+    }
+    const dim3 g((unsigned)c.ntile), b(kQTile * LANES * form.sub);
+    if constexpr (LANES == 2) {
+        if (form.sub == 4) {
+            hipLaunchKernelGGL((k_residual_tiled<MIXED, 2, kTileStride, 4>), g, b, 0, s.stream, A);
+            return;
         }
-        if (c.ntile >= kResidualMinTiles) {
-            hipLaunchKernelGGL((k_residual_tiled<MIXED, LANES, kTileStride, 1>), g,
-                               dim3(kQTile * LANES), 0, s.stream, A);
+        if (form.sub == 2) {
+            hipLaunchKernelGGL((k_residual_tiled<MIXED, 2, kTileStride, 2>), g, b, 0, s.stream, A);
             return;
         }
     }
-    {
-        hipLaunchKernelGGL((k_residual<MIXED, LANES>), dim3(grid_for(c.n * LANES)), dim3(kBlock), 0,
-                           s.stream, A);
-    }
+    hipLaunchKernelGGL((k_residual_tiled<MIXED, LANES, kTileStride, 1>), g, b, 0, s.stream, A);
 }
 
 template <bool MIXED>

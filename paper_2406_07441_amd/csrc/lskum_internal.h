@@ -222,6 +222,35 @@ struct State {
     bool have_events = false;
 };
 
+// The usual stride of a tile's staged arrays: a 16 x 4 block of points with 5 x 5
+// stencils lists 160 points.
+constexpr int kTileStride = 160;
+
+// Which residual kernel a state's launches take: LDS tiles or direct gathers,
+// and threads per lane.  Few tiles leave a launch as long as one lane's walk: four
+// threads to a lane up to a block for every CU, two up to ten, one beyond, where
+// the threads that wait for each other's turn cost more than they bring (FP64,
+// one / two / four threads: 1,024 points 16 / 12 / 11 us, 16,384 points 21 / 13 /
+// 12, 40,250 points 24 / 20 / 27, 163,840 points 57 / 55 / 81, 640,000 points 169
+// / 189 / 322).  With lanes asked for, small clouds gather: 1,024 points 16 us,
+// 6,400 points 16, 40,250 points 26, 2,621,440 points 712 against 617 tiled.  So do
+// clouds without tiles, and those with a tile list beyond the stride.  All forms
+// give the same bits, whatever the q-derivative passes take.
+constexpr int kResidualMinTiles = 256;              // one block per CU
+constexpr int kSub4Tiles = 256, kSub2Tiles = 2560;  // one and ten blocks per CU
+
+struct ResidualForm {
+    bool tiled;
+    int sub;
+};
+inline ResidualForm residual_form(const State& s) {
+    const Cloud& c = *s.cloud;
+    if (c.ntile == 0 || c.tile_hmax > kTileStride) return {false, 1};
+    if (!s.prm.residual_lanes && c.ntile <= kSub2Tiles)
+        return {true, c.ntile <= kSub4Tiles ? 4 : 2};
+    return {c.ntile >= kResidualMinTiles, 1};
+}
+
 // Residual-driven CFL control of a batch (lskum_batch_set_cfl_control): a
 // condition whose residual reaches no new minimum during a window of
 // iterations has its CFL number reduced.

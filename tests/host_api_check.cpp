@@ -183,11 +183,36 @@ static void short_lived_states() {
     CHECK(fake::events_live == 0);
 }
 
+// The lanes of the q-derivative passes leave the residual's form alone.
+static void residual_form() {
+    for (int64_t n : {1000, 20000, 200000}) {
+        lskum_cloud* c = chain(n);
+        for (int32_t lanes : {0, 2}) {
+            lskum_params p = params();
+            p.residual_lanes = lanes;
+            lskum_state* s = nullptr;
+            CHECK(lskum_state_create(c, 0.5, 0.0, &p, nullptr, &s) == LSKUM_OK);
+            const lskum::ResidualForm want = lskum::residual_form(s->s);
+            CHECK(want.tiled == (n > 16384 || lanes == 0));
+            CHECK(want.sub == (lanes || n > 163840 ? 1 : n > 16384 ? 2 : 4));
+            for (int32_t q : {1, 2, 4, 8}) {
+                p.qgrad_lanes = q;
+                CHECK(lskum_state_set_params(s, &p) == LSKUM_OK);
+                const lskum::ResidualForm got = lskum::residual_form(s->s);
+                CHECK(got.tiled == want.tiled && got.sub == want.sub);
+            }
+            lskum_state_destroy(s);
+        }
+        lskum_cloud_destroy(c);
+    }
+}
+
 int main(int argc, char** argv) {
     const std::string name = argc > 1 ? argv[1] : "";
     if (name == "concurrent_copies") concurrent_copies();
     else if (name == "other_device_current") other_device_current();
     else if (name == "short_lived_states") short_lived_states();
+    else if (name == "residual_form") residual_form();
     else return 2;
     return failures ? 1 : 0;
 }

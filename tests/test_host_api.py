@@ -24,7 +24,8 @@ def harness():
     shutil.rmtree(d, ignore_errors=True)
 
 
-@pytest.mark.parametrize("name", ["concurrent_copies", "other_device_current", "short_lived_states"])
+@pytest.mark.parametrize("name", ["concurrent_copies", "other_device_current", "short_lived_states",
+                                  "residual_form"])
 def test_host_api(harness, name):
     r = subprocess.run([harness, name], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stderr
