@@ -87,7 +87,9 @@ typedef struct {
     int32_t sweep_lanes;    /* lanes per point in the sweep kernels: 1, 2, 4, 8,
                                16; 0 = library choice */
     int32_t residual_lanes; /* lanes per point in the residual kernel: 1, 2, 4,
-                               8; 0 = library choice */
+                               8; 0 = library choice.  On small clouds the
+                               library may spread a lane over several threads
+                               (both kernels; the same bits) */
     int32_t limiter;        /* 0: none (the paper's scheme); 1: Venkatakrishnan
                                limiter on the q~ reconstruction (an addition
                                for flows with shocks) */
@@ -323,8 +325,8 @@ int lskum_batch_set_U(lskum_batch* b, int32_t cond, const double* U, int on_devi
  * the residual kernels, and times the q-derivative passes in their LDS-tiled
  * form and with direct gathers at 1, 2, 4, 8 lanes and keeps the fastest
  * (written to *sweep_lanes, *residual_lanes, *qgrad_lanes as lskum_params
- * values; any of the three may be NULL).  The batch's state is restored
- * afterwards. */
+ * values; any of the three may be NULL).  What the library chooses by itself is
+ * among the candidates.  The batch's state is restored afterwards. */
 int lskum_batch_autotune(lskum_batch* b, int32_t iters, int32_t* sweep_lanes,
                          int32_t* residual_lanes, int32_t* qgrad_lanes);
 

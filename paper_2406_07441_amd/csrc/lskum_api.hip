@@ -490,17 +490,20 @@ lskum::Params to_params(const lskum_params* p) {
 // and 2 for the compute-bound residual (measured best on the 163,840-point
 // transonic cloud, FP64 and mixed).  Up to kSmallSweep points a colour phase
 // leaves most of the chip idle and lasts as long as one lane's walk: 16 lanes
-// then, and 32, one entry each, up to kTinySweep (the sums of 8 lanes bit for
-// bit while no list exceeds 32 entries, so the choice may depend on how many
-// conditions share a launch).  Iteration at 6,400 points with 8 and 16 lanes:
+// then, which up to kTinySweep points are 32, one entry each (the sums of 8 lanes
+// bit for bit while no list exceeds 32 entries, so the choice may depend on how
+// many conditions share a launch).  Iteration at 6,400 points with 8 and 16 lanes:
 // 116.5 and 110.4 us; 40,250: 142.5 and 141.6; 80,000: 173 and 176; 163,840: 227
 // and 229.  With 16 and 32: 1,024 points 100.6 and 96.1, 6,400 points 101.2 and
 // 95.8, 16,384 points 119.8 and 112.4, 25,600 points 114 and 114, 40,250 points
-// (mixed) 114 and 118.
+// (mixed) 114 and 118.  A caller's 16 are 32 there too: the lane counts that a
+// caller can ask for (and the autotuner tries) include every form of the library's own.
 constexpr int64_t kSmallSweep = 50000, kTinySweep = 20000;
 void apply_lanes(lskum::State& s) {
-    const bool small = s.cloud->n <= kSmallSweep && s.cloud->max_list <= 32;
-    s.sweep_lanes = s.prm.sweep_lanes ? s.prm.sweep_lanes : (small ? (s.cloud->n <= kTinySweep ? 32 : 16) : 8);
+    const bool short_lists = s.cloud->max_list <= 32;
+    s.sweep_lanes = s.prm.sweep_lanes;
+    if (!s.sweep_lanes) s.sweep_lanes = short_lists && s.cloud->n <= kSmallSweep ? 16 : 8;
+    if (s.sweep_lanes == 16 && short_lists && s.cloud->n <= kTinySweep) s.sweep_lanes = 32;
     s.residual_lanes = s.prm.residual_lanes ? s.prm.residual_lanes : 2;
     s.qgrad_tiled = s.prm.qgrad_lanes == 0;
     s.qgrad_lanes = s.prm.qgrad_lanes ? s.prm.qgrad_lanes : 4;
@@ -1545,7 +1548,10 @@ int lskum_batch_set_U(lskum_batch* b, int32_t cond, const double* U, int on_devi
 }
 
 // Times each candidate lane count (1, 2, 4, 8 lanes per point; 16 for the sweeps) for the sweep
-// and the residual kernels on the batch itself and keeps the fastest of each.
+// and the residual kernels on the batch itself and keeps the fastest of each.  The
+// library's own forms are among them (apply_lanes, residual_form): 18,432 points in
+// FP64, an iteration 128 us untuned, 123 to 125 tuned, and 133 when the candidates
+// lacked those forms.
 // The batch's state is saved before and restored after the trial steps.
 int lskum_batch_autotune(lskum_batch* b, int32_t iters, int32_t* sweep_lanes,
                          int32_t* residual_lanes, int32_t* qgrad_lanes) {
@@ -1561,37 +1567,47 @@ int lskum_batch_autotune(lskum_batch* b, int32_t iters, int32_t* sweep_lanes,
     // candidate of its own
     const int cands[5] = {1, 2, 4, 8, 16};
     double best_sw = 1e300, best_rs = 1e300, best_qg = 1e300;
-    int bsw = 8, brs = 2, bqg = 0;
     lskum_state tmp;
     std::swap(tmp.s, b->s);
+    // the library's own choices; a candidate's time is its shortest, and they
+    // win unless another is faster by more than such times differ
+    tmp.s.prm.sweep_lanes = tmp.s.prm.residual_lanes = tmp.s.prm.qgrad_lanes = 0;
+    apply_lanes(tmp.s);
+    const int own_sw = std::min(tmp.s.sweep_lanes, 16), own_rs = tmp.s.residual_lanes,
+              own_qg = b->c.ntile ? 0 : tmp.s.qgrad_lanes;
+    constexpr double kMargin = 0.97;
+    int bsw = own_sw, brs = own_rs, bqg = own_qg;
     int rc = LSKUM_OK;
     for (int li = 0; li < 6 && rc == LSKUM_OK; ++li) {
         const bool tiles = li == 5;
         if (tiles && b->c.ntile == 0) break;
-        tmp.s.prm.sweep_lanes = li < 5 ? cands[li] : bsw;
-        tmp.s.prm.residual_lanes = li < 4 ? cands[li] : brs;
-        tmp.s.prm.qgrad_lanes = tiles ? 0 : (li < 4 ? cands[li] : 4);
+        const int sl = li < 5 ? cands[li] : bsw, rl = li < 4 ? cands[li] : brs;
+        const int ql = tiles ? 0 : (li < 4 ? cands[li] : 4);
+        tmp.s.prm.sweep_lanes = sl;
+        tmp.s.prm.residual_lanes = rl;
+        tmp.s.prm.qgrad_lanes = ql;
         apply_lanes(tmp.s);
-        double ms[6], sw = 0, rs = 0, qg = 0;
+        double ms[6], sw = 1e300, rs = 1e300, qg = 1e300;
         for (int it = 0; it < iters + 1 && rc == LSKUM_OK; ++it) {
-            rc = lskum_step_timed(&tmp, ms);
+            // untimed work ahead of the timed: behind an idle device a phase of few
+            // launches takes as long as the host needs to launch it
+            hipError_t e = hipSuccess;
+            for (int k = 0; k < 3 && e == hipSuccess; ++k) e = lskum::launch_q_derivatives(tmp.s);
+            rc = e == hipSuccess ? lskum_step_timed(&tmp, ms) : hip_fail(e, "launch_q_derivatives");
             if (it == 0) continue;  // warm-up
-            qg += ms[0];
-            rs += ms[1];
-            sw += ms[3] + ms[4];
+            qg = std::min(qg, ms[0]);
+            rs = std::min(rs, ms[1]);
+            sw = std::min(sw, ms[3] + ms[4]);
         }
-        if (li < 5 && sw < best_sw) {
-            best_sw = sw;
-            bsw = cands[li];
-        }
-        if (li < 4 && rs < best_rs) {
-            best_rs = rs;
-            brs = cands[li];
-        }
-        if ((li < 4 || tiles) && qg < best_qg) {
-            best_qg = qg;
-            bqg = tiles ? 0 : cands[li];
-        }
+        auto better = [&](double t, int lanes, int own, double& best, int& kept) {
+            if (lanes == own) t *= kMargin;
+            if (t >= best) return;
+            best = t;
+            kept = lanes;
+        };
+        if (li < 5) better(sw, sl, own_sw, best_sw, bsw);
+        if (li < 4) better(rs, rl, own_rs, best_rs, brs);
+        if (li < 4 || tiles) better(qg, ql, own_qg, best_qg, bqg);
     }
     std::swap(tmp.s, b->s);
     s.prm = keep;

@@ -185,7 +185,7 @@ struct State {
     double* rr = nullptr;                  // per point R_rho^2 (0 at outer points)
     hipStream_t stream = nullptr;
     bool own_stream = false;
-    int sweep_lanes = 4;         // lanes per point in the sweep kernels (1, 2, 4 or 8)
+    int sweep_lanes = 4;         // lanes per point in the sweep kernels (1, 2, 4, 8, 16 or 32)
     int residual_lanes = 4;      // lanes per point in the residual kernel (1, 2, 4 or 8)
     int qgrad_lanes = 4;         // lanes per point in the q-derivative kernels
     bool qgrad_tiled = true;     // LDS-tiled q-derivative passes when the cloud has tiles
@@ -232,10 +232,11 @@ constexpr int kTileStride = 160;
 // the threads that wait for each other's turn cost more than they bring (FP64,
 // one / two / four threads: 1,024 points 16 / 12 / 11 us, 16,384 points 21 / 13 /
 // 12, 40,250 points 24 / 20 / 27, 163,840 points 57 / 55 / 81, 640,000 points 169
-// / 189 / 322).  With lanes asked for, small clouds gather: 1,024 points 16 us,
-// 6,400 points 16, 40,250 points 26, 2,621,440 points 712 against 617 tiled.  So do
-// clouds without tiles, and those with a tile list beyond the stride.  All forms
-// give the same bits, whatever the q-derivative passes take.
+// / 189 / 322).  With other lane counts than two, small clouds gather (two lanes:
+// 1,024 points 16 us, 6,400 points 16, 40,250 points 26, 2,621,440 points 712 against
+// 617 tiled).  So do clouds without tiles, and those with a tile list beyond the
+// stride.  All forms of a lane count give the same bits, whatever the q-derivative
+// passes take.
 constexpr int kResidualMinTiles = 256;              // one block per CU
 constexpr int kSub4Tiles = 256, kSub2Tiles = 2560;  // one and ten blocks per CU
 
@@ -246,7 +247,7 @@ struct ResidualForm {
 inline ResidualForm residual_form(const State& s) {
     const Cloud& c = *s.cloud;
     if (c.ntile == 0 || c.tile_hmax > kTileStride) return {false, 1};
-    if (!s.prm.residual_lanes && c.ntile <= kSub2Tiles)
+    if (s.residual_lanes == 2 && c.ntile <= kSub2Tiles)
         return {true, c.ntile <= kSub4Tiles ? 4 : 2};
     return {c.ntile >= kResidualMinTiles, 1};
 }

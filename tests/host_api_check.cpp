@@ -7,18 +7,25 @@
 #include <condition_variable>
 #include <thread>
 
+// Time (ms) that the timed kernels take, by the form that they are launched in.
+static std::function<double(const lskum::State&)> residual_ms, sweep_ms, qgrad_ms;
+
 namespace lskum {
 static hipError_t ok() { return hipSuccess; }
+static hipError_t timed(const std::function<double(const State&)>& ms, const State& s) {
+    if (ms) fake::now_ms += ms(s);
+    return hipSuccess;
+}
 hipError_t launch_precompute(Cloud&, hipStream_t) { return ok(); }
 hipError_t launch_sweep_weights(Cloud&, hipStream_t) { return ok(); }
 hipError_t launch_free_stream(State&) { return ok(); }
 hipError_t launch_q_from_U(State&) { return ok(); }
-hipError_t launch_q_derivatives(State&, bool) { return ok(); }
-hipError_t launch_residual(State&, int, bool) { return ok(); }
+hipError_t launch_q_derivatives(State& s, bool) { return timed(qgrad_ms, s); }
+hipError_t launch_residual(State& s, int, bool) { return timed(residual_ms, s); }
 hipError_t launch_norm(State&, int) { return ok(); }
 hipError_t launch_reset_components(State&) { return ok(); }
 hipError_t launch_sweeps(State&) { return ok(); }
-hipError_t launch_sweep_dir(State&, bool) { return ok(); }
+hipError_t launch_sweep_dir(State& s, bool) { return timed(sweep_ms, s); }
 hipError_t launch_update(State&) { return ok(); }
 hipError_t launch_explicit_update(State&) { return ok(); }
 hipError_t launch_forces(State&) { return ok(); }
@@ -183,18 +190,20 @@ static void short_lived_states() {
     CHECK(fake::events_live == 0);
 }
 
-// The lanes of the q-derivative passes leave the residual's form alone.
+// The lanes of the q-derivative passes leave the residual's form alone; so does
+// asking for the two lanes that the library takes by itself.
 static void residual_form() {
     for (int64_t n : {1000, 20000, 200000}) {
         lskum_cloud* c = chain(n);
-        for (int32_t lanes : {0, 2}) {
+        for (int32_t lanes : {0, 1, 2, 4, 8}) {
             lskum_params p = params();
             p.residual_lanes = lanes;
             lskum_state* s = nullptr;
             CHECK(lskum_state_create(c, 0.5, 0.0, &p, nullptr, &s) == LSKUM_OK);
             const lskum::ResidualForm want = lskum::residual_form(s->s);
-            CHECK(want.tiled == (n > 16384 || lanes == 0));
-            CHECK(want.sub == (lanes || n > 163840 ? 1 : n > 16384 ? 2 : 4));
+            const bool threads = lanes == 0 || lanes == 2;
+            CHECK(want.tiled == (n > 16384 || threads));
+            CHECK(want.sub == (!threads || n > 163840 ? 1 : n > 16384 ? 2 : 4));
             for (int32_t q : {1, 2, 4, 8}) {
                 p.qgrad_lanes = q;
                 CHECK(lskum_state_set_params(s, &p) == LSKUM_OK);
@@ -207,12 +216,61 @@ static void residual_form() {
     }
 }
 
+// The forms that a state's kernels are launched in.
+struct Forms {
+    int sweep_lanes, residual_lanes, sub, qgrad_lanes;
+    bool tiled, qgrad_tiled;
+    explicit Forms(const lskum::State& s)
+        : sweep_lanes(s.sweep_lanes), residual_lanes(s.residual_lanes),
+          sub(lskum::residual_form(s).sub), qgrad_lanes(s.qgrad_tiled ? 0 : s.qgrad_lanes),
+          tiled(lskum::residual_form(s).tiled), qgrad_tiled(s.qgrad_tiled) {}
+    bool sweep(const Forms& o) const { return sweep_lanes == o.sweep_lanes; }
+    bool residual(const Forms& o) const {
+        return residual_lanes == o.residual_lanes && sub == o.sub && tiled == o.tiled;
+    }
+    bool qgrad(const Forms& o) const {
+        return qgrad_tiled == o.qgrad_tiled && qgrad_lanes == o.qgrad_lanes;
+    }
+};
+
+// Where the forms that the library picks by itself are the fastest, tuning a
+// batch leaves it with them, and so do the reported values as parameters; where
+// another lane count is the fastest, that one is kept.
+static void autotune() {
+    for (int64_t n : {500, 9000, 20000, 50000, 100000}) {
+        lskum_cloud* c = chain(n);
+        const int32_t which[2] = {0, 0};
+        const double mach[2] = {0.5, 0.6}, aoa[2] = {0.0, 1.0};
+        for (int32_t fastest : {0, 1, 4}) {
+            lskum_params p = params();
+            p.sweep_lanes = p.residual_lanes = p.qgrad_lanes = fastest;
+            lskum_batch* b = nullptr;
+            CHECK(lskum_batch_create(1, &c, 2, which, mach, aoa, &p, nullptr, &b) == LSKUM_OK);
+            const Forms want(b->s);
+            residual_ms = [&](const lskum::State& s) { return Forms(s).residual(want) ? 1.0 : 1.5; };
+            sweep_ms = [&](const lskum::State& s) { return Forms(s).sweep(want) ? 1.0 : 1.5; };
+            qgrad_ms = [&](const lskum::State& s) { return Forms(s).qgrad(want) ? 1.0 : 1.5; };
+            CHECK(lskum_batch_autotune(b, 2, &p.sweep_lanes, &p.residual_lanes, &p.qgrad_lanes) ==
+                  LSKUM_OK);
+            const Forms tuned(b->s);
+            CHECK(tuned.sweep(want) && tuned.residual(want) && tuned.qgrad(want));
+            CHECK(lskum_batch_set_params(b, &p) == LSKUM_OK);
+            const Forms again(b->s);
+            CHECK(again.sweep(want) && again.residual(want) && again.qgrad(want));
+            residual_ms = sweep_ms = qgrad_ms = nullptr;
+            lskum_batch_destroy(b);
+        }
+        lskum_cloud_destroy(c);
+    }
+}
+
 int main(int argc, char** argv) {
     const std::string name = argc > 1 ? argv[1] : "";
     if (name == "concurrent_copies") concurrent_copies();
     else if (name == "other_device_current") other_device_current();
     else if (name == "short_lived_states") short_lived_states();
     else if (name == "residual_form") residual_form();
+    else if (name == "autotune") autotune();
     else return 2;
     return failures ? 1 : 0;
 }
