@@ -583,8 +583,7 @@ __device__ __forceinline__ double scatter_extreme(const double a[4], int lane) {
     return pick(odd ? x1 : x0, dpp<kDppXor1>(odd ? x0 : x1));
 }
 
-// S: stride of the staged arrays, at least the cloud's longest list (160 for
-// the 16 x 4 blocks of 5 x 5 stencils; kQTileMax otherwise).
+// S: stride of the staged arrays, at least the cloud's longest list (tile_stride).
 template <bool INNER, bool LIMIT, int S>
 __global__ void __launch_bounds__(kBlock, 4) k_qgrad_tiled(
     double K, const D2* __restrict__ xy, const int32_t* __restrict__ off,
@@ -2036,8 +2035,12 @@ static void qgrad_tiled(State& s, bool keep) {
 
 hipError_t launch_q_derivatives(State& s, bool keep_unlimited) {
     if (s.qgrad_tiled && s.cloud->ntile > 0) {
-        if (s.cloud->tile_hmax <= kTileStride) qgrad_tiled<kTileStride>(s, keep_unlimited);
-        else qgrad_tiled<kQTileMax>(s, keep_unlimited);
+        switch (tile_stride(s.cloud->tile_hmax)) {
+            case kTileStride: qgrad_tiled<kTileStride>(s, keep_unlimited); break;
+            case kTileStride4: qgrad_tiled<kTileStride4>(s, keep_unlimited); break;
+            case kTileStride3: qgrad_tiled<kTileStride3>(s, keep_unlimited); break;
+            default: qgrad_tiled<kQTileMax>(s, keep_unlimited);
+        }
         return hipGetLastError();
     }
     switch (s.qgrad_lanes) {

@@ -222,9 +222,21 @@ struct State {
     bool have_events = false;
 };
 
-// The usual stride of a tile's staged arrays: a 16 x 4 block of points with 5 x 5
-// stencils lists 160 points.
-constexpr int kTileStride = 160;
+// Strides of a tile's staged arrays, 112 bytes a listed point in the inner passes.
+// The usual one: a 16 x 4 block of points with 5 x 5 stencils lists 160 points.
+// Irregular clouds list more (174 to 489 with the 12 to 90 nearest neighbours along
+// a space-filling curve), and the longest strides with which four and three blocks
+// share a CU's 160 KB keep their wavefronts: q-derivatives of 300,000 points and
+// lists of up to 174 points 62 us with room for 512 (two blocks) and 49 us, 236
+// points 74 and 59 us, 389 points 134 and 116 us.
+constexpr int kTileStride = 160, kTileStride4 = 365, kTileStride3 = 480;
+
+// The stride for a cloud whose longest tile list has `longest` points.
+inline int tile_stride(int32_t longest) {
+    for (int s : {kTileStride, kTileStride4, kTileStride3})
+        if (longest <= s) return s;
+    return kQTileMax;
+}
 
 // Which residual kernel a state's launches take: LDS tiles or direct gathers,
 // and threads per lane.  Few tiles leave a launch as long as one lane's walk: four

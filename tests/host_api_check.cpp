@@ -216,6 +216,18 @@ static void residual_form() {
     }
 }
 
+// The staged arrays of a tile (112 bytes a listed point, LDS handed out by 1,280
+// bytes) take no blocks from a CU that the cloud's longest list leaves room for, of
+// the four that the kernels' registers allow.
+static void tile_strides() {
+    auto blocks = [](int points) { return std::min(4, 128 / ((112 * points + 1279) / 1280)); };
+    for (int h = 1; h <= lskum::kQTileMax; ++h) {
+        const int s = lskum::tile_stride(h);
+        CHECK(s >= h && s <= lskum::kQTileMax);
+        CHECK(blocks(s) == blocks(h));
+    }
+}
+
 // The forms that a state's kernels are launched in.
 struct Forms {
     int sweep_lanes, residual_lanes, sub, qgrad_lanes;
@@ -271,6 +283,7 @@ int main(int argc, char** argv) {
     else if (name == "short_lived_states") short_lived_states();
     else if (name == "residual_form") residual_form();
     else if (name == "autotune") autotune();
+    else if (name == "tile_strides") tile_strides();
     else return 2;
     return failures ? 1 : 0;
 }

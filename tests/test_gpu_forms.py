@@ -3,6 +3,7 @@ against those that it does: the same bits."""
 import numpy as np
 import pytest
 
+import oracle as O
 from paper_2406_07441_amd import cloudgen as cg
 
 pytestmark = pytest.mark.gpu
@@ -72,4 +73,34 @@ def test_residual_of_shuffled_points_bitwise(lk, nw, nk, kw):
     st = lk.State(lk.Cloud(s), 0.7, 2.0, prm)
     st.set_U(np.ascontiguousarray(U[:, perm]))
     assert np.isfinite(R).all() and np.array_equal(st.residual()[0], R[:, perm])
+    st.close()
+
+
+@pytest.mark.parametrize("limiter,inner", [(1, 0), (1, 2), (0, 1)])
+@pytest.mark.parametrize("r", [3, 4, 5, 6, 7])
+def test_q_derivatives_by_tile_stride(lk, r, limiter, inner):
+    """Box clouds with every point within r rows and columns as neighbour: tile
+    lists of 220, 288, 364, 448 and 540 points (up to 365, 480 and beyond what a
+    tile holds), against the oracle, the suite's bar of 1e-11."""
+    c = cg.box(40, 20, wall_bottom=True)
+    nx, ny = c.nw, c.nk
+    off, idx = [0], []
+    for p in range(c.n):
+        j, k = p % nx, p // nx
+        idx += [q * nx + i for q in range(max(0, k - r), min(ny, k + r + 1))
+                for i in range(max(0, j - r), min(nx, j + r + 1)) if q * nx + i != p]
+        off.append(len(idx))
+    c.nbr_off, c.nbr_idx = np.array(off, np.int32), np.array(idx, np.int32)
+    kw = dict(cfl=5.0, inner_iters=inner, limiter=limiter, limiter_k=5.0)
+    o = O.Oracle(c, mach=0.4, aoa_deg=5.0, **kw)
+    bump = np.stack([np.sin(2 * c.x + c.y), np.cos(c.x - 2 * c.y), np.sin(c.x * c.y), np.cos(3 * c.x)])
+    U = o.free_stream() * (1.0 + 0.05 * bump)
+    U[2, c.type == 0] = 0.0
+    st = lk.State(lk.Cloud(c), 0.4, 5.0, lk.default_params(**kw))
+    st.set_U(U)
+    got = (*st.q_derivatives(), st.residual()[0])
+    want = (*o.q_derivatives(O.q_from_U(U)), o.residual(U)[0])
+    errs = [max(np.abs(a[v] - b[v]).max() / np.abs(b[v]).max() for v in range(4))
+            for a, b in zip(got, want)]
+    assert np.isfinite(errs).all() and max(errs) < 1e-11, errs
     st.close()
