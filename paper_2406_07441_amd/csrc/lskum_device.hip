@@ -819,7 +819,11 @@ __device__ __forceinline__ D4 end_sum(const D4& q, const D2& t, double hwa, doub
 #pragma clang fp contract(off)
     const double beta = -0.5 * q.w;
     const double r = rsqrt_pos(beta);
-    const double r2 = r * r, i2b = 0.5 * r2;
+    // 1/beta, corrected: r^2 alone is off by up to 2 units in the last place, and
+    // velocity, density and pressure would all take that over
+    double r2 = r * r;
+    r2 = fma(r2, fma(-beta, r2, 1.0), r2);
+    const double i2b = 0.5 * r2;
     const double u1 = q.y * i2b, u2 = q.z * i2b;
     const double sb = beta * r;  // sqrt(beta)
     const double ua = FRAME ? fma(u1, t.x, u2 * t.y) : u1;
@@ -830,8 +834,9 @@ __device__ __forceinline__ D4 end_sum(const D4& q, const D2& t, double hwa, doub
     double era, ga, erb, gb;
     unit_or_outer(Sa, ta, lead, era, ga);
     unit_or_outer(Sb, tb, lead, erb, gb);
-    const double e = exp_lead(q.x + bu, lead);
-    const double rho = G14 ? e * (r2 * r2 * r) : e * exp(-inv_gm1 * log(beta));
+    const double lr = q.x + bu;  // log rho + log(beta)/(gamma - 1)
+    const double rho = G14 ? exp_lead(lr, lead) * (r2 * r2 * r)
+                           : exp_lead(fma(-inv_gm1, log(beta), lr), lead);
     return weighted_flux<FRAME>(rho, rho * i2b, r, u1, u2, ua, ub, bu, era, ga, erb, gb, t, hwa, hsa,
                                 hwb, hsb, inv_gm1);
 }
@@ -841,9 +846,16 @@ __device__ __forceinline__ D4 end_sum(const D4& q, const D2& t, double hwa, doub
 // flux differences of every split the neighbour lies in (x+-/y+- at interior
 // points, t+-/n- at a wall), weighted by the point's split coefficients.
 // A split that the neighbour is not in has weight zero.
-// q~ = q - (dx q_x + dy q_y)/2 from hx = -dx/2, hy = -dy/2 (eq. 15)
+// q~ = q - (dx q_x + dy q_y)/2 from hx = -dx/2, hy = -dy/2 (eq. 15).  G14 rounds
+// twice at q's magnitude, one instruction less per component: with the corrected
+// 1/beta of end_sum the residual is still nearer to its exact value than with one
+// rounding here and r^2 there.
+template <bool G14>
 __device__ __forceinline__ D4 reconstruct(const D4& q, const D4& gx, const D4& gy, double hx,
                                           double hy) {
+    if (!G14)
+        return {q.x + fma(hy, gy.x, hx * gx.x), q.y + fma(hy, gy.y, hx * gx.y),
+                q.z + fma(hy, gy.z, hx * gx.z), q.w + fma(hy, gy.w, hx * gx.w)};
     return {fma(hy, gy.x, fma(hx, gx.x, q.x)), fma(hy, gy.y, fma(hx, gx.y, q.y)),
             fma(hy, gy.z, fma(hx, gx.z, q.z)), fma(hy, gy.w, fma(hx, gx.w, q.w))};
 }
@@ -1243,8 +1255,8 @@ __global__ void __launch_bounds__(kBlock) k_residual(ResidualArgs A) {
             for (; e < e1; e += LANES) {
                 const double dx = nb.r.x - r0.x, dy = nb.r.y - r0.y;
                 const double hx = -0.5 * dx, hy = -0.5 * dy;
-                const D4 qti = reconstruct(nb.q, nb.gx, nb.gy, hx, hy);
-                const D4 qt0 = reconstruct(q0, gx0, gy0, hx, hy);
+                const D4 qti = reconstruct<G14>(nb.q, nb.gx, nb.gy, hx, hy);
+                const D4 qt0 = reconstruct<G14>(q0, gx0, gy0, hx, hy);
                 if (PIPE) {
                     nb = load_nbr(i_next, A.xy, A.q, A.qx, A.qy);
                     i_next = A.idx[min(e + 2 * LANES, last)];
@@ -1335,9 +1347,9 @@ __global__ void __launch_bounds__(kQTile * LANES * SUB) k_residual_tiled(Residua
                 li = lnbr[min(e + kStep + LANES * sub, e1 - 1)];  // the next entry's position
                 const double dx = r.x - r0.x, dy = r.y - r0.y;
                 const double hx = -0.5 * dx, hy = -0.5 * dy;
-                const D4 qti = reconstruct({qa.x, qa.y, qb.x, qb.y}, {xa.x, xa.y, xb.x, xb.y},
+                const D4 qti = reconstruct<G14>({qa.x, qa.y, qb.x, qb.y}, {xa.x, xa.y, xb.x, xb.y},
                                            {ya.x, ya.y, yb.x, yb.y}, hx, hy);
-                const D4 qt0 = reconstruct(q0, gx0, gy0, hx, hy);
+                const D4 qt0 = reconstruct<G14>(q0, gx0, gy0, hx, hy);
                 if constexpr (SUB == 1) {
                     pair_add<FRAME, G14>(dx, dy, qti, qt0, t, ty, coef, kQTile, inv_gm1, lead, R);
                 } else {
