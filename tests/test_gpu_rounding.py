@@ -1,6 +1,6 @@
-"""Rounding of the residual: its distance from the oracle evaluated in extended
-precision (the oracle's source with `long double` for `double`), against the
-distance of the oracle's own double precision."""
+"""Rounding of the residual and of flux-difference increments: their distance from
+the oracle evaluated in extended precision (the oracle's source with `long double`
+for `double`), against the distance of the oracle's own double precision."""
 import ctypes as C
 import os
 import re
@@ -44,27 +44,50 @@ def extended(tmp_path_factory):
                     str(d / "o.cpp"), "-o", str(d / "o.so")], check=True)
     L = C.CDLL(str(d / "o.so"))
     L.ora_residual.restype = C.c_int32
-    L.ora_residual.argtypes = [P] * 6
+    L.ora_residual.argtypes = L.ora_lusgs.argtypes = [P] * 6
+    L.ora_timestep_diag.argtypes = [P] * 5
+    L.ora_lusgs.restype = L.ora_timestep_diag.restype = None
     return L
 
 
-def _residual(L, c, U, mach, aoa, gamma, farfield):
-    xs = [np.ascontiguousarray(a, np.longdouble) for a in (c.x, c.y, c.tx, c.ty)]
-    col, nc = O.colour(c)
-    cloud = O._Cloud(c.n, *[a.ctypes.data for a in xs], c.type.ctypes.data, c.nbr_off.ctypes.data,
-                     c.nbr_idx.ctypes.data, col.ctypes.data, nc)
-    prm = _Params(gamma, 20.0, mach, aoa, 1, 0, 1, 0, 5.0, 0, farfield)
-    U, R, res = U.astype(np.longdouble), np.zeros((4, c.n), np.longdouble), np.zeros(1, np.longdouble)
-    assert L.ora_residual(C.byref(cloud), C.byref(prm), U.ctypes.data, R.ctypes.data,
-                          res.ctypes.data, None) == 0
-    return R
+class _Case:
+    """Cloud and parameters of the extended oracle."""
+
+    def __init__(self, c, mach, gamma=1.4, jvp_mode=0, farfield=0):
+        self.n = c.n
+        self.keep = [np.ascontiguousarray(a, np.longdouble) for a in (c.x, c.y, c.tx, c.ty)]
+        col, nc = O.colour(c)
+        self.keep += [c.type, c.nbr_off, c.nbr_idx, col]
+        self.cloud = O._Cloud(c.n, *[a.ctypes.data for a in self.keep], nc)
+        self.prm = _Params(gamma, 20.0, mach, 1.0, 1, jvp_mode, 1, 0, 5.0, 0, farfield)
+
+    def residual(self, L, U):
+        U, R = U.astype(np.longdouble), np.zeros((4, self.n), np.longdouble)
+        res = np.zeros(1, np.longdouble)
+        assert L.ora_residual(C.byref(self.cloud), C.byref(self.prm), U.ctypes.data, R.ctypes.data,
+                              res.ctypes.data, None) == 0
+        return R
+
+    def increment(self, L, U, R):
+        U, R = U.astype(np.longdouble), R.astype(np.longdouble)
+        dt, D, dU = (np.zeros(s, np.longdouble) for s in (self.n, self.n, (4, self.n)))
+        head = C.byref(self.cloud), C.byref(self.prm), U.ctypes.data
+        L.ora_timestep_diag(*head, dt.ctypes.data, D.ctypes.data)
+        L.ora_lusgs(*head, R.ctypes.data, D.ctypes.data, dU.ctypes.data)
+        return dU
+
+
+def _distance(a, exact):
+    """Per component, the median over points."""
+    d = np.abs(a.astype(np.longdouble) - exact) / np.abs(exact).max(axis=1, keepdims=True)
+    return np.median(d.astype(float), axis=1)
 
 
 @pytest.mark.parametrize("mach,gamma,farfield,bar", [
     (0.3, 1.4, 0, 1.5), (0.63, 1.4, 1, 1.5), (0.85, 1.4, 0, 1.5), (1.4, 1.4, 0, 1.5),
     (0.3, 1.3, 0, 1.1), (0.85, 1.3, 0, 1.1)])
 def test_residual_rounding(lk, extended, mach, gamma, farfield, bar):
-    """Median distance over points and components, after some iterations.  Separate
+    """Median distance over points, mean of the components, after some iterations.  Separate
     fluxes per split direction, from r = 1/sqrt(beta) with 1/beta = r^2 and the q~ sum
     rounded once, are 1.6 to 1.9 (gamma 1.4) and 1.0 to 1.1 (gamma 1.3, whose density
     takes log and exp as the oracle's does) times as far as the oracle: no more than
@@ -76,12 +99,38 @@ def test_residual_rounding(lk, extended, mach, gamma, farfield, bar):
     for _ in range(6 if mach < 1 else 2):
         U = o.iteration(U)[0]
     U = np.ascontiguousarray(U)
-    exact = _residual(extended, c, U, mach, 1.0, gamma, farfield)
+    exact = _Case(c, mach, gamma, farfield=farfield).residual(extended, U)
     st = lk.State(lk.Cloud(c), mach, 1.0, lk.default_params(**kw))
     st.set_U(U)
-    scale = np.abs(exact).max(axis=1, keepdims=True)
-    d = [float(np.median(np.abs(R.astype(np.longdouble) - exact) / scale))
-         for R in (st.residual()[0], o.residual(U)[0])]
+    d = [_distance(R, exact).mean() for R in (st.residual()[0], o.residual(U)[0])]
     st.close()
     print(f"M {mach} gamma {gamma}: {d[0]:.2e}, oracle {d[1]:.2e}: {d[0] / d[1]:.2f}")
     assert d[0] <= bar * d[1]
+
+
+def test_flux_difference_rounding(lk, extended):
+    """Energy component of one increment by flux differences, from the residual that
+    either side has itself: six states, mean ratio to the oracle's distance.  Separate
+    flux differences per split direction are 1.06 times as far."""
+    ratios = []
+    for c in (cg.ogrid(160, 40, r=1.1, jitter_p=0.04, seed=5), cg.ogrid(96, 30, r=1.15, t=0.1)):
+        gc = lk.Cloud(c)
+        for mach in (0.3, 0.63, 0.85):
+            kw = dict(cfl=20.0, inner_iters=1, limiter=1, limiter_k=5.0, jvp_mode=1)
+            o = O.Oracle(c, mach=mach, aoa_deg=1.0, **kw)
+            U = o.free_stream()
+            for _ in range(6):
+                U = o.iteration(U)[0]
+            U = np.ascontiguousarray(U)
+            st = lk.State(gc, mach, 1.0, lk.default_params(**kw))
+            st.set_U(U)
+            R, _ = st.residual()
+            st.set_U(U)
+            st.step()
+            case = _Case(c, mach, jvp_mode=1)
+            d = [_distance(dU, case.increment(extended, U, res))[3]
+                 for dU, res in ((st.get_dU(), R), (o.iteration(U)[2], o.residual(U)[0]))]
+            ratios.append(d[0] / d[1])
+            st.close()
+    print("ratios", np.round(ratios, 3))
+    assert np.exp(np.mean(np.log(ratios))) <= 1.07
