@@ -587,16 +587,17 @@ struct Adam {
 
 // The gradient from the blocks' partial sums: block b covers parameters
 // [64 b, 64 b + 64) with four thread groups, group g adding parts g, g + 4, ...
-// in order, the four group sums in group order (fixed throughout); the last
-// block adds the loss.  Into grad (may be NULL), and with STEP into an Adam
-// step of the parameters and their copies.
+// in order, the four group sums in group order (fixed throughout; in double
+// precision, rounded once: 8,192 rows are 256 parts, and in fp32 their sum was off
+// by 7e-8, with the same time); the last block adds the loss.  Into grad (may be
+// NULL), and with STEP into an Adam step of the parameters and their copies.
 template <bool STEP>
 __global__ void __launch_bounds__(256) k_grad_sum(int nparts, const float* __restrict__ part,
                                                   const double* __restrict__ loss_part,
                                                   float* __restrict__ grad,
                                                   double* __restrict__ loss, Adam A,
                                                   WeightCopies C) {
-    __shared__ float group[4][64];
+    __shared__ double group[4][64];
     const int j = threadIdx.x & 63, g = threadIdx.x >> 6;
     if (blockIdx.x == gridDim.x - 1) {
         if (g != 0) return;
@@ -607,14 +608,14 @@ __global__ void __launch_bounds__(256) k_grad_sum(int nparts, const float* __res
         return;
     }
     const int k = blockIdx.x * 64 + j;
-    float s = 0.0f;
+    double s = 0.0;
     if (k < kParams)
 #pragma unroll 8
         for (int b = g; b < nparts; b += 4) s += part[(int64_t)b * kParams + k];
     group[g][j] = s;
     __syncthreads();
     if (g != 0 || k >= kParams) return;
-    const float gk = ((group[0][j] + group[1][j]) + group[2][j]) + group[3][j];
+    const float gk = (float)(((group[0][j] + group[1][j]) + group[2][j]) + group[3][j]);
     if (grad) grad[k] = gk;
     if (STEP) {
         const float mk = A.b1 * A.m[k] + (1.0f - A.b1) * gk;
