@@ -46,29 +46,29 @@ __device__ __forceinline__ float gelu_prime(float z) {
 typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
 
 // Phi(-a) for a >= 0 (the normal CDF's lower half) as 2^P(a), P a degree-10
-// fit of log2 Phi(-a) on [0, 6], minimax in the error of a Phi(-a) where a
-// exceeds 1.5 and in the relative error below; beyond 6, P falls on and 2^P is
-// below 1e-9.  (Degree 9 turns upwards there.)
+// fit of log2 Phi(-a) on [0, 6] (gen_lskum_gelu.py), minimax in the error of
+// Phi(-a); beyond 6, P falls on and 2^P is below 1e-9.  (Degree 9 turns upwards there.)
 __device__ __forceinline__ float phi_lower(float a) {
-    float p = -2.508991770e-08f;
-    p = fmaf(p, a, 7.670555533e-07f);
-    p = fmaf(p, a, -1.002338104e-05f);
-    p = fmaf(p, a, 7.115060725e-05f);
-    p = fmaf(p, a, -2.618829894e-04f);
-    p = fmaf(p, a, -3.622323129e-05f);
-    p = fmaf(p, a, 6.990640890e-03f);
-    p = fmaf(p, a, -5.247051269e-02f);
-    p = fmaf(p, a, -4.592113495e-01f);
-    p = fmaf(p, a, -1.151105285e+00f);
-    p = fmaf(p, a, -1.0f);
+    float p = -6.841560207e-08f;
+    p = fmaf(p, a, 1.628766199e-06f);
+    p = fmaf(p, a, -1.707519550e-05f);
+    p = fmaf(p, a, 1.021452845e-04f);
+    p = fmaf(p, a, -3.417893604e-04f);
+    p = fmaf(p, a, 8.748981782e-05f);
+    p = fmaf(p, a, 6.877615582e-03f);
+    p = fmaf(p, a, -5.241313577e-02f);
+    p = fmaf(p, a, -4.592256248e-01f);
+    p = fmaf(p, a, -1.151103973e+00f);
+    p = fmaf(p, a, -1.000000000e+00f);
     return __builtin_amdgcn_exp2f(p);
 }
 
 // bf16(gelu(z)) of four values, mostly without erff but with its bits:
-// max(z, 0) - |z| Phi(-|z|) is within 1.8e-7 |z| of gelu(z) (the largest
-// difference over all floats is 1.763e-7 |z|), so where both ends of that
-// interval round to the same bf16, gelu(z) does too.  Elsewhere (one value in
-// 10,000 at z = 1, in 300 at z = -2, all below -5 or so) the lane takes gelu
+// max(z, 0) - |z| Phi(-|z|) is within 1.8e-7 |z| of gelu(z) (with the fit above, and
+// erff and 2^P rounded correctly, at most 1.48e-7 |z| over the floats), so where both
+// ends of that interval round to the same bf16, gelu(z) does too; every float from
+// 1e-30 to 1e30 gives erff's bits.  Elsewhere (one value in 10,000 at z = 1, in 300 at
+// z = -2, all below -5 or so) the lane takes gelu
 // itself, and so does the whole wave where no |z| exceeds kNear: there erff
 // is the quicker one (1,000,003 rows: 221 against 257 us; with inputs that
 // spread z beyond, 297 against 260 us).  |z| is bounded at 1e4 in the interval,
