@@ -68,24 +68,25 @@ __device__ __forceinline__ float phi_lower(float a) {
 // erff and 2^P rounded correctly, at most 1.48e-7 |z| over the floats), so where both
 // ends of that interval round to the same bf16, gelu(z) does too; every float from
 // 1e-30 to 1e30 gives erff's bits.  Elsewhere (one value in 10,000 at z = 1, in 300 at
-// z = -2, all below -5 or so) the lane takes gelu
-// itself, and so does the whole wave where no |z| exceeds kNear: there erff
-// is the quicker one (1,000,003 rows: 221 against 257 us; with inputs that
-// spread z beyond, 297 against 260 us).  |z| is bounded at 1e4 in the interval,
-// so that infinities have one; NaNs pass through Phi.  (Zeros may differ in sign.)
-// (Medians in place of maximum and minimum: those functions would first bring
-// their operands to a canonical form, two instructions more.)
+// z = -2, all below -5 or so) the lane takes gelu itself.  So does the whole wave
+// where no |z| exceeds kNear, since there erff is the quicker one (1,000,003 rows: 221
+// against 257 us; with inputs that spread z beyond, 297 against 260 us), and
+// where one exceeds kFar: some lane's fit would settle nothing, and the wave pay for
+// both (1,000,003 rows, weights and inputs three times the initial ones: 512 us, with
+// this rule 378, with erff throughout 372).  Infinities are beyond kFar, and NaNs
+// pass through Phi.  (Zeros may differ in sign.  A median in place of the maximum
+// with zero: that function would first bring its operand to a canonical form.)
 __device__ __forceinline__ bf16x4 gelu_bf16(const f32x4& z) {
-    constexpr float kDiff = 1.8e-7f, kNear = 1.4f;
+    constexpr float kDiff = 1.8e-7f, kNear = 1.4f, kFar = 4.0f;
     bf16x4 up, down;
     const float far = fmaxf(fmaxf(fabsf(z[0]), fabsf(z[1])), fmaxf(fabsf(z[2]), fabsf(z[3])));
     bool exact = true;
-    if (__any(far > kNear)) {
+    if (__any(far > kNear) && !__any(far > kFar)) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const float relu = __builtin_amdgcn_fmed3f(z[k], 0.0f, __builtin_inff());
-            const float a = __builtin_amdgcn_fmed3f(fabsf(z[k]), 0.0f, 1e4f);
-            const float v = fmaf(-a, phi_lower(fabsf(z[k])), relu);
+            const float a = fabsf(z[k]);
+            const float v = fmaf(-a, phi_lower(a), relu);
             up[k] = (__bf16)fmaf(kDiff, a, v);
             down[k] = (__bf16)fmaf(-kDiff, a, v);
         }
