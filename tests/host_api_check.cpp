@@ -276,6 +276,49 @@ static void autotune() {
     }
 }
 
+// The runs of a wall of 70 points (two of 32 and one of 6): boxes, coordinates and
+// offsets, in one copy to the device.
+static void wall_runs() {
+    const int64_t n = 140, nwall = 70;
+    auto make = [&](int64_t walls) {
+        std::vector<double> x(n), y(n), tx(n, 1.0), ty(n, 0.0);
+        std::vector<int8_t> type(n, 1);
+        std::vector<int32_t> off(1, 0), idx;
+        for (int64_t p = 0; p < n; ++p) {
+            x[p] = std::cos(0.05 * (double)p);
+            y[p] = std::sin(0.05 * (double)p);
+            if (p < walls) type[p] = 0;
+            if (p) idx.push_back((int32_t)p - 1);
+            if (p + 1 < n) idx.push_back((int32_t)p + 1);
+            off.push_back((int32_t)idx.size());
+        }
+        lskum_cloud* c = nullptr;
+        CHECK(lskum_cloud_create(n, x.data(), y.data(), type.data(), tx.data(), ty.data(),
+                                 off.data(), idx.data(), nullptr, &c) == LSKUM_OK);
+        return c;
+    };
+    int before = fake::device_copies;
+    lskum_cloud* none = make(0);
+    const int without = fake::device_copies - before;
+    before = fake::device_copies;
+    lskum_cloud* c = make(nwall);
+    CHECK(fake::device_copies - before <= without + 1);  // the list of wall points
+    CHECK(none->c.wall_run_off[1] == 0);
+    const lskum::Cloud& w = c->c;
+    CHECK(w.wall_run_off[0] == 0 && w.wall_run_off[1] == 3);
+    CHECK((void*)w.wall_xy == (void*)(w.wall_box + 3));
+    for (int r = 0; r < 3; ++r)
+        for (int k = 0; k < lskum::kWallRun; ++k) {
+            const int64_t p = std::min<int64_t>(r * lskum::kWallRun + k, nwall - 1);
+            const lskum::D2 q = w.wall_xy[r * lskum::kWallRun + k];
+            const lskum::D4 b = w.wall_box[r];
+            CHECK(q.x == w.h_x[p] && q.y == w.h_y[p]);
+            CHECK(b.x <= q.x && q.x <= b.y && b.z <= q.y && q.y <= b.w);
+        }
+    lskum_cloud_destroy(c);
+    lskum_cloud_destroy(none);
+}
+
 int main(int argc, char** argv) {
     const std::string name = argc > 1 ? argv[1] : "";
     if (name == "concurrent_copies") concurrent_copies();
@@ -284,6 +327,7 @@ int main(int argc, char** argv) {
     else if (name == "residual_form") residual_form();
     else if (name == "autotune") autotune();
     else if (name == "tile_strides") tile_strides();
+    else if (name == "wall_runs") wall_runs();
     else return 2;
     return failures ? 1 : 0;
 }

@@ -37,7 +37,7 @@ typedef FakeGraph* hipGraphExec_t;
 namespace fake {
 inline thread_local int device = 0;               // current device of the thread
 inline std::atomic<int> pinned_allocs{0}, pinned_live{0}, events_live{0}, foreign_events{0};
-inline std::atomic<int> event_records{0};
+inline std::atomic<int> event_records{0}, device_copies{0};
 inline double now_ms = 0.0;                       // time of the timed work
 inline std::function<void()> on_wait;             // before a wait for an event returns
 }  // namespace fake
@@ -60,7 +60,8 @@ inline hipError_t hipHostFree(void* p) {
     if (p) --fake::pinned_live;
     return hipFree(p);
 }
-inline hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) {
+inline hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind k) {
+    if (k == hipMemcpyHostToDevice) ++fake::device_copies;
     std::memcpy(d, s, n);
     return hipSuccess;
 }
