@@ -7,7 +7,8 @@
   erf: for |x| < 1,  erf(x) = x P(x^2),
        P(t) = erf(sqrt t)/sqrt t on [0, 1] of degree 11 (fit error 7.4e-18);
   exp(-t) for 0 <= t < 1 without a range reduction: E(t - 1/2),
-       E(u) = e^(-u - 1/2) on |u| <= 1/2 of degree 12 (fit error 3.0e-18);
+       E(u) = e^(-u) on |u| <= 1/2 of degree 12, of which the callers take
+       e^(-1/2) (fit error 5.0e-18, of exp(-t) 3.0e-18);
   erf for 1 <= |x|: sign(x) (1 - e^(-x^2) W(v)), v = (|x| - 3)/(|x| + 3),
        W(v) = erfcx(|x|) on 1 <= |x| <= 6 of degree 14 (fit error 1.0e-17).
 

@@ -93,13 +93,11 @@ __device__ __forceinline__ Prim prim_from_q(const D4& q, double inv_gm1, bool g1
     return w;
 }
 
-// Kinetic split flux G_d^sg of a primitive state (half-range moments of the
-// Maxwellian, eq. 3-6): DIR 0 = x, 1 = y, 2 = unit direction (dx, dy).
-template <int DIR>
+// Kinetic split flux G_d^sg of a primitive state along the unit direction (dx, dy)
+// (half-range moments of the Maxwellian, eq. 3-6).
 __device__ __forceinline__ void split_flux(const Prim& w, double dx, double dy, double sg,
-                                           double inv_gm1, double G[4]) {
-    (void)inv_gm1;
-    const double ud = DIR == 0 ? w.u1 : (DIR == 1 ? w.u2 : w.u1 * dx + w.u2 * dy);
+                                           double G[4]) {
+    const double ud = w.u1 * dx + w.u2 * dy;
     const double S = ud * w.sb;
     double er, g;
     erf_exp(S, er, g);
@@ -108,16 +106,8 @@ __device__ __forceinline__ void split_flux(const Prim& w, double dx, double dy, 
     const double mass = w.rho * (ud * A + sg * B);
     const double pA = w.p * A;
     G[0] = mass;
-    if (DIR == 0) {
-        G[1] = pA + w.u1 * mass;
-        G[2] = w.u2 * mass;
-    } else if (DIR == 1) {
-        G[1] = w.u1 * mass;
-        G[2] = pA + w.u2 * mass;
-    } else {
-        G[1] = pA * dx + w.u1 * mass;
-        G[2] = pA * dy + w.u2 * mass;
-    }
+    G[1] = pA * dx + w.u1 * mass;
+    G[2] = pA * dy + w.u2 * mass;
     G[3] = (w.rhoE + w.p) * ud * A + sg * (w.rhoE + 0.5 * w.p) * B;
 }
 
@@ -753,19 +743,6 @@ __device__ __forceinline__ Nbr load_nbr(int32_t i, const D2* __restrict__ xy,
     return {xy[i], q[i], qx[i], qy[i]};
 }
 
-// One end of a stencil pair: the weighted sum of its split fluxes along the
-// two split directions of the point,
-//   sum_d w_d G_d^{sg_d},   d = x, y (interior) or t, n (frame points),
-// from a reconstructed q vector.  The primitive state is that of prim_from_q;
-// with A_d = (1 + sg_d erf S_d)/2, B_d = exp(-S_d^2)/(2 sqrt(pi beta)) and
-//   P = sum_d w_d u_d A_d,   Q = sum_d w_d sg_d B_d,   F = P + Q,
-// the mass term is rho F, the momentum term sum_d w_d p A_d d + u rho F and
-// the energy term (rhoE + p) P + (rhoE + p/2) Q = p ((1/(gamma-1) + 1/2 +
-// beta |u|^2) F + P/2), since rhoE = p (1/(gamma-1) + beta |u|^2).  The two
-// directions share everything but A, B: 18 instructions after the functions
-// where two separate fluxes took about 60.  hw_d = w_d/2 and hs_d = sg_d w_d/2.
-// Written in explicit fused steps with contraction off, so that both ends of a
-// pair round alike (a uniform field's residual is exactly zero).
 // 1/sqrt(x) for x > 0; for x <= 0, infinite or NaN the split fluxes end as NaN
 // with this as with a guarded function, so it has no guard (four instructions
 // fewer of ten).
@@ -796,8 +773,21 @@ __device__ __forceinline__ void unit_or_outer(double S, double t, const PolyLead
     }
 }
 
-// The energy term from beta |u|^2, or (RHO_E) from rho E where the state has it:
-// (rho E + p/2) F + p P/2.
+// One end of a stencil pair: the weighted sum of its split fluxes along the
+// two split directions of the point,
+//   sum_d w_d G_d^{sg_d},   d = x, y (interior) or t, n (frame points),
+// from a reconstructed q vector.  The primitive state is that of prim_from_q;
+// with A_d = (1 + sg_d erf S_d)/2, B_d = exp(-S_d^2)/(2 sqrt(pi beta)) and
+//   P = sum_d w_d u_d A_d,   Q = sum_d w_d sg_d B_d,   F = P + Q,
+// the mass term is rho F, the momentum term sum_d w_d p A_d d + u rho F and
+// the energy term (rhoE + p) P + (rhoE + p/2) Q = p ((1/(gamma-1) + 1/2 +
+// beta |u|^2) F + P/2), since rhoE = p (1/(gamma-1) + beta |u|^2).  The two
+// directions share everything but A, B: 18 instructions after the functions
+// where two separate fluxes took about 60.  hw_d = w_d/2 and hs_d = sg_d w_d/2.
+// Written in explicit fused steps with contraction off, so that both ends of a
+// pair round alike (a uniform field's residual is exactly zero).
+// The energy term from beta |u|^2 (from a q vector), or with RHO_E from rho E (of a
+// conserved state): (rho E + p/2) F + p P/2.
 template <bool FRAME, bool RHO_E>
 __device__ __forceinline__ D4 weighted_flux(double rho, double p, double r, double u1, double u2,
                                             double ua, double ub, double en, double era, double ga,
@@ -844,11 +834,6 @@ __device__ __forceinline__ D4 end_sum(const D4& q, const D2& t, double hwa, doub
                                 hwb, hsb, inv_gm1);
 }
 
-// One (point, neighbour) pair of the residual sum (eq. 11): the q~
-// reconstructions at both ends (eq. 15), their primitive states and the split
-// flux differences of every split the neighbour lies in (x+-/y+- at interior
-// points, t+-/n- at a wall), weighted by the point's split coefficients.
-// A split that the neighbour is not in has weight zero.
 // q~ = q - (dx q_x + dy q_y)/2 from hx = -dx/2, hy = -dy/2 (eq. 15).  G14 rounds
 // twice at q's magnitude, one instruction less per component: with the corrected
 // 1/beta of end_sum the residual is still nearer to its exact value than with one
@@ -908,8 +893,11 @@ struct ResidualSum {
     bool bad;
 };
 
-// The pair (point, neighbour at offset (dx, dy)) added to R; coef[k * stride]
-// is the point's split coefficient k.
+// One (point, neighbour) pair of the residual sum (eq. 11), added to R: from the q~
+// at both ends their primitive states and the split flux differences of every split
+// the neighbour at offset (dx, dy) lies in (x+-/y+- at interior points, t+-/n- at a
+// wall), weighted by the point's split coefficients coef[k * stride].  A split that
+// the neighbour is not in has weight zero.
 template <bool FRAME, bool G14>
 __device__ __forceinline__ void pair_add(double dx, double dy, const D4& qti, const D4& qt0,
                                          const D2& t, int8_t ty, const D2* coef, int stride,
@@ -1059,8 +1047,8 @@ __device__ __forceinline__ void residual_finish(int64_t p, int8_t ty, const Resi
         wf.rhoE = wf.p * inv_gm1 + 0.5 * (v1 * v1 + v2 * v2);
         const Prim w0 = prim_from_q(gload(A.q, p), inv_gm1, g14);
         double Gf[4], G0[4];
-        split_flux<2>(wf, -t.y, t.x, -1.0, inv_gm1, Gf);
-        split_flux<2>(w0, -t.y, t.x, -1.0, inv_gm1, G0);
+        split_flux(wf, -t.y, t.x, -1.0, Gf);
+        split_flux(w0, -t.y, t.x, -1.0, G0);
         const double ih = 1.0 / gload(A.lsq, p).w;
 #pragma unroll
         for (int v = 0; v < 4; ++v) Rp[v] += (Gf[v] - G0[v]) * ih;
@@ -1178,7 +1166,7 @@ __device__ __forceinline__ void residual_finish(int64_t p, int8_t ty, const Resi
     }
     // the forward sweep's first colour phase: its points have no lower
     // neighbours, dU* = -R / D (R - S for the Manish variant), in the
-    // sweep precision and with the sweep kernel's arithmetic
+    // sweep precision, by the reciprocal of D
     if (A.sweep0 && gload(A.colour, p) == 0) {
         double rs[4] = {Rp[0], Rp[1], Rp[2], Rp[3]};
         if (A.variant != 0) {
@@ -1218,8 +1206,8 @@ __device__ __forceinline__ void residual_finish(int64_t p, int8_t ty, const Resi
     if (bad || !(rho > 0.0) || !(pr > 0.0)) gstore(A.flags, 0, 1);
 }
 
-// Direct gathers, for clouds without tiles.  LANES consecutive lanes share one
-// point: each takes every LANES-th neighbour, the four residual sums are
+// Direct gathers, where residual_form does not take tiles.  LANES consecutive lanes
+// share one point: each takes every LANES-th neighbour, the four residual sums are
 // combined with cross-lane shuffles and the first lane finishes the point.
 // Software pipeline (interior points, gamma 1.4): neighbour indices two
 // entries ahead; the next neighbour's data is requested as soon as this one's
@@ -2369,15 +2357,6 @@ hipError_t launch_residual_out(State& s, double* R, double* out) {
     const int64_t n = R ? s.cloud->n : 0;
     hipLaunchKernelGGL(k_residual_out, dim3(std::max(grid_for(n), 1u)), dim3(kBlock), 0, s.stream, n,
                        s.R, s.res_hist, s.flags, R, out);
-    return hipGetLastError();
-}
-
-__global__ void k_copy_flag(const int32_t* __restrict__ src, int32_t* __restrict__ dst) {
-    if (threadIdx.x == 0) dst[0] = src[0];
-}
-
-hipError_t launch_copy_flag(const int32_t* src, int32_t* dst, hipStream_t st) {
-    hipLaunchKernelGGL(k_copy_flag, dim3(1), dim3(64), 0, st, src, dst);
     return hipGetLastError();
 }
 

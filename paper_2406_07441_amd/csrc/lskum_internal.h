@@ -306,11 +306,8 @@ hipError_t clear_increment(State& s, int64_t p0, int64_t n);
 // every component's CFL number to params.cfl
 hipError_t reset_cfl(State& s);
 
-// fill n doubles with v, and copy one int32 (kernels, so that graph capture
-// records no memset node)
-hipError_t launch_copy_flag(const int32_t* src, int32_t* dst, hipStream_t st);
-// out[0] = res[0], out[1] = 1 if flags[0] is set else 0
-// First and last launches of the allocation-free residual (R may be NULL).
+// First and last launches of the allocation-free residual: R (may be NULL) as
+// components, out[0] = the norm, out[1] = 1 if flags[0] is set else 0.
 hipError_t launch_scratch_begin(State& s, double v1, double v2, const double* U);
 hipError_t launch_residual_out(State& s, double* R, double* out);
 
