@@ -752,6 +752,18 @@ __device__ __forceinline__ double rsqrt_pos(double x) {
     return fma(y * e, fma(e, 0.375, 0.5), y);
 }
 
+// 1/sqrt(x) and, in r2, 1/x: both from the seed y and e = 1 - x y^2, where e is that
+// of the rounded y^2, so 1/x = y^2/(1 - e) is within one unit in the last place.
+// (The square of the first is off by up to 2, and velocity, density and pressure
+// would all take that over.)
+__device__ __forceinline__ double rsqrt_recip_pos(double x, double& r2) {
+    const double y = __builtin_amdgcn_rsq(x);
+    const double y2 = y * y;
+    const double e = fma(-x, y2, 1.0);
+    r2 = fma(y2, fma(e, e, e), y2);
+    return fma(y * e, fma(e, 0.375, 0.5), y);
+}
+
 // v for s < 0, -v for s > 0 (the sign of the split that offset s lies in)
 __device__ __forceinline__ double flip_by(double v, double s) {
     const uint64_t sign = (uint64_t)1 << 63;
@@ -811,12 +823,8 @@ __device__ __forceinline__ D4 end_sum(const D4& q, const D2& t, double hwa, doub
                                       const PolyLead& lead) {
 #pragma clang fp contract(off)
     const double beta = -0.5 * q.w;
-    const double r = rsqrt_pos(beta);
-    // 1/beta, corrected: r^2 alone is off by up to 2 units in the last place, and
-    // velocity, density and pressure would all take that over
-    double r2 = r * r;
-    r2 = fma(r2, fma(-beta, r2, 1.0), r2);
-    const double i2b = 0.5 * r2;
+    double r2;
+    const double r = rsqrt_recip_pos(beta, r2), i2b = 0.5 * r2;
     const double u1 = q.y * i2b, u2 = q.z * i2b;
     const double sb = beta * r;  // sqrt(beta)
     const double ua = FRAME ? fma(u1, t.x, u2 * t.y) : u1;
