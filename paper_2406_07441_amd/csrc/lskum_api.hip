@@ -17,6 +17,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <string>
@@ -597,9 +598,10 @@ public:
         if (busy) (void)hipStreamSynchronize(s_.stream);
         give_slots(slot_pool(s_.cloud->device), h_);
     }
-    int take() {
-        HIPCHK(device_.enter(s_.cloud->device));
-        if (take_slots(slot_pool(s_.cloud->device), points(), h_)) return LSKUM_OK;
+    // False if there is no pinned memory to be had.
+    bool take() {
+        if (device_.enter(s_.cloud->device) != hipSuccess) return false;
+        if (take_slots(slot_pool(s_.cloud->device), points(), h_)) return true;
         HostSlots h;
         h.points = points();
         hipError_t e = hipSuccess;
@@ -611,10 +613,11 @@ public:
                               hipHostMallocCoherent);
         if (e != hipSuccess) {
             free_slots(h);
-            return hip_fail(e, "pinned memory for host fields");
+            (void)hipGetLastError();
+            return false;
         }
         h_ = h;
-        return LSKUM_OK;
+        return true;
     }
     int64_t points() const { return std::min(s_.cloud->n, kSlotPoints); }
     double* slot(int64_t chunk) const { return h_.mem + chunk % kSlots * 4 * points(); }
@@ -626,6 +629,32 @@ private:
     lskum::State& s_;
     HostSlots h_;
 };
+
+// Where memory cannot be pinned: one copy through pageable memory of the field's
+// size, transposed on the host.
+template <class V>
+int copy_out_pageable(lskum::State& s, const V* src, int64_t n, double* dst) {
+    std::unique_ptr<V[]> h(new (std::nothrow) V[n]);
+    if (!h) return fail(LSKUM_ERR_OOM, "host memory for a field");
+    HIPCHK(hipMemcpyAsync(h.get(), src, n * sizeof(V), hipMemcpyDeviceToHost, s.stream));
+    HIPCHK(hipStreamSynchronize(s.stream));
+    for (int64_t p = 0; p < n; ++p) {
+        dst[p] = h[p].x;
+        dst[n + p] = h[p].y;
+        dst[2 * n + p] = h[p].z;
+        dst[3 * n + p] = h[p].w;
+    }
+    return LSKUM_OK;
+}
+
+int copy_in_pageable(lskum::State& s, const double* U, int64_t n, lskum::D4* dst) {
+    std::unique_ptr<lskum::D4[]> h(new (std::nothrow) lskum::D4[n]);
+    if (!h) return fail(LSKUM_ERR_OOM, "host memory for a field");
+    for (int64_t p = 0; p < n; ++p) h[p] = {U[p], U[n + p], U[2 * n + p], U[3 * n + p]};
+    HIPCHK(hipMemcpyAsync(dst, h.get(), n * sizeof(lskum::D4), hipMemcpyHostToDevice, s.stream));
+    HIPCHK(hipStreamSynchronize(s.stream));
+    return LSKUM_OK;
+}
 
 template <class V>
 int copy_field_out(lskum::State& s, const V* src, int64_t p0, int64_t n, double* dst,
@@ -642,7 +671,7 @@ int copy_field_out(lskum::State& s, const V* src, int64_t p0, int64_t n, double*
         return LSKUM_OK;
     }
     SlotLease lease(s);
-    if (int r = lease.take()) return r;
+    if (!lease.take()) return copy_out_pageable(s, src + p0, n, dst);
     lease.busy = true;
     const int64_t size = lease.points(), nchunk = (n + size - 1) / size;
     for (int64_t k = 0; k < nchunk + kSlots; ++k) {
@@ -670,7 +699,7 @@ int copy_U_in(lskum::State& s, const double* U, int64_t p0, int64_t n, int on_de
         HIPCHK(lskum::launch_soa_to_aos(U, s.U + p0, n, s.stream));
         return LSKUM_OK;
     }
-    if (int r = lease.take()) return r;
+    if (!lease.take()) return copy_in_pageable(s, U, n, s.U + p0);
     lease.busy = true;
     const int64_t size = lease.points(), nchunk = (n + size - 1) / size;
     for (int64_t c = 0; c < nchunk; ++c) {

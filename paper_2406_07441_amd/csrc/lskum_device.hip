@@ -1283,10 +1283,11 @@ __global__ void __launch_bounds__(kBlock) k_residual(ResidualArgs A) {
 // pairs of its walk together and add them in the walk's order.  The lanes' sums
 // meet in LDS, and the first wavefront finishes the tile's points, one per lane.
 // The arithmetic and the order of the sums are those of k_residual.
-// Bound by vector instruction issue: about 260 per pair after sharing the two
-// directions' work (end_sum), 430 before.  2,621,440 points, two lanes per
-// point: 854 us with separate fluxes per direction, 617 us now (FP64); a bound
-// of four wavefronts per SIMD spills 56 bytes and takes 1,055 us.
+// Bound by vector instruction issue: about 280 per pair in the loop and 300 with
+// staging and the points' ends, after sharing the two directions' work (end_sum), 430
+// before.  2,621,440 points, two lanes per point: 854 us with separate fluxes per
+// direction, 615 us now (FP64); a bound of four wavefronts per SIMD spills 56 bytes
+// and takes 1,055 us.
 template <bool MIXED, int LANES, int S, int SUB>
 __global__ void __launch_bounds__(kQTile * LANES * SUB) k_residual_tiled(ResidualArgs A) {
     __shared__ D2 s_nb[7 * S];  // (x, y), q, q_x, q_y in pairs of components

@@ -190,6 +190,28 @@ static void short_lived_states() {
     CHECK(fake::events_live == 0);
 }
 
+// Where no memory can be pinned, fields cross all the same, and the failed attempt
+// is not reported by a later launch.
+static void nothing_to_pin() {
+    fake::no_pinned = true;
+    for (int64_t n : {100, 40000}) {
+        lskum_cloud* c = chain(n);
+        const lskum_params p = params();
+        lskum_state* s = nullptr;
+        CHECK(lskum_state_create(c, 0.5, 0.0, &p, nullptr, &s) == LSKUM_OK);
+        const std::vector<double> U = field(n, 1.0);
+        std::vector<double> got(4 * n);
+        CHECK(lskum_state_set_U(s, U.data(), 0) == LSKUM_OK);
+        CHECK(lskum_state_get_U(s, got.data(), 0) == LSKUM_OK);
+        CHECK(got == U);
+        CHECK(fake::last_error == 0);
+        lskum_state_destroy(s);
+        lskum_cloud_destroy(c);
+    }
+    CHECK(fake::events_live == 0);
+    fake::no_pinned = false;
+}
+
 // The lanes of the q-derivative passes leave the residual's form alone; so does
 // asking for the two lanes that the library takes by itself.
 static void residual_form() {
@@ -324,6 +346,7 @@ int main(int argc, char** argv) {
     if (name == "concurrent_copies") concurrent_copies();
     else if (name == "other_device_current") other_device_current();
     else if (name == "short_lived_states") short_lived_states();
+    else if (name == "nothing_to_pin") nothing_to_pin();
     else if (name == "residual_form") residual_form();
     else if (name == "autotune") autotune();
     else if (name == "tile_strides") tile_strides();

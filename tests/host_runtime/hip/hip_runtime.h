@@ -38,12 +38,14 @@ namespace fake {
 inline thread_local int device = 0;               // current device of the thread
 inline std::atomic<int> pinned_allocs{0}, pinned_live{0}, events_live{0}, foreign_events{0};
 inline std::atomic<int> event_records{0}, device_copies{0};
+inline bool no_pinned = false;                    // hipHostMalloc fails
+inline std::atomic<int> last_error{0};
 inline double now_ms = 0.0;                       // time of the timed work
 inline std::function<void()> on_wait;             // before a wait for an event returns
 }  // namespace fake
 
 inline const char* hipGetErrorString(hipError_t e) { return e == hipSuccess ? "success" : "error"; }
-inline hipError_t hipGetLastError() { return hipSuccess; }
+inline hipError_t hipGetLastError() { return (hipError_t)fake::last_error.exchange(0); }
 inline hipError_t hipGetDevice(int* d) { *d = fake::device; return hipSuccess; }
 inline hipError_t hipSetDevice(int d) { fake::device = d; return hipSuccess; }
 inline hipError_t hipMalloc(void** p, size_t n) {
@@ -52,6 +54,10 @@ inline hipError_t hipMalloc(void** p, size_t n) {
 }
 inline hipError_t hipFree(void* p) { std::free(p); return hipSuccess; }
 inline hipError_t hipHostMalloc(void** p, size_t n, unsigned) {
+    if (fake::no_pinned) {
+        fake::last_error = hipErrorOutOfMemory;
+        return hipErrorOutOfMemory;
+    }
     ++fake::pinned_allocs;
     ++fake::pinned_live;
     return hipMalloc(p, n);

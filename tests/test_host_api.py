@@ -25,7 +25,7 @@ def harness():
 
 
 @pytest.mark.parametrize("name", ["concurrent_copies", "other_device_current", "short_lived_states",
-                                  "residual_form", "autotune", "tile_strides", "wall_runs"])
+                                  "nothing_to_pin", "residual_form", "autotune", "tile_strides", "wall_runs"])
 def test_host_api(harness, name):
     r = subprocess.run([harness, name], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stderr
