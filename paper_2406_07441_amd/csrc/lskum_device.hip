@@ -1283,7 +1283,7 @@ __global__ void __launch_bounds__(kBlock) k_residual(ResidualArgs A) {
 // pairs of its walk together and add them in the walk's order.  The lanes' sums
 // meet in LDS, and the first wavefront finishes the tile's points, one per lane.
 // The arithmetic and the order of the sums are those of k_residual.
-// Bound by vector instruction issue: about 280 per pair in the loop and 300 with
+// Bound by vector instruction issue: about 280 per pair in the loop and 310 with
 // staging and the points' ends, after sharing the two directions' work (end_sum), 430
 // before.  2,621,440 points, two lanes per point: 854 us with separate fluxes per
 // direction, 615 us now (FP64); a bound of four wavefronts per SIMD spills 56 bytes
