@@ -326,7 +326,8 @@ int lskum_batch_set_U(lskum_batch* b, int32_t cond, const double* U, int on_devi
  * form and with direct gathers at 1, 2, 4, 8 lanes and keeps the fastest
  * (written to *sweep_lanes, *residual_lanes, *qgrad_lanes as lskum_params
  * values; any of the three may be NULL).  What the library chooses by itself is
- * among the candidates.  The batch's state is restored afterwards. */
+ * among the candidates and stays unless another is 3% faster.  The batch's state
+ * is restored afterwards. */
 int lskum_batch_autotune(lskum_batch* b, int32_t iters, int32_t* sweep_lanes,
                          int32_t* residual_lanes, int32_t* qgrad_lanes);
 
